@@ -536,9 +536,9 @@ int backward_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* p
   if (e != hipSuccess) return UG_ERR_HIP;
   {
     StageScope sc(plan, UG_STAGE_ACCUM_BWD, s);
-    e = launch_accum_bwd(plan->prm.tile_w, plan->prm.tile_h, ctrl, plan->d_tile_org, so.key, so.val, so.rec, at<Rec>(ws, L.recs),
-                         at<float>(ws, L.gq),
-                         at<float>(ws, L.partial), std::isfinite(plan->prm.chi2), plan->key_cap, s);
+    e = launch_accum_bwd(plan->prm.tile_w, plan->prm.tile_h, plan->d_tile_org, at<uint32_t>(ws, L.tile_start), so.key,
+                         so.val, so.rec, at<Rec>(ws, L.recs), at<float>(ws, L.gq), at<float>(ws, L.partial),
+                         std::isfinite(plan->prm.chi2), plan->num_tiles, plan->key_cap, s);
   }
   if (e != hipSuccess) return UG_ERR_HIP;
   {

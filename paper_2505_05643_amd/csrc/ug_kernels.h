@@ -128,10 +128,10 @@ hipError_t launch_bwd_prep(int tile_w, int tile_h, const PlaneInt* pint, const u
                            const float* image, const float* second, bool mse, float scale, float* loss_part,
                            const float* dsave, float* gq, uint32_t num_tiles, hipStream_t s);
 // tile_org[t] = pixel origin of tile t, x0 | y0 << 16.
-hipError_t launch_accum_bwd(int tile_w, int tile_h, const Ctrl* ctrl, const uint32_t* tile_org,
-                            const uint32_t* skey, const uint32_t* sval,
-                            const uint32_t* srec, const Rec* recs,
-                            const float* gq, float* partial, bool cut, uint32_t key_cap, hipStream_t s);
+hipError_t launch_accum_bwd(int tile_w, int tile_h, const uint32_t* tile_org, const uint32_t* tile_start,
+                            const uint32_t* skey, const uint32_t* sval, const uint32_t* srec, const Rec* recs,
+                            const float* gq, float* partial, bool cut, uint32_t num_tiles, uint32_t key_cap,
+                            hipStream_t s);
 
 // ---- training helpers (ug_train.hip)
 hipError_t launch_mse(const float* image, const float* target, int64_t m, float* d_image, float* loss,

@@ -16,11 +16,13 @@
 // list: per pixel-record pair two FMAs give the exponent, one compare
 // applies the cut-off and one v_exp_f32 gives the weight.
 //
-// Adjoint: a wave takes 64 keys and expands them into (key, sub-block)
-// items through an LDS queue in key order; lanes = items, each walking its
-// 64 pixels and accumulating the record's seven partial derivatives in
-// registers.  The items of a key are summed in sub-block order into the
-// key's partial, so no atomic is needed and the result is deterministic.
+// Adjoint: a block takes keys of one tile, four waves of up to 64 at a time,
+// and expands them into (key, four-column strip) items; lanes = items, each
+// walking its strip's rows and accumulating the record's seven partial
+// derivatives in registers.  The items of a key are summed in strip order
+// into the key's partial, so no atomic is needed and the result is
+// deterministic.
+#include <algorithm>
 #include <cfloat>
 
 #include "ug_kernels.h"
@@ -308,328 +310,366 @@ __global__ __launch_bounds__(256) void k_bwd_prep(const PlaneInt* __restrict__ p
 }
 
 // ---------------------------------------------------------------- backward
-// A wave loads 64 keys.  Each key's touched 8x8 sub-blocks become items
-// (key, sub-block), queued in key order.  For every item a first pass over
-// the queue (lanes = items) finds the rows of its sub-block that can hold a
-// pixel inside the record's ellipse: row y can only if the larger of the
-// exponents at the strip's two end columns -- or the row exponent itself
-// when t1 changes sign across the strip -- passes the cut-off (t1 is
-// monotone along the row, so no pixel between the ends does better); the
-// first and last such rows bound the item.  Items are then ranked by their
-// row count, largest first, and the evaluation pass (lanes = items in that
-// order) walks 64 items with similar row counts together, each lane
-// accumulating the record's seven sums over its rows in registers into the
-// item's LDS slot.  Once a sub-chunk's items are done each key adds its
-// slots in sub-block order.  A sub-chunk is the longest run of the wave's
-// keys whose items fit the slots (at least one key: a key has at most 16
-// items).  Rows an item skips would only add exact zeros, so the sums are
-// those of walking all 64 pixels of every touched sub-block.
-constexpr int kBwdSlots = 192;
+// nsplit blocks of four waves per tile; each wave has a contiguous share of
+// the tile's keys and takes up to 64 of them per pass.  The block copies the
+// tile's gamma into LDS once (every row the evaluation reads comes from
+// there).
+//
+// A key's ellipse touches a range of four-column strips of the tile; each
+// becomes an item (key, strip over the whole tile height).  lanes = items: a
+// closed form gives the rows of the strip that can hold a pixel inside the
+// ellipse, and the pass's items are ranked by their row count over the whole
+// block, largest first.  The evaluation (lanes = items in that order, groups
+// of 64 taken by the waves as they get free) walks items with similar row
+// counts together, each lane summing its record's seven derivatives over its
+// rows in registers into the item's LDS slot; then each key adds its slots in
+// strip order.  Pixels an item skips would only add exact zeros, so the sums
+// are those of walking all pixels of the tile, and neither the order of the
+// ranks nor an atomic touches them: deterministic.
+//
+// Bound by its VALU issue: about 54 instructions per four-pixel row, three
+// quarters of the evaluated pixels inside the support (four-column strips
+// with trimmed rows; 0.57 with eight columns).  Ranking 64 keys' items (three
+// groups) left 0.62 of the evaluation's lanes at work, 256 keys' (eleven
+// groups) 0.85.  Measured, against (key, 8 x 8 sub-block) items ranked per
+// wave with the rows found by testing all eight: 33M keys of 32x16 tiles 2300
+// -> 1680 us (1,780 instead of 2,500 VALU instructions per 64 keys), 25M of
+// 16x16 1567 -> 1190 us, 160,000 of 16x32 28 -> 23 us.
+constexpr int kStrip = 4;  // columns per item
+// items of one wave's keys per pass: four blocks' LDS fit a CU (three with
+// the 9 KB of a 32 x 32 tile's gamma)
+__host__ __device__ constexpr int slots_wave(int tw, int th) { return tw * th <= 256 || tw * th > 512 ? 224 : 208; }
 
-template <int TW, int TH, bool GT>
-__global__ __launch_bounds__(256) void k_accum_bwd(const Ctrl* __restrict__ ctrl,
-                                                   const uint32_t* __restrict__ tile_org,
-                                                   const uint32_t* __restrict__ skey,
-                                                   const uint32_t* __restrict__ sval,
-                                                   const uint32_t* __restrict__ srec,
-                                                   const Rec* __restrict__ recs,
-                                                   const float2* __restrict__ gq, float4* __restrict__ partial,
-                                                   int kcut) {
-  constexpr int K = TW / kSubBlock, Q = K * (TH / kSubBlock);
+// Inclusive prefix sum over the wave's lanes.
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true);  // lane 15 of a row to the next
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true);  // lane 31 to the upper half
+  return x;
+}
+
+// What the item stage needs of a key.  The ellipse t1^2 + t2^2 <= d has at
+// column offset du from its centre the rows dv = -m du -/+ sqrt(D - E du^2)
+// with S = t12^2 + t22^2, m = t11 t12 / S, D = d / S, E = (t11 t22 / S)^2; its
+// bottom row sits at du = us (t1 = 0), its top row at -us.
+struct StripGeo {
+  float m, D, E, us;
+};
+
+// The key's StripGeo, its row padding py and the strips [sa, sa + return) of
+// a TW x TH tile its ellipse reaches.  The strips are the column counterpart
+// of strip_rows over the tile's rows: at row offset dv the ellipse spans
+// du = -(t12 / t11) dv -/+ sqrt(d - t22^2 dv^2) / t11, with its right end at
+// dvr and its left at -dvr.  Every bound is widened far above the float
+// rounding of these forms: d by 1e-4 (the cancellation near the ellipse's
+// ends), the offsets by 1e-3 of a pixel and more far from the centre.
+// Without a cut-off, or where a constant is not finite, every strip and row
+// passes; a record without support (d < 0, or d = -inf for a zero amplitude)
+// has no strip.
+template <int TW, int TH>
+__device__ __forceinline__ int key_strips(float t11, float t12, float t22, float d, float du0, float dv0, bool cut,
+                                          StripGeo& g, float& py, int& sa) {
+  const float iS = __builtin_amdgcn_rcpf(fmaf(t12, t12, t22 * t22));
+  const float i11 = __builtin_amdgcn_rcpf(t11), i22 = __builtin_amdgcn_rcpf(t22);
+  const float vext = __builtin_amdgcn_sqrtf(d) * i22, a = t12 * i11, dw = d * 1.0001f;
+  const float e = t11 * t22 * iS;
+  g.m = t11 * t12 * iS;
+  g.D = dw * iS;
+  g.E = e * e;
+  g.us = -a * vext;
+  py = fmaf(1e-5f, vext + fabsf(dv0), 2e-3f);
+  const float dvr = -t12 * vext * __builtin_amdgcn_sqrtf(iS);
+  const float pv = fmaf(2e-6f, fabsf(dv0), 1e-3f);
+  const float lo = -dv0 - pv, hi = ((float)(TH - 1) - dv0) + pv;
+  const float vr = __builtin_amdgcn_fmed3f(dvr, lo, hi), vl = __builtin_amdgcn_fmed3f(-dvr, lo, hi);
+  const float tr = t22 * vr, tl = t22 * vl;
+  const float qr = fmaf(-tr, tr, dw), ql = fmaf(-tl, tl, dw);
+  const float hr = __builtin_amdgcn_sqrtf(fmaxf(qr, 0.f)) * i11, hl = __builtin_amdgcn_sqrtf(fmaxf(ql, 0.f)) * i11;
+  const float ur = fmaf(-a, vr, hr), ul = fmaf(-a, vl, -hl);
+  const float px = fmaf(1e-5f, (ur - ul) + fabsf(du0), 2e-3f);
+  const float fa = fmaxf(floorf((ul + du0 - px) * (1.f / kStrip)), 0.f);
+  const float fz = fminf(floorf((ur + du0 + px) * (1.f / kStrip)), (float)(TW / kStrip - 1));
+  const bool any = qr >= 0.f && fz >= fa;  // qr < 0: the tile's rows lie beside the ellipse
+  sa = any ? (int)fa : 0;
+  int ns = any ? (int)fz - sa + 1 : 0;
+  // finite and far from overflow: m du and E du^2 stay finite over any tile
+  const bool fin = fabsf(g.m) < 1e12f && g.D < 1e30f && g.E < 1e24f && fabsf(g.us) < 1e12f && py < 1e12f &&
+                   fabsf(a) < 1e12f && fabsf(dvr) < 1e12f;
+  if (!cut || !fin) {
+    g.m = g.D = g.E = g.us = 0.f;
+    py = INFINITY;
+    sa = 0;
+    ns = TW / kStrip;
+  }
+  return d >= 0.f ? ns : 0;  // NaN: no pixel passes its cut-off either
+}
+
+// First row and number of rows (0: none) of the strip of kStrip columns from
+// tile column xa that can hold a pixel of the key's support.
+template <int TH>
+__device__ __forceinline__ int strip_rows(const StripGeo& g, float du0, float dv0, float py, float xa, int& ya) {
+  const float px = fmaf(2e-6f, fabsf(du0), 1e-3f);
+  const float lo = (xa - px) - du0, hi = fmaf(2.f, px, lo + (float)(kStrip - 1));
+  const float db = __builtin_amdgcn_fmed3f(g.us, lo, hi), dt = __builtin_amdgcn_fmed3f(-g.us, lo, hi);
+  const float qb = fmaf(-g.E * db, db, g.D), qt = fmaf(-g.E * dt, dt, g.D);
+  const float vb = fmaf(-g.m, db, __builtin_amdgcn_sqrtf(fmaxf(qb, 0.f)));
+  const float vt = fmaf(-g.m, dt, -__builtin_amdgcn_sqrtf(fmaxf(qt, 0.f)));
+  const float fa = fmaxf(ceilf((vt + dv0) - py), 0.f);
+  const float fb = fminf(floorf((vb + dv0) + py), (float)(TH - 1));
+  // qb < 0 with both clamped ends on one side: the strip lies beside the ellipse
+  const bool any = qb >= 0.f && fb >= fa;
+  ya = any ? (int)fa : 0;
+  return any ? (int)fb - ya + 1 : 0;
+}
+
+template <int TW, int TH>
+__global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
+    const uint32_t* __restrict__ tile_org, const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ skey,
+    const uint32_t* __restrict__ sval, const uint32_t* __restrict__ srec, const Rec* __restrict__ recs,
+    const float2* __restrict__ gq, float4* __restrict__ partial, int kcut, uint32_t num_tiles, uint32_t nsplit) {
   constexpr int kMaskShift = key_mask_shift(TW, TH);
-  static_assert(Q <= 16 && kBwdSlots >= Q && kBwdSlots <= 256, "sub-blocks per tile; slot ids fit a byte");
-  __shared__ float4 kpA[4][64];     // t11, t12, t22, -t11 du0
-  __shared__ float4 kpB[4][64];     // du0, dv0, d, s (the weight's scaled form)
-  __shared__ float kpC[4][64];      // c
-  __shared__ uint32_t kpT[4][64];   // tile
-  __shared__ uint32_t qoff[4][65];  // first item of each key
-  __shared__ uint32_t queue[4][kBwdSlots];   // key | sub-block << 6 | first row << 10 | rows << 13
-  __shared__ uint8_t order[4][kBwdSlots];    // items with rows, by row count (largest first)
-  __shared__ float slot[4][7][kBwdSlots];
-  // GT (tiles of at most 512 pixels, launches with many keys): each wave
-  // copies the gamma of its chunk's first tile (at most 4 KB) into LDS, and
-  // items of that tile (nearly all: a tile holds many chunks) read their
-  // rows there instead of through the L1, whose accesses otherwise set the
-  // kernel's pace.  It costs a wave per SIMD of occupancy (LDS), which
-  // small launches feel more than they gain; larger tiles would take too
-  // much LDS.  Without it every row is read from memory.
-  static_assert(!GT || TW * TH <= 512, "staged tile size");
-  constexpr bool kGT = GT;
-  constexpr int kGTQ = kGT ? TW * TH / 2 : 1;  // float4 per staged tile
-  constexpr int kGTL = (kGTQ + 63) / 64;       // of them per lane
-  __shared__ float4 gt[4][kGTQ];
-  const uint32_t n = ctrl->n_key_eff;
+  constexpr int kSlotsWave = slots_wave(TW, TH), kGroups = (kSlotsWave + 63) / 64;
+  constexpr int kMaxStrips = TW / kStrip;
+  // float4 per tile row of (gamma, gamma c_hat) in LDS: one more than it
+  // needs, so that the rows of a column strip start in different banks
+  constexpr int kRow = TW / 2 + 1;
+  static_assert(kMaxStrips <= 8 && TH <= 32 && kSlotsWave <= 256, "item fields");
+  __shared__ float4 gt[(TH + 1) * kRow];        // the tile's gamma, then a row of zeros
+  __shared__ float4 kpA[256];                   // t11, t12, t22, -t11 du0
+  __shared__ float4 kpB[256];                   // du0, dv0, d, c
+  __shared__ uint32_t bucket[TH + 1];           // items per row count
+  __shared__ uint32_t more[4];                  // whether the wave has keys left after the pass
+  __shared__ uint32_t grab;                     // next group of 64 items to evaluate
+  __shared__ uint32_t sorted[4 * kSlotsWave];   // slot | wave << 8 | key << 10 | strip << 18 | first row << 21 | rows << 26
+  // the items' sums; before a wave's items are evaluated its part holds what
+  // the item stage needs of its keys (read by the same wave only)
+  struct ItemStage {
+    float4 geo[64];                // StripGeo of the wave's keys
+    float py[64];                  // and their row padding
+    uint16_t queue[kSlotsWave];    // lane of the key | strip << 8
+  };
+  union Slots {
+    float f[7][kSlotsWave];
+    ItemStage in;
+  };
+  __shared__ Slots slot[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // all tiles' first parts, then their second ...: the blocks left without
+  // keys come last, instead of every few (which left the same CUs idle)
+  const uint32_t part = blockIdx.x / num_tiles, t = xcd_remap(blockIdx.x - part * num_tiles, num_tiles);
+  const uint32_t s = tile_start[t], n = tile_start[t + 1] - s;
+  // the waves' shares of the tile's keys, at least 32 each (fewer, fuller
+  // waves where a tile has few)
+  const uint32_t share = max((n + 4u * nsplit - 1u) / (4u * nsplit), 32u);
+  if (part * 4u * share >= n) return;  // uniform: no keys left for this block
+  if (threadIdx.x <= TH) bucket[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) grab = 0u;
+  const uint32_t org = tile_org[t];  // x0 | y0 << 16
+  const int x0 = (int)(org & 0xffffu), y0 = (int)(org >> 16);
   const float ln2 = (float)kLn2;
   const bool cut = kcut != kNoCutBits;
-  // rows pass the pre-pass test iff their best pixel is in the support;
-  // without a cut-off only zero-amplitude records (d = -inf) fail it
-  const float thr = cut ? 0.f : -FLT_MAX;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t nchunks = (n + 63u) / 64u;
-  const uint32_t W = gridDim.x * 4u;
-  const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x) * 4u + (uint32_t)wave;
-  // The wave's chunks are fetched two ahead: while a chunk is processed,
-  // the records and tile origins of the wave's next chunk (a random gather)
-  // and the key words and record ids of the one after are in flight.  Lanes
-  // past the last key read record 0 and tile 0 (both exist whenever there
-  // is a key) and are masked off.
-  const uint32_t kmask = (1u << kMaskShift) - 1u;
-  auto fetch_keys = [&](uint32_t ch, uint32_t& kw, uint32_t& r) {
-    const uint32_t j = ch * 64u + (uint32_t)lane;
-    kw = j < n ? skey[j] : 0u;
-    r = j < n ? srec[j] : 0u;
+  uint32_t k = min((part * 4u + (uint32_t)wave) * share, n);  // the wave's next key
+  const uint32_t ke = min(k + share, n);                      // its last
+  // A pass's keys are loaded during the pass before it, and their records (a
+  // random 64-byte gather per key) before that pass's evaluation.  Lanes past
+  // the wave's keys read the tile's last key and are masked off.
+  uint32_t kw, rid, eidx;
+  RecAcc A;
+  int ub, vb;
+  auto load_keys = [&]() {
+    const uint32_t j = s + min(k + (uint32_t)lane, n - 1u);
+    kw = skey[j];
+    rid = srec[j];
+    eidx = sval[j];
   };
-  uint32_t chunk = wid;
-  uint32_t kwN = 0u, rN = 0u, kwNN = 0u, rNN = 0u, orgN = 0u;
-  RecAcc AN{};
-  RecGeo GN{};
-  if (chunk < nchunks) {
-    fetch_keys(chunk, kwN, rN);
-    AN = recs[rN].acc;
-    GN = recs[rN].geo;
-    orgN = tile_org[kwN & kmask];
-    fetch_keys(chunk + W, kwNN, rNN);
+  auto load_recs = [&]() {
+    A = recs[rid].acc;
+    ub = recs[rid].geo.ub;
+    vb = recs[rid].geo.vb;
+  };
+  load_keys();
+  {
+    // the tile's gamma is in flight with the first keys and records
+    constexpr int kTile = TH * (TW / 2), kPer = (kTile + 255) / 256;
+    const float4* __restrict__ src = reinterpret_cast<const float4*>(gq + (size_t)t * (TW * TH));
+    float4 v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) v[i] = src[min((int)threadIdx.x + 256 * i, kTile - 1)];
+    load_recs();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int j = (int)threadIdx.x + 256 * i;
+      if (j < kTile) gt[j / (TW / 2) * kRow + j % (TW / 2)] = v[i];
+    }
+    if (threadIdx.x < kRow) gt[TH * kRow + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  for (; chunk < nchunks; chunk += W) {
-    // ---- the chunk's keys; item offsets in key order
-    const uint32_t i = chunk * 64u + (uint32_t)lane;
-    const bool act = i < n;
-    uint32_t eidx = act ? sval[i] : 0u;  // where the key's partial goes
-    const uint32_t m = act ? kwN >> kMaskShift : 0u;
-    // the staged tile: lane 0's key's (the wave's LDS syncs below order
-    // these writes before the evaluation reads them)
-    const uint32_t t0 = __builtin_amdgcn_readfirstlane(kwN & kmask);
-    if constexpr (kGT) {
-      const float4* __restrict__ src = reinterpret_cast<const float4*>(gq + (size_t)t0 * (TW * TH));
+  __syncthreads();  // gt, bucket and grab are ready
+  for (;;) {
+    const uint32_t dst = eidx, left = ke - k;
+    // a pass takes an even part of what is left, at most 64 keys
+    const uint32_t want = left > 64u ? (left + (left + 63u) / 64u - 1u) / ((left + 63u) / 64u) : left;
+    const float du0 = (float)(ub - x0) + A.fu, dv0 = (float)(vb - y0) + A.fv;
+    const WeightScale ws = weight_scale(A.e0, A.emin, cut);
+    ItemStage& in = slot[wave].in;
+    int sa;
+    uint32_t pc;  // the key's items
+    {
+      StripGeo g;
+      float py;
+      const int ns = key_strips<TW, TH>(A.t11, A.t12, A.t22, ws.d, du0, dv0, cut, g, py, sa);
+      pc = (uint32_t)lane < want && (kw >> kMaskShift) != 0u ? (uint32_t)ns : 0u;
+      kpA[threadIdx.x] = make_float4(A.t11, A.t12, A.t22, -A.t11 * du0);
+      kpB[threadIdx.x] = make_float4(du0, dv0, ws.d, A.c);
+      in.geo[lane] = make_float4(g.m, g.D, g.E, g.us);
+      in.py[lane] = py;
+    }
+    const float t11k = A.t11, t12k = A.t12, t22k = A.t22;
+    uint32_t off = 0u;  // the key's first item
 #pragma unroll
-      for (int j = 0; j < kGTL; ++j)
-        if (j * 64 + lane < kGTQ) gt[wave][j * 64 + lane] = src[j * 64 + lane];
-    }
-    if (act) {
-      const uint32_t t = kwN & kmask;
-      const RecAcc A = AN;
-      const RecGeo Gg = GN;
-      const uint32_t org = orgN;  // x0 | y0 << 16
-      const int x0 = (int)(org & 0xffffu), y0 = (int)(org >> 16);
-      const float du0 = (float)(Gg.ub - x0) + A.fu;
-      const float dv0 = (float)(Gg.vb - y0) + A.fv;
-      const WeightScale ws = weight_scale(A.e0, A.emin, cut);
-      kpA[wave][lane] = make_float4(A.t11, A.t12, A.t22, -A.t11 * du0);
-      kpB[wave][lane] = make_float4(du0, dv0, ws.d, ws.s);
-      kpC[wave][lane] = A.c;
-      kpT[wave][lane] = t;
-    }
-    const uint32_t pop = (uint32_t)__popc(m);
-    uint32_t x = pop;
+    for (int bit = 0; bit < 4; ++bit) off += lanemask_lt_popc(__ballot((pc >> bit) & 1u)) << bit;
+    // the leading keys whose items fit the slots (nearly always all of them)
+    const bool mine = (uint32_t)lane < want && off + pc <= (uint32_t)kSlotsWave;
+    const uint32_t took = (uint32_t)__popcll(__ballot(mine));
+    if (!mine) pc = 0u;
+    const uint32_t L = (uint32_t)__builtin_amdgcn_readlane((int)(off + pc), (int)(took ? took - 1u : 0u));
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    const uint32_t off = x - pop;
-    qoff[wave][lane] = off;
-    if (lane == 63) qoff[wave][64] = x;
-    // the next chunk's records (its keys arrived during the previous chunk)
-    // and the keys of the one after
-    AN = recs[rNN].acc;
-    GN = recs[rNN].geo;
-    orgN = tile_org[kwNN & kmask];
-    kwN = kwNN;
-    fetch_keys(chunk + 2u * W, kwNN, rNN);
+    for (uint32_t i = 0; i < kMaxStrips; ++i)
+      if (i < pc) in.queue[off + i] = (uint16_t)((uint32_t)lane | ((uint32_t)sa + i) << 8);
+    k += took;
+    if (lane == 0) more[wave] = ke - k;
+    if (k < ke) load_keys();
     wave_lds_sync();
-    float acc[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < 64;) {
-      // ---- the sub-chunk: keys [k0, k1) whose items fit the slots
-      const uint32_t base = qoff[wave][k0];
-      const bool fits = lane >= k0 && qoff[wave][lane + 1] - base <= (uint32_t)kBwdSlots;
-      const int k1 = k0 + (int)__popcll(__ballot(fits));
-      const uint32_t L = qoff[wave][k1] - base;
-      if (lane >= k0 && lane < k1) {
-        uint32_t mm = m;
-        uint32_t q = off - base;
-        while (mm) {
-          const uint32_t sb = (uint32_t)__builtin_ctz(mm);
-          queue[wave][q++] = (uint32_t)lane | sb << 6;
-          mm &= mm - 1u;
-        }
+    // ---- lanes = items: the rows each can reach, ranked by their count (an
+    // item without rows is ranked last and its sums come out as zeros)
+    uint32_t ent[kGroups], rank[kGroups];
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+      ent[i] = 0u;
+      rank[i] = 0xffffffffu;
+      const uint32_t q = (uint32_t)(i * 64 + lane);
+      if (q < L) {
+        const uint32_t e = in.queue[q];
+        const int kl = (int)(e & 63u);
+        const float4 kb = kpB[wave * 64 + kl], kd = in.geo[kl];
+        int ya;
+        const int nr = strip_rows<TH>(StripGeo{kd.x, kd.y, kd.z, kd.w}, kb.x, kb.y, in.py[kl],
+                                      (float)((e >> 8) * kStrip), ya);
+        ent[i] = q | (uint32_t)wave << 8 | (e | (uint32_t)wave << 6) << 10 | (uint32_t)ya << 21 | (uint32_t)nr << 26;
+        rank[i] = atomicAdd(&bucket[nr], 1u);
       }
-      wave_lds_sync();
-      // ---- lanes = items: the rows each item can reach; counts per row count
-      uint32_t bucket_tot[kSubBlock + 1];
-#pragma unroll
-      for (int b = 0; b <= kSubBlock; ++b) bucket_tot[b] = 0u;
-      for (uint32_t q0 = 0; q0 < L; q0 += 64) {
-        const uint32_t q = q0 + (uint32_t)lane;
-        const bool has = q < L;
-        const uint32_t ent = has ? queue[wave][q] : (uint32_t)k0;
-        const int kl = (int)(ent & 63u), sb = (int)((ent >> 6) & 15u);
-        const float4 a = kpA[wave][kl];
-        const float4 b = kpB[wave][kl];
-        const float xa = (float)((sb % K) * kSubBlock);
-        const int by = (sb / K) * kSubBlock;
-        uint32_t rows = 0u;
-#pragma unroll
-        for (int y = 0; y < kSubBlock; ++y) {
-          const float dv = (float)(by + y) - b.y;
-          const float B = fmaf(a.y, dv, a.w);
-          const float t2 = a.z * dv;
-          const float erow = fmaf(-t2, t2, b.z);
-          // t1 at the strip's end columns, as the evaluation forms them; the
-          // median of (ta, 0, tb) is the end value nearest zero, or zero when
-          // t1 changes sign in between
-          const float ta = fmaf(a.x, xa, B), tb = fmaf(a.x, (float)(kSubBlock - 1), ta);
-          const float tm = __builtin_amdgcn_fmed3f(ta, 0.f, tb);
-          rows |= (fmaf(-tm, tm, erow) >= thr ? 1u : 0u) << y;
-        }
-        const int ya = rows ? __builtin_ctz(rows) : 0, yb = rows ? 31 - __builtin_clz(rows) : -1;
-        const int nr = has && rows ? yb - ya + 1 : 0;
-        if (has) {
-          queue[wave][q] = ent | (uint32_t)(nr ? ya : 0) << 10 | (uint32_t)nr << 13;
-          if (nr == 0) {  // no pixel of the sub-block is inside: its sums are zero
-#pragma unroll
-            for (int f = 0; f < 7; ++f) slot[wave][f][q] = 0.f;
-          }
-        }
-#pragma unroll
-        for (int r = 1; r <= kSubBlock; ++r) bucket_tot[r] += (uint32_t)__popcll(__ballot(nr == r));
-      }
-      // bucket starts, largest row count first
-      uint32_t bstart[kSubBlock + 1];
-      uint32_t run = 0u;
-#pragma unroll
-      for (int r = kSubBlock; r >= 1; --r) {
-        bstart[r] = run;
-        run += bucket_tot[r];
-      }
-      const uint32_t Ls = run;  // items with rows
-      wave_lds_sync();
-      for (uint32_t q0 = 0; q0 < L; q0 += 64) {
-        const uint32_t q = q0 + (uint32_t)lane;
-        const uint32_t nr = q < L ? queue[wave][q] >> 13 : 0u;
-        uint32_t pos = 0u;
-#pragma unroll
-        for (int r = 1; r <= kSubBlock; ++r) {
-          const unsigned long long bal = __ballot(nr == (uint32_t)r);
-          if (nr == (uint32_t)r) pos = bstart[r] + lanemask_lt_popc(bal);
-          bstart[r] += (uint32_t)__popcll(bal);
-        }
-        if (nr) order[wave][pos] = (uint8_t)q;
-      }
-      wave_lds_sync();
-      // ---- lanes = items by row count: the rows of one key's sub-block
-      for (uint32_t s0 = 0; s0 < Ls; s0 += 64) {
-        const uint32_t sidx = s0 + (uint32_t)lane;
-        const bool has = sidx < Ls;
-        const uint32_t q = has ? (uint32_t)order[wave][sidx] : 0u;
-        const uint32_t ent = has ? queue[wave][q] : (uint32_t)k0;
-        const int kl = (int)(ent & 63u), sb = (int)((ent >> 6) & 15u);
-        const int ry = (int)((ent >> 10) & 7u), nr = has ? (int)(ent >> 13) : 0;
-        const float4 a = kpA[wave][kl];
-        const float4 b = kpB[wave][kl];
-        const float c = kpC[wave][kl];
-        const uint32_t t = kpT[wave][kl];
-        const float t11 = a.x, t12 = a.y, t22 = a.z, P = a.w;
-        const float d = b.z;
-        const int bx0 = (sb % K) * kSubBlock, by = (sb / K) * kSubBlock + ry;
-        const float bxf = (float)bx0;
-        const float4* __restrict__ pq = reinterpret_cast<const float4*>(gq + (size_t)t * (TW * TH) + by * TW + bx0);
-        const bool staged = kGT && t == t0;
-        const int gbase = by * (TW / 2) + bx0 / 2;  // the item's first row in the staged tile (float4)
-        float Sge = 0.f, Sa = 0.f, Sau = 0.f, S12 = 0.f, S22 = 0.f, Sb = 0.f, Sdc = 0.f;
-        // row y of the item for y < nr; later rows (and lanes without an
-        // item) re-read the item's last row (or the key's first) with a
-        // row exponent of -inf, so they add exact zeros.  The loop ends
-        // once no lane of the wave has rows left.  Each row's gamma is
-        // loaded at the row's start: with four waves per SIMD the wait is
-        // mostly hidden, and loading it a row ahead measured slower.
-        const int nlast = nr > 0 ? nr - 1 : 0;
-#pragma unroll
-        for (int y = 0; y < kSubBlock; ++y) {
-          if (!__any(y < nr)) break;  // uniform
-          const int yl = y < nlast ? y : nlast;
-          float4 cur[kSubBlock / 2];
-          if (staged) {
-#pragma unroll
-            for (int x2 = 0; x2 < kSubBlock / 2; ++x2) cur[x2] = gt[wave][gbase + yl * (TW / 2) + x2];
-          } else {
-#pragma unroll
-            for (int x2 = 0; x2 < kSubBlock / 2; ++x2) cur[x2] = pq[yl * (TW / 2) + x2];
-          }
-          const float dv = (float)(by + y) - b.y;
-          const float B0 = fmaf(t11, bxf, fmaf(t12, dv, P));  // t1 at the strip's first column
-          const float t2 = t22 * dv;
-          const float erow = y < nr ? fmaf(-t2, t2, d) : -INFINITY;
-          // per row: sum ge, sum ge j, sum ge j^2 over the strip's columns
-          // j = 0..7; with t1 = B0 + t11 j the row's sum ge t1 and sum ge t1 x
-          // (x = bx0 + j) follow from them, which saves the per-pixel
-          // product ge t1 and the sums over it
-          float rge = 0.f, rj = 0.f, rjj = 0.f;
-#pragma unroll
-          for (int x2 = 0; x2 < kSubBlock / 2; ++x2) {
-            const float4 gg2 = cur[x2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const int j = 2 * x2 + h;
-              const float gx = h ? gg2.z : gg2.x, gy = h ? gg2.w : gg2.y;
-              const float t1 = j ? fmaf(t11, (float)j, B0) : B0;
-              const float w = fast_exp2(support_clamp(fmaf(-t1, t1, erow), kcut));  // the weight over s
-              const float gw = fmaf(gx, c, -gy);  // dL/dw = gamma (c - c_hat)
-              const float ge = w * gw;
-              rge += ge;
-              Sdc = fmaf(gx, w, Sdc);
-              if (j) {
-                rj = fmaf(ge, (float)j, rj);
-                rjj = fmaf(ge, (float)(j * j), rjj);
-              }
-            }
-          }
-          const float ra = fmaf(t11, rj, B0 * rge);  // sum ge t1
-          Sau = fmaf(bxf, ra, Sau);                   // + sum ge t1 x = bx0 ra + t11 rjj + B0 rj
-          Sau = fmaf(t11, rjj, Sau);
-          Sau = fmaf(B0, rj, Sau);
-          Sge += rge;
-          Sa += ra;
-          S12 = fmaf(dv, ra, S12);
-          Sb = fmaf(t2, rge, Sb);
-          S22 = fmaf(t2 * dv, rge, S22);
-        }
-        if (has) {
-          slot[wave][0][q] = Sge;
-          slot[wave][1][q] = Sa;
-          slot[wave][2][q] = Sau;
-          slot[wave][3][q] = S12;
-          slot[wave][4][q] = S22;
-          slot[wave][5][q] = Sb;
-          slot[wave][6][q] = Sdc;
-        }
-      }
-      wave_lds_sync();
-      // ---- each key adds its items in sub-block order
-      if (lane >= k0 && lane < k1) {
-        const uint32_t q1 = off - base + pop;
-        for (uint32_t q = off - base; q < q1; ++q) {
-#pragma unroll
-          for (int f = 0; f < 7; ++f) acc[f] += slot[wave][f][q];
-        }
-      }
-      wave_lds_sync();  // the next sub-chunk rewrites the queue and the slots
-      k0 = k1;
     }
-    if (act) {
-      const float4 a = kpA[wave][lane];
-      const float du0 = kpB[wave][lane].x, sw = kpB[wave][lane].w;
+    __syncthreads();
+    // first rank of every row count, largest first (lane l: TH - l rows)
+    const uint32_t bv = lane <= TH ? bucket[TH - lane] : 0u;
+    const uint32_t bx = wave_incl_sum(bv);
+    const uint32_t Ls = (uint32_t)__builtin_amdgcn_readlane((int)bx, 63);  // items of the pass
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+      const uint32_t f = __shfl(bx - bv, TH - (int)(ent[i] >> 26), 64);
+      if (rank[i] != 0xffffffffu) sorted[f + rank[i]] = ent[i];
+    }
+    const bool again = (more[0] | more[1] | more[2] | more[3]) != 0u;
+    __syncthreads();
+    if (threadIdx.x <= TH) bucket[threadIdx.x] = 0u;
+    if (k < ke) load_recs();  // in flight during the evaluation
+    // ---- lanes = items by row count: the rows of one key's strip.  Each wave
+    // takes the next group of 64 when it is done with its last one.
+    for (;;) {
+      uint32_t taken = 0u;
+      if (lane == 0) taken = atomicAdd(&grab, 1u);
+      const uint32_t s0 = 64u * __builtin_amdgcn_readfirstlane(taken);
+      if (s0 >= Ls) break;
+      const bool has = s0 + (uint32_t)lane < Ls;
+      const uint32_t e = has ? sorted[s0 + (uint32_t)lane] : 0u;
+      const int kl = (int)((e >> 10) & 255u), st = (int)((e >> 18) & 7u), by = (int)((e >> 21) & 31u);
+      const int nr = (int)(e >> 26);  // 0 for a lane without an item
+      const float4 ka = kpA[kl];
+      const float4 kb = kpB[kl];
+      const float t11 = ka.x, t12 = ka.y, t22 = ka.z, P = ka.w;
+      const float dvo = kb.y, d = kb.z, c = kb.w;
+      const float bxf = (float)((st >> 1) * kSubBlock);  // the sub-block's first column
+      // t1 as over the whole sub-block: B0 at its first column, column j
+      // from there at B0 + t11 j, j = 0..3 or 4..7
+      const float j0 = (float)((st & 1) * kStrip);
+      const float j1 = j0 + 1.f, j2 = j0 + 2.f, j3 = j0 + 3.f;
+      float rowf = (float)by;
+      int at = (by * kRow + st * (kStrip / 2)) * (int)sizeof(float4);
+      const int stop = at + nr * kRow * (int)sizeof(float4);  // rows past the item's read zeros: they add exact zeros
+      const int nmax = __builtin_amdgcn_readfirstlane(nr);  // the group's first item has the most rows
+      float Sge = 0.f, Sa = 0.f, Sau = 0.f, S12 = 0.f, S22 = 0.f, Sb = 0.f, Sdc = 0.f;
+      for (int r = 0; r < nmax; ++r) {
+        const float4* row = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(gt) +
+                                                            (at < stop ? at : TH * kRow * (int)sizeof(float4)));
+        const float4 g0 = row[0], g1 = row[1];
+        at += kRow * (int)sizeof(float4);
+        const float dv = rowf - dvo;
+        rowf += 1.f;
+        const float B0 = fmaf(t11, bxf, fmaf(t12, dv, P));
+        const float t2 = t22 * dv;
+        const float erow = fmaf(-t2, t2, d);
+        const float ta = fmaf(t11, j0, B0), tb = fmaf(t11, j1, B0), tc = fmaf(t11, j2, B0), td = fmaf(t11, j3, B0);
+        // weights over s; dL/dw = gamma (c - c_hat)
+        const float wa = fast_exp2(support_clamp(fmaf(-ta, ta, erow), kcut));
+        const float wb = fast_exp2(support_clamp(fmaf(-tb, tb, erow), kcut));
+        const float wc = fast_exp2(support_clamp(fmaf(-tc, tc, erow), kcut));
+        const float wd = fast_exp2(support_clamp(fmaf(-td, td, erow), kcut));
+        const float ga = wa * fmaf(g0.x, c, -g0.y), gb = wb * fmaf(g0.z, c, -g0.w);
+        const float gc = wc * fmaf(g1.x, c, -g1.y), gd = wd * fmaf(g1.z, c, -g1.w);
+        Sdc = fmaf(g0.x, wa, Sdc);
+        Sdc = fmaf(g0.z, wb, Sdc);
+        Sdc = fmaf(g1.x, wc, Sdc);
+        Sdc = fmaf(g1.z, wd, Sdc);
+        // the row's sums of ge, ge i, ge i^2 over i = 0..3; with t1 = ta +
+        // t11 i they give its sums of ge t1 and ge t1 i
+        const float rge = (ga + gb) + (gc + gd);
+        const float rj = fmaf(3.f, gd, fmaf(2.f, gc, gb));
+        const float rjj = fmaf(9.f, gd, fmaf(4.f, gc, gb));
+        const float ra = fmaf(t11, rj, ta * rge);
+        Sau = fmaf(t11, rjj, Sau);
+        Sau = fmaf(ta, rj, Sau);
+        Sge += rge;
+        Sa += ra;
+        S12 = fmaf(dv, ra, S12);
+        const float u = t2 * rge;
+        Sb += u;
+        S22 = fmaf(dv, u, S22);
+      }
+      if (has) {
+        float* o = &slot[(e >> 8) & 3u].f[0][e & 255u];
+        o[0 * kSlotsWave] = Sge;
+        o[1 * kSlotsWave] = Sa;
+        o[2 * kSlotsWave] = fmaf((float)(st * kStrip), Sa, Sau);  // sum ge t1 x, x the tile column
+        o[3 * kSlotsWave] = S12;
+        o[4 * kSlotsWave] = S22;
+        o[5 * kSlotsWave] = Sb;
+        o[6 * kSlotsWave] = Sdc;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) grab = 0u;  // every wave has left the loop above
+    // ---- each key adds its items in strip order
+    float acc[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (uint32_t i = 0; i < kMaxStrips; ++i) {
+      if (i < pc) {
+#pragma unroll
+        for (int f = 0; f < 7; ++f) acc[f] += slot[wave].f[f][off + i];
+      }
+    }
+    if (mine) {
       // every sum is linear in the weights: scale them back by s once
-      const float Sge = acc[0] * sw, Sa = acc[1] * sw, Sau = acc[2] * sw, S12 = acc[3] * sw, S22 = acc[4] * sw,
-                  Sb = acc[5] * sw, Sdc = acc[6] * sw;
+      const float Sge = acc[0] * ws.s, Sa = acc[1] * ws.s, Sau = acc[2] * ws.s, S12 = acc[3] * ws.s,
+                  S22 = acc[4] * ws.s, Sb = acc[5] * ws.s, Sdc = acc[6] * ws.s;
       // w = 2^(e0 - t1^2 - t2^2):  dL/ds = -ln2 w dL/dw, s = t1^2 + t2^2.
       const float k2 = 2.f * ln2;
-      // keeps the address arithmetic here: moved up beside the load, it
-      // would wait for it at the chunk's start
-      asm volatile("" : "+v"(eidx));
-      partial[2 * (size_t)eidx] = make_float4(-k2 * (Sau - du0 * Sa), -k2 * S12, -k2 * S22, k2 * a.x * Sa);
-      partial[2 * (size_t)eidx + 1] = make_float4(k2 * (a.y * Sa + a.z * Sb), ln2 * Sge, Sdc, 0.f);
+      partial[2 * (size_t)dst] = make_float4(-k2 * (Sau - du0 * Sa), -k2 * S12, -k2 * S22, k2 * t11k * Sa);
+      partial[2 * (size_t)dst + 1] = make_float4(k2 * (t12k * Sa + t22k * Sb), ln2 * Sge, Sdc, 0.f);
     }
-    wave_lds_sync();  // the next chunk rewrites this wave's LDS
+    if (!again) break;  // uniform over the block
+    wave_lds_sync();    // the next pass's item stage takes the slots' place
   }
 }
 
@@ -730,38 +770,31 @@ hipError_t launch_bwd_prep(int tile_w, int tile_h, const PlaneInt* pint, const u
   return hipErrorInvalidValue;
 }
 
-// Launches with at least this key capacity (about 100,000 64-key chunks)
-// stage their chunks' gamma tiles in LDS when the tile fits.
-constexpr uint32_t kGTMinKeys = 1u << 22;
+// Blocks per tile: about 1,024 keys each (four passes of a block, so its
+// start-up is a small part; measured at 3,700 keys per tile: one block per
+// tile 787 us, four 739, sixteen 824), and where that leaves fewer than 1,024
+// blocks (four per CU) down to 128 keys each (84 tiles of 1,025 keys: one
+// block per tile 41 us, eight 13; 600 tiles of 150: one 11, two 15).
+constexpr uint32_t kBwdBlockKeys = 1024, kBwdMinBlocks = 1024, kBwdMinKeys = 128;
 
-template <int TW, int TH>
-static hipError_t bwd_launch(bool gt, uint32_t blocks, hipStream_t s, const Ctrl* ctrl, const uint32_t* tile_org,
-                             const uint32_t* skey, const uint32_t* sval, const uint32_t* srec, const Rec* recs,
-                             const float2* g2, float4* p4, int kcut) {
-  if constexpr (TW * TH <= 512) {
-    if (gt) {
-      hipLaunchKernelGGL((k_accum_bwd<TW, TH, true>), dim3(blocks), dim3(256), 0, s, ctrl, tile_org, skey, sval,
-                         srec, recs, g2, p4, kcut);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((k_accum_bwd<TW, TH, false>), dim3(blocks), dim3(256), 0, s, ctrl, tile_org, skey, sval, srec,
-                     recs, g2, p4, kcut);
-  return hipGetLastError();
-}
-
-hipError_t launch_accum_bwd(int tile_w, int tile_h, const Ctrl* ctrl, const uint32_t* tile_org,
-                            const uint32_t* skey, const uint32_t* sval,
-                            const uint32_t* srec, const Rec* recs,
-                            const float* gq, float* partial, bool cut, uint32_t key_cap, hipStream_t s) {
+hipError_t launch_accum_bwd(int tile_w, int tile_h, const uint32_t* tile_org, const uint32_t* tile_start,
+                            const uint32_t* skey, const uint32_t* sval, const uint32_t* srec, const Rec* recs,
+                            const float* gq, float* partial, bool cut, uint32_t num_tiles, uint32_t key_cap,
+                            hipStream_t s) {
   const float2* g2 = reinterpret_cast<const float2*>(gq);
   float4* p4 = reinterpret_cast<float4*>(partial);
-  uint32_t want = (key_cap / 64u + 4u) / 4u;
-  const uint32_t blocks = want < 1u ? 1u : (want > 16384u ? 16384u : want);
-  const bool gt = key_cap >= kGTMinKeys;
-#define UG_BWD(W, H)                                                                                          \
-  if (tile_w == W && tile_h == H) return bwd_launch<W, H>(gt, blocks, s, ctrl, tile_org, skey, sval, srec, recs, \
-                                                          g2, p4, cut ? kCutBits : kNoCutBits);
+  if (num_tiles == 0) return hipSuccess;
+  const uint32_t avg = key_cap / num_tiles;
+  const uint32_t fill = std::min((kBwdMinBlocks + num_tiles - 1u) / num_tiles, avg / kBwdMinKeys);
+  const uint32_t nsplit = std::max(std::max(avg / kBwdBlockKeys, fill), 1u);
+  const dim3 grid(num_tiles * nsplit);
+  const int kcut = cut ? kCutBits : kNoCutBits;
+#define UG_BWD(W, H)                                                                                           \
+  if (tile_w == W && tile_h == H) {                                                                            \
+    hipLaunchKernelGGL((k_accum_bwd<W, H>), grid, dim3(256), 0, s, tile_org, tile_start, skey, sval, srec, recs, \
+                       g2, p4, kcut, num_tiles, nsplit);                                                                  \
+    return hipGetLastError();                                                                                  \
+  }
   UG_TILE_SHAPES(UG_BWD)
 #undef UG_BWD
   return hipErrorInvalidValue;
