@@ -370,8 +370,10 @@ int64_t ug_debug_records(const ug_plan *plan, const void *workspace, ug_record *
 /* ---- test hook: the tile binning of the last render ---------------------- */
 
 /* Copies the keys of the last gather render as the radix sort left them
- * (Section 4.4 binning: one key per (record, touched tile), sorted by tile
- * id, stably, so a tile's keys keep the order in which they were emitted)
+ * (Section 4.4 binning: one key per (record, touched tile) -- with
+ * UG_BOX_PAPER no key for the tiles of its box that the ellipse does not
+ * reach, though ug_plan_measure and ug_plan_status count those too -- sorted
+ * by tile id, stably, so a tile's keys keep the order in which they were emitted)
  * and the tile ranges derived from them:
  *   key_out[j]   key word: the tile id in its low 32 - Q bits, the tile's
  *                8 x 8 sub-block coverage mask in its top Q bits

@@ -173,6 +173,8 @@ RenderParams make_rp(const ug_plan* pl) {
   rp.tile_h = pl->prm.tile_h;
   rp.box_mode = pl->prm.box_mode;
   rp.box_support = (pl->prm.flags & UG_FLAG_BOX_SUPPORT) ? 1 : 0;
+  rp.by_rows = !rp.box_support && (rp.box_mode == UG_BOX_ROWS ||
+                                   (rp.box_mode == UG_BOX_PAPER && !(pl->prm.flags & UG_FLAG_SCATTER)));
   rp.n = pl->n;
   rp.p = pl->p;
   rp.num_tiles = pl->num_tiles;

@@ -212,8 +212,9 @@ __device__ __forceinline__ bool pixel_range(double centre, double half, int32_t 
 struct Footprint {
   RecAcc acc;
   RecGeo geo;
-  uint32_t keys;
-  uint32_t spans[kRowSpans];  // ROWS mode: as in Rec
+  uint32_t keys;              // keys emitted
+  uint32_t counted;           // keys reported and held against the capacity (the PAPER rectangle's tiles)
+  uint32_t spans[kRowSpans];  // by rows: as in Rec
 };
 
 // Column ranges of the record's ellipse over bands of pixel rows.  The
@@ -323,7 +324,7 @@ __device__ __forceinline__ uint32_t tile_mask(const int (&ua)[kMaxBands], const 
 // cost a few dozen instructions.
 __device__ __forceinline__ int tile_of(int px, int T) { return px >> (31 - __builtin_clz((unsigned)T)); }
 
-// Tiles [tx0, tx1] of tile row ty that a ROWS-mode record covers: those under
+// Tiles [tx0, tx1] of tile row ty that a record binned by rows covers: those under
 // the column range of the ellipse over the whole tile row; false if none.
 __device__ __forceinline__ bool rows_span(const BandPrep& bp, int ty, int TW, int TH, int H, int umin, int umax,
                                           int& tx0, int& tx1) {
@@ -335,7 +336,7 @@ __device__ __forceinline__ bool rows_span(const BandPrep& bp, int ty, int TW, in
   return true;
 }
 
-// Key count of a ROWS-mode record over its tile rectangle (rows_span summed
+// Key count of a record binned by rows over its tile rectangle (rows_span summed
 // over its tile rows), and the spans of its first kRowSpans tile rows.
 __device__ __forceinline__ uint32_t rows_count(const RecAcc& ra, const RecGeo& geo, int W, int H, int TW, int TH,
                                                uint32_t (&spans)[kRowSpans]) {
@@ -411,14 +412,18 @@ __device__ __forceinline__ bool make_box_record(const GaussIn& G, const PlaneCon
   f.geo.tx1 = (uint16_t)uhi;
   f.geo.ty0 = (uint16_t)vlo;
   f.geo.ty1 = (uint16_t)vhi;
-  f.keys = 0;
+  f.keys = f.counted = 0;
   return true;
 }
 
 // Record, tile rectangle and key count of an accepted pair (conic_full done).
-// Returns false if the footprint misses the image.
+// Returns false if the footprint misses the image.  by_rows: keys only for
+// the tiles the ellipse reaches.  PAPER rectangles hold a fair share of tiles
+// it does not (their mask would be empty): at 1M Gaussians and 256 planes of
+// 256^2 69M tiles of 16 x 16, 41M of them reached; counting them here costs
+// the record kernel less than emitting, sorting and skipping the rest.
 __device__ __forceinline__ bool make_footprint(const GaussIn& G, const PlaneConst& P, const PlaneInt& PI,
-                                               const Conic& k, double chi2, int box_mode, int TW, int TH,
+                                               const Conic& k, double chi2, int box_mode, bool by_rows, int TW, int TH,
                                                Footprint& f) {
   const double u0 = k.c1 / P.sx + P.cu;
   const double v0 = k.c2 / P.sy + P.cv;
@@ -440,12 +445,10 @@ __device__ __forceinline__ bool make_footprint(const GaussIn& G, const PlaneCons
   f.geo.tx1 = (uint16_t)tile_of(uhi, TW);
   f.geo.ty0 = (uint16_t)tile_of(vlo, TH);
   f.geo.ty1 = (uint16_t)tile_of(vhi, TH);
-  if (box_mode == UG_BOX_ROWS) {
-    f.keys = rows_count(f.acc, f.geo, PI.W, PI.H, TW, TH, f.spans);
-  } else {
-    f.keys = (uint32_t)(f.geo.tx1 - f.geo.tx0 + 1) * (uint32_t)(f.geo.ty1 - f.geo.ty0 + 1);
-  }
-  return f.keys > 0;
+  f.counted = (uint32_t)(f.geo.tx1 - f.geo.tx0 + 1) * (uint32_t)(f.geo.ty1 - f.geo.ty0 + 1);
+  f.keys = by_rows ? rows_count(f.acc, f.geo, PI.W, PI.H, TW, TH, f.spans) : f.counted;
+  if (box_mode == UG_BOX_ROWS) f.counted = f.keys;
+  return f.counted > 0;
 }
 
 // Adjoint of make_footprint's float record with respect to the Gaussian's

@@ -123,7 +123,7 @@ static_assert(sizeof(RecGeo) == 16, "RecGeo layout");
 // A record as stored: both parts in one 64-byte slot, so the accumulate
 // kernels' gathers (one record per key, in tile order: random in record
 // order) fetch one 64-byte segment per key instead of two.  The slot's last
-// 16 bytes carry, for ROWS-mode binning, the tile span of each of the
+// 16 bytes carry, for binning by rows, the tile span of each of the
 // record's first kRowSpans tile rows as counted by the record kernel
 // (tx0 | tx1 << 16; kNoSpan for a row the ellipse misses), so the emission
 // reuses them instead of recomputing them; unused in the other modes.
@@ -147,6 +147,7 @@ struct RenderParams {
   float beta, chi2, bg_alpha, bg_color;
   int32_t tile_w, tile_h, box_mode;
   int32_t box_support;  // paper-literal Phase-2 support (records carry pixel boxes)
+  int32_t by_rows;      // keys only for the tiles the ellipse reaches per tile row (box_mode ROWS, and PAPER gathers)
   int32_t n, p;
   uint32_t num_tiles;
   uint32_t rec_cap, key_cap;

@@ -422,17 +422,17 @@ __device__ __forceinline__ uint32_t record_rpb_dev(uint32_t nrec, uint32_t grid)
   return (per < 1u ? 1u : per) * 256u;
 }
 __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, const uint4& spans, const PlaneInt& PI,
-                                          int box_mode, int TW, int TH, uint32_t r, uint32_t e, uint32_t e_end,
+                                          bool by_rows, int TW, int TH, uint32_t r, uint32_t e, uint32_t e_end,
                                           uint32_t* __restrict__ key_tile, uint32_t* __restrict__ rec_of_key) {
   const int mshift = key_mask_shift(TW, TH);
   const int umin = geo.tx0 * TW;
   const int umax = min(geo.tx1 * TW + TW - 1, PI.W - 1);
   BandPrep bp;
   const bool ok = band_prep(ra, geo.ub, geo.vb, bp);
-  if (box_mode == UG_BOX_ROWS && !ok) return;
+  if (by_rows && !ok) return;
   for (int ty = geo.ty0; ty <= geo.ty1; ++ty) {
     int tx0 = geo.tx0, tx1 = geo.tx1;
-    if (box_mode == UG_BOX_ROWS) {
+    if (by_rows) {
       // the record kernel's span for the first kRowSpans rows, else recomputed
       const int i = ty - (int)geo.ty0;
       if (i < kRowSpans) {
@@ -484,10 +484,10 @@ __global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, co
                                                               const uint2* __restrict__ rec_pair,
                                                               Rec* __restrict__ recs, uint32_t* __restrict__ rec_nkey,
                                                               uint32_t* __restrict__ blk_tot,
-                                                              const Ctrl* __restrict__ ctrl) {
+                                                              Ctrl* __restrict__ ctrl) {
   constexpr uint32_t NT = STAGE ? 512u : 256u;
   extern __shared__ double s_planes[];  // STAGE: rp.p PlaneConst, then rp.p PlaneInt
-  __shared__ uint32_t s_tot;
+  __shared__ uint32_t s_tot, s_counted;
   const uint32_t nrec = ctrl->n_rec_eff;
   const uint32_t rpb = record_rpb_dev(nrec, gridDim.x);
   const uint32_t r_begin = blockIdx.x * rpb;
@@ -500,11 +500,11 @@ __global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, co
       s_pi[q] = pint[q];
     }
   }
-  if (threadIdx.x == 0) s_tot = 0;
+  if (threadIdx.x == 0) s_tot = s_counted = 0;
   __syncthreads();
   const double chi2 = (double)rp.chi2;
-  const bool rows = rp.box_mode == UG_BOX_ROWS && !rp.box_support;  // the records carry their row spans
-  uint32_t mine = 0;
+  const bool rows = rp.by_rows != 0;  // the records carry their row spans
+  uint32_t mine = 0, counted = 0;
   const uint32_t r_end = min(r_begin + rpb, nrec);
   for (uint32_t r = r_begin + threadIdx.x; r < r_end; r += NT) {
     const uint2 gp = rec_pair[r];
@@ -520,10 +520,10 @@ __global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, co
     // Box support: the FP64 Phase-1 decision is final (a pair the
     // conservative float cull let through would otherwise fill its box).
     const bool ok = rp.box_support ? (meets && make_box_record(G, P, PI, k, chi2, f))
-                                   : make_footprint(G, P, PI, k, chi2, rp.box_mode, rp.tile_w, rp.tile_h, f);
+                                   : make_footprint(G, P, PI, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
     if (!ok) {
       // the plane cuts the ellipsoid (or box) outside the image: a record with no keys
-      f.keys = 0;
+      f.keys = f.counted = 0;
       f.acc = RecAcc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       f.geo = RecGeo{0, 0, 1, 0, 1, 0};
     }
@@ -532,10 +532,17 @@ __global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, co
     if (rows) *reinterpret_cast<uint4*>(recs[r].spans) = make_uint4(f.spans[0], f.spans[1], f.spans[2], f.spans[3]);
     rec_nkey[r] = f.keys;
     mine += f.keys;
+    counted += f.counted;
   }
+  // with PAPER boxes binned by rows the reported key count is the rectangles'
+  const bool rect = rows && rp.box_mode == UG_BOX_PAPER;
   if (mine) atomicAdd(&s_tot, mine);
+  if (rect && counted) atomicAdd(&s_counted, counted);
   __syncthreads();
-  if (threadIdx.x == 0) blk_tot[blockIdx.x] = s_tot;
+  if (threadIdx.x == 0) {
+    blk_tot[blockIdx.x] = s_tot;
+    if (rect && s_counted) atomicAdd(&ctrl->n_key, (unsigned long long)s_counted);
+  }
 }
 
 // Key offsets (block prefix + in-block scan) and key emission.  The last
@@ -593,7 +600,7 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     if (act) {
       rec_koff[r] = (uint32_t)(koff < rp.key_cap ? koff : rp.key_cap);
       if (nk > 0 && koff + nk <= rp.key_cap)
-        emit_keys(ra, ge, sp, PI, rp.box_mode, rp.tile_w, rp.tile_h, r, (uint32_t)koff, (uint32_t)(koff + nk),
+        emit_keys(ra, ge, sp, PI, rp.by_rows != 0, rp.tile_w, rp.tile_h, r, (uint32_t)koff, (uint32_t)(koff + nk),
                   key_tile, rec_of_key);
     }
     r = rn;
@@ -605,8 +612,9 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     PI = pint[pln];
   }
   if (blockIdx.x == nact - 1 && threadIdx.x == 0) {
-    ctrl->n_key = carry;
-    const bool ok = carry <= rp.key_cap;
+    const unsigned long long counted = rp.by_rows && rp.box_mode == UG_BOX_PAPER ? ctrl->n_key : carry;
+    ctrl->n_key = counted;
+    const bool ok = counted <= rp.key_cap;
     if (!ok) atomicOr(&ctrl->flags, kFlagKeyCap);
     ctrl->n_key_eff = ok ? (uint32_t)carry : 0u;
     rec_koff[nrec] = ok ? (uint32_t)carry : 0u;
