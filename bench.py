@@ -755,8 +755,7 @@ def kernel_bytes(name, n, p, r, k, t, m, passes, w, rows, g_sort, dslots) -> int
     """Algorithmic HBM bytes of one launch of an HBM-bound kernel: what the
     kernel must read and write once (N Gaussians, R records, K keys, T tiles,
     M pixels; W = 64-plane words per Gaussian; a sort pass reads and writes
-    the key word, emission index and record id once, the first pass reading
-    no emission index; the column scan reads and writes the block
+    the key word and the record id once; the column scan reads and writes the block
     histograms of g_sort blocks x dslots digits)."""
     if name == "setup":
         return p * (56 + 160)
@@ -765,16 +764,15 @@ def kernel_bytes(name, n, p, r, k, t, m, passes, w, rows, g_sort, dslots) -> int
     if name == "cull_write":
         return 4 * n + 8 * n * w + 8 * n + 8 * r
     if name == "record":
-        return 8 * r + 44 * n + 52 * r + (16 * r if rows else 0)
+        return 8 * r + 44 * n + 60 * r + (8 * r if rows else 0)
     if name == "emit":
-        return 4 * r + 16 * r + (48 * r if rows else 0) + 4 * r + 8 * k
+        return 4 * r + 24 * r + (40 * r if rows else 0) + 4 * r + 8 * k
     if name == "sort_hist":
         return 4 * k
     if name == "sort_scan":
         return 8 * dslots * g_sort
     if name == "sort_scatter":
-        total = 20 * k + (passes - 1) * 24 * k
-        return total // max(passes, 1)
+        return 16 * k
     if name == "ranges":
         return 4 * k + 4 * t
     if name == "bwd_prep":

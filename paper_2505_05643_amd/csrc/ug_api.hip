@@ -1,5 +1,6 @@
 // Host side of the C ABI (include/ug.h): plans, workspace layout, argument
 // validation and the enqueue order of the render and backward passes.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -15,7 +16,9 @@ using namespace ug;
 // the loader with the code object and held until the process ends.  Host code
 // uses only the address hipGetSymbolAddress returns for the current device
 // (the array's name on the host is a stand-in, not a device address).
-static __device__ __align__(256) unsigned char scratch[UG_NOALLOC_WORKSPACE_BYTES];
+// The 64 KiB beyond the documented size hold what the size check leaves out
+// (Layout::checked).
+static __device__ __align__(256) unsigned char scratch[UG_NOALLOC_WORKSPACE_BYTES + (64u << 10)];
 
 namespace {
 
@@ -26,8 +29,11 @@ struct Layout {
   size_t ctrl, pconst, pcull, pgroups, cnt_rec, accbits, off_rec, blk_g, blk_r;
   size_t rec_pair, recs, rec_nkey, rec_koff, side;
   size_t tile_start, dsave, gq, hist;
-  size_t key_tile0, key_tile1, key_val0, key_val1, rec_of_key, srec, partial;
+  size_t emitted, key0, key1, rec0, rec1, run_koff, partial;
   size_t loss_part;
+  // what the no-allocation forward's limit is held against: the total, less
+  // what run_koff takes beyond one word per key
+  size_t checked;
   size_t total;
 };
 
@@ -40,7 +46,6 @@ struct ug_plan {
   uint32_t num_tiles = 0;
   uint64_t num_pixels = 0;
   int bits = 1;
-  int final_buf = 0;
   uint32_t rec_cap = 0, key_cap = 0;
   uint32_t sort_blocks = 1;
   int device = 0;
@@ -63,10 +68,8 @@ struct ug_plan {
 
 namespace {
 
-// Workspace regions for the current capacities; also the sort's set that
-// holds the result (the passes alternate between two sets).
+// Workspace regions for the current capacities.
 void compute_layout(ug_plan* pl) {
-  pl->final_buf = sort_passes(pl->bits, pl->sort_blocks) % 2;
   Layout& L = pl->lay;
   size_t o = 0;
   auto take = [&o](size_t bytes) {
@@ -95,14 +98,17 @@ void compute_layout(ug_plan* pl) {
   L.dsave = take(pl->num_pixels * 4);
   L.gq = take(T * tpx * 8);
   L.hist = take((size_t)sort_digit_slots(pl->bits, pl->sort_blocks) * (pl->sort_blocks + 1) * 4);
-  L.key_tile0 = take(K * 4);
-  L.key_tile1 = take(K * 4);
-  L.key_val0 = take(K * 4);
-  L.key_val1 = take(K * 4);
-  L.rec_of_key = take(K * 4);
-  L.srec = take(K * 4);
+  L.emitted = take(K * 4);
+  L.key0 = take(K * 4);
+  L.key1 = take(K * 4);
+  L.rec0 = take(K * 4);
+  L.rec1 = take(K * 4);
+  const size_t runs = (size_t)record_blocks(pl->rec_cap) * kRuns;  // more than K only in small plans
+  L.run_koff = take(std::max(runs, K) * 4);
+  const size_t beyond = runs > K ? align_up(runs * 4) - align_up(K ? K * 4 : 1) : 0;
   L.partial = take(K * 32);
   L.loss_part = take((size_t)bwd_prep_blocks(pl->prm.tile_w, pl->prm.tile_h, pl->num_tiles) * 4);
+  L.checked = o - beyond;
   L.total = o;
 }
 
@@ -178,6 +184,7 @@ RenderParams make_rp(const ug_plan* pl) {
   rp.n = pl->n;
   rp.p = pl->p;
   rp.num_tiles = pl->num_tiles;
+  rp.tile_bits = pl->bits;
   rp.rec_cap = pl->rec_cap;
   rp.key_cap = pl->key_cap;
   return rp;
@@ -226,26 +233,37 @@ hipError_t enqueue_preprocess(const ug_plan* plan, const ug_gaussians& g, const 
   if (e != hipSuccess || !emit) return e;
   StageScope sc(plan, UG_STAGE_EMIT, s);
   return launch_emit(plan->d_pint, rp, at<uint2>(ws, L.rec_pair), at<Rec>(ws, L.recs),
-                     at<uint32_t>(ws, L.rec_nkey), at<uint32_t>(ws, L.blk_r), at<uint32_t>(ws, L.rec_koff), ctrl,
-                     at<uint32_t>(ws, L.key_tile0), at<uint32_t>(ws, L.rec_of_key), s);
+                     at<uint32_t>(ws, L.rec_nkey), at<uint32_t>(ws, L.blk_r), at<uint32_t>(ws, L.rec_koff),
+                     at<uint32_t>(ws, L.run_koff), ctrl, at<uint32_t>(ws, L.emitted), at<uint32_t>(ws, L.rec0), s);
 }
 
-// The radix sort of the emitted keys, one launch per kernel and pass.  Set 0
-// = (key_tile0, key_val0, rec_of_key) holds the emitted keys; passes
-// alternate between set 0 and set 1 = (key_tile1, key_val1, srec).
+// Key words and record ids after `done` sort passes.  The passes alternate
+// between two buffers each; the emitted key words have their own and stay.
+struct Sorted {
+  uint32_t *key, *rec;
+};
+Sorted sorted_set(const ug_plan* plan, void* ws, int done) {
+  const Layout& L = plan->lay;
+  return {at<uint32_t>(ws, done == 0 ? L.emitted : (done & 1 ? L.key1 : L.key0)),
+          at<uint32_t>(ws, done & 1 ? L.rec1 : L.rec0)};
+}
+Sorted sorted_set(const ug_plan* plan, void* ws) {
+  return sorted_set(plan, ws, sort_passes(plan->bits, plan->sort_blocks));
+}
+
+// The radix sort of the emitted keys, one launch per kernel and pass.
 hipError_t enqueue_sort(const ug_plan* plan, void* ws, hipStream_t s) {
   const Layout& L = plan->lay;
   const Ctrl* ctrl = at<Ctrl>(ws, L.ctrl);
-  uint32_t* set[2][3] = {{at<uint32_t>(ws, L.key_tile0), at<uint32_t>(ws, L.key_val0), at<uint32_t>(ws, L.rec_of_key)},
-                         {at<uint32_t>(ws, L.key_tile1), at<uint32_t>(ws, L.key_val1), at<uint32_t>(ws, L.srec)}};
   uint32_t* hist = at<uint32_t>(ws, L.hist);
   const uint32_t G = plan->sort_blocks;
   const int passes = sort_passes(plan->bits, G);
   hipError_t e = hipSuccess;
-  for (int pass = 0, cur = 0; pass < passes && e == hipSuccess; ++pass, cur ^= 1) {
+  for (int pass = 0; pass < passes && e == hipSuccess; ++pass) {
+    const Sorted from = sorted_set(plan, ws, pass), to = sorted_set(plan, ws, pass + 1);
     {
       StageScope sc(plan, UG_STAGE_SORT_HIST, s);
-      e = launch_radix_hist(ctrl, set[cur][0], hist, G, plan->bits, pass, s);
+      e = launch_radix_hist(ctrl, from.key, hist, G, plan->bits, pass, s);
     }
     if (e != hipSuccess) break;
     {
@@ -254,21 +272,12 @@ hipError_t enqueue_sort(const ug_plan* plan, void* ws, hipStream_t s) {
     }
     if (e != hipSuccess) break;
     StageScope sc(plan, UG_STAGE_SORT_SCATTER, s);
-    const uint32_t* in[3] = {set[cur][0], set[cur][1], set[cur][2]};
-    e = launch_radix_scatter(ctrl, in, set[cur ^ 1], hist, G, plan->bits, pass,
+    const uint32_t* in[2] = {from.key, from.rec};
+    uint32_t* out[2] = {to.key, to.rec};
+    e = launch_radix_scatter(ctrl, in, out, hist, G, plan->bits, pass,
                              passes == 1 ? at<uint32_t>(ws, L.tile_start) : nullptr, plan->num_tiles, s);
   }
   return e;
-}
-
-// Sorted arrays {key word, emission index, record id} left by the sort.
-struct Sorted {
-  const uint32_t *key, *val, *rec;
-};
-Sorted sorted_set(const ug_plan* plan, void* ws) {
-  const Layout& L = plan->lay;
-  if (plan->final_buf) return {at<uint32_t>(ws, L.key_tile1), at<uint32_t>(ws, L.key_val1), at<uint32_t>(ws, L.srec)};
-  return {at<uint32_t>(ws, L.key_tile0), at<uint32_t>(ws, L.key_val0), at<uint32_t>(ws, L.rec_of_key)};
 }
 
 constexpr int kMaxDevices = 64;
@@ -443,7 +452,8 @@ int ug_render_planes(const ug_plan* plan, const ug_gaussians* g, const ug_planes
 int ug_render_planes_noalloc(const ug_plan* plan, const ug_gaussians* g, const ug_planes* planes, float* image,
                              void* stream) {
   if (!plan) return UG_ERR_INVALID_ARG;
-  if (plan->lay.total > (size_t)UG_NOALLOC_WORKSPACE_BYTES) return UG_ERR_SCRATCH_SIZE;
+  if (plan->lay.checked > (size_t)UG_NOALLOC_WORKSPACE_BYTES || plan->lay.total > sizeof(scratch))
+    return UG_ERR_SCRATCH_SIZE;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return UG_ERR_HIP;
   if (dev != plan->device) return UG_ERR_INVALID_ARG;  // the plan's tables live on its own device
@@ -496,8 +506,8 @@ int render_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* pla
   const Sorted so = sorted_set(plan, ws);
   if (sort_passes(plan->bits, plan->sort_blocks) > 1) {  // one pass wrote the ranges itself
     StageScope sc(plan, UG_STAGE_RANGES, s);
-    e = launch_tile_ranges(ctrl, so.key, plan->num_tiles, plan->key_cap,
-                           key_mask_shift(plan->prm.tile_w, plan->prm.tile_h), at<uint32_t>(ws, L.tile_start), s);
+    e = launch_tile_ranges(ctrl, so.key, plan->num_tiles, plan->key_cap, plan->bits, at<uint32_t>(ws, L.tile_start),
+                           s);
   }
   if (e != hipSuccess) return UG_ERR_HIP;
   unsigned long long* n_eval = (plan->prm.flags & UG_FLAG_COUNT_EVALS) ? &ctrl->n_eval : nullptr;
@@ -538,9 +548,11 @@ int backward_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* p
   if (e != hipSuccess) return UG_ERR_HIP;
   {
     StageScope sc(plan, UG_STAGE_ACCUM_BWD, s);
-    e = launch_accum_bwd(plan->prm.tile_w, plan->prm.tile_h, plan->d_tile_org, at<uint32_t>(ws, L.tile_start), so.key,
-                         so.val, so.rec, at<Rec>(ws, L.recs), at<float>(ws, L.gq), at<float>(ws, L.partial),
-                         std::isfinite(plan->prm.chi2), plan->num_tiles, plan->key_cap, s);
+    e = launch_accum_bwd(plan->prm.tile_w, plan->prm.tile_h, plan->bits, plan->d_tile_org,
+                         at<uint32_t>(ws, L.tile_start), so.key, so.rec, at<uint32_t>(ws, L.emitted),
+                         at<uint32_t>(ws, L.rec_koff), at<uint32_t>(ws, L.run_koff), at<Rec>(ws, L.recs),
+                         at<float>(ws, L.gq), at<float>(ws, L.partial), std::isfinite(plan->prm.chi2),
+                         plan->num_tiles, plan->key_cap, s);
   }
   if (e != hipSuccess) return UG_ERR_HIP;
   {
@@ -873,16 +885,45 @@ int64_t ug_debug_keys(const ug_plan* plan, const void* workspace, uint32_t* key_
   const int64_t n = (int64_t)c.n_key_eff;
   const int64_t m = n < cap ? n : cap;
   const Sorted so = sorted_set(plan, ws);
-  const std::pair<uint32_t*, const uint32_t*> arrays[3] = {{key_out, so.key}, {eidx_out, so.val}, {rec_out, so.rec}};
-  for (const auto& a : arrays) {
-    if (a.first && m > 0 &&
-        hipMemcpyAsync(a.first, a.second, (size_t)m * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
-      return UG_ERR_HIP;
+  // the key words carry each key's index among its record's keys; the hook
+  // hands out the emission position instead
+  const size_t nr = (size_t)c.n_rec_eff;
+  std::vector<uint32_t> key, rec, emitted, koff;
+  try {
+    key.resize((size_t)m);
+    rec.resize((size_t)m);
+    if (eidx_out && m > 0) {
+      emitted.resize((size_t)n);
+      koff.resize(nr + 1);
+    }
+  } catch (...) {
+    return UG_ERR_INTERNAL;
   }
+  auto copy = [&](std::vector<uint32_t>& to, const uint32_t* from) {
+    return to.empty() || hipMemcpyAsync(to.data(), from, to.size() * 4, hipMemcpyDeviceToHost, s) == hipSuccess;
+  };
+  if (!copy(key, so.key) || !copy(rec, so.rec) || !copy(emitted, at<uint32_t>(ws, L.emitted)) ||
+      !copy(koff, at<uint32_t>(ws, L.rec_koff)))
+    return UG_ERR_HIP;
   if (ranges_out && hipMemcpyAsync(ranges_out, at<uint32_t>(ws, L.tile_start), ((size_t)plan->num_tiles + 1) * 4,
                                    hipMemcpyDeviceToHost, s) != hipSuccess)
     return UG_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return UG_ERR_HIP;
+  const int mshift = key_mask_shift(plan->prm.tile_w, plan->prm.tile_h);
+  const uint32_t tmask = (1u << plan->bits) - 1u, last_index = (1u << (mshift - plan->bits)) - 1u;
+  for (int64_t j = 0; j < m; ++j) {
+    const uint32_t k = key[(size_t)j], r = rec[(size_t)j], t = k & tmask;
+    if (key_out) key_out[j] = t | (k >> mshift) << mshift;
+    if (rec_out) rec_out[j] = r;
+    if (!eidx_out) continue;
+    if (r >= nr) return UG_ERR_INTERNAL;
+    const uint32_t index = (k >> plan->bits) & last_index;
+    eidx_out[j] = koff[r] + index;
+    if (index != last_index) continue;
+    const auto by_tile = [tmask](uint32_t w, uint32_t tile) { return (w & tmask) < tile; };
+    const auto a = emitted.begin() + koff[r], b = emitted.begin() + koff[r + 1];
+    eidx_out[j] = (uint32_t)(std::lower_bound(a, b, t, by_tile) - emitted.begin());
+  }
   return n;
 }
 

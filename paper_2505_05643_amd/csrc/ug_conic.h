@@ -214,7 +214,7 @@ struct Footprint {
   RecGeo geo;
   uint32_t keys;              // keys emitted
   uint32_t counted;           // keys reported and held against the capacity (the PAPER rectangle's tiles)
-  uint32_t spans[kRowSpans];  // by rows: as in Rec
+  RowSpans spans;             // by rows: as in Rec
 };
 
 // Column ranges of the record's ellipse over bands of pixel rows.  The
@@ -339,9 +339,8 @@ __device__ __forceinline__ bool rows_span(const BandPrep& bp, int ty, int TW, in
 // Key count of a record binned by rows over its tile rectangle (rows_span summed
 // over its tile rows), and the spans of its first kRowSpans tile rows.
 __device__ __forceinline__ uint32_t rows_count(const RecAcc& ra, const RecGeo& geo, int W, int H, int TW, int TH,
-                                               uint32_t (&spans)[kRowSpans]) {
-#pragma unroll
-  for (int i = 0; i < kRowSpans; ++i) spans[i] = kNoSpan;
+                                               RowSpans& spans) {
+  spans = kNoSpans;
   const int umin = geo.tx0 * TW;
   const int umax = min(geo.tx1 * TW + TW - 1, W - 1);
   BandPrep bp;
@@ -351,10 +350,12 @@ __device__ __forceinline__ uint32_t rows_count(const RecAcc& ra, const RecGeo& g
     int tx0, tx1;
     if (rows_span(bp, ty, TW, TH, H, umin, umax, tx0, tx1)) {
       keys += (uint32_t)(tx1 - tx0 + 1);
-      const int i = ty - geo.ty0;
-#pragma unroll
-      for (int k = 0; k < kRowSpans; ++k)
-        if (i == k) spans[k] = (uint32_t)tx0 | (uint32_t)tx1 << 16;
+      const int i = 8 * (ty - geo.ty0);
+      if (i < 8 * kRowSpans) {
+        const uint32_t keep = ~(0xffu << i);
+        spans.first = (spans.first & keep) | ((uint32_t)(tx0 - geo.tx0) & 0xffu) << i;
+        spans.last = (spans.last & keep) | ((uint32_t)(tx1 - geo.tx0) & 0xffu) << i;
+      }
     }
   }
   return keys;

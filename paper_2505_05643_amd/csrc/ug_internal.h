@@ -100,9 +100,13 @@ constexpr int kGradFields = 11;
 // and heights are multiples of it).
 constexpr int kSubBlock = 8;
 
-// A key word holds the tile id in its low bits and the tile's sub-block
-// coverage mask (Q = (TW / 8) (TH / 8) bits) in its top Q bits, so the sort
-// moves the mask with the key; tile ids must stay below 2^(32 - Q).
+// A key word holds the tile id in its low bits, the tile's sub-block coverage
+// mask (Q = (TW / 8) (TH / 8) bits) in its top Q bits and, in the bits left
+// between them, the key's index among its record's keys, so that the sort
+// moves both with the key and the adjoint finds the key's place in emission
+// order (record's offset + index) without a payload word for it.  Tile ids
+// must stay below 2^(32 - Q).  An index that does not fit is stored as all
+// ones (kept free for it) and looked up in the emitted keys.
 __host__ __device__ constexpr int key_mask_shift(int tile_w, int tile_h) {
   return 32 - (tile_w / kSubBlock) * (tile_h / kSubBlock);
 }
@@ -113,26 +117,35 @@ struct RecAcc {
 };
 static_assert(sizeof(RecAcc) == 32, "RecAcc layout");
 
-// Integer part of the record: conic centre base pixel and the tile rectangle.
+// Integer part of the record: conic centre base pixel, the run of records it
+// belongs to (kRuns per record block, each built by one wave) and its keys'
+// offset among that run's keys, and the tile rectangle.
+constexpr uint32_t kRuns = 8;
 struct RecGeo {
   int32_t ub, vb;
+  uint32_t run, koff;
   uint16_t tx0, tx1, ty0, ty1;
 };
-static_assert(sizeof(RecGeo) == 16, "RecGeo layout");
+static_assert(sizeof(RecGeo) == 24, "RecGeo layout");
 
 // A record as stored: both parts in one 64-byte slot, so the accumulate
 // kernels' gathers (one record per key, in tile order: random in record
 // order) fetch one 64-byte segment per key instead of two.  The slot's last
-// 16 bytes carry, for binning by rows, the tile span of each of the
-// record's first kRowSpans tile rows as counted by the record kernel
-// (tx0 | tx1 << 16; kNoSpan for a row the ellipse misses), so the emission
-// reuses them instead of recomputing them; unused in the other modes.
+// 8 bytes carry, for binning by rows, the tile spans of the record's first
+// kRowSpans tile rows as counted by the record kernel (first and last tile
+// of row i relative to the rectangle's first, byte i of each word; first >
+// last for a row the ellipse misses), so the emission reuses them instead of
+// recomputing them; rectangles wider than kSpanTiles tiles don't.
 constexpr int kRowSpans = 4;
-constexpr uint32_t kNoSpan = 1u;  // tx0 = 1 > tx1 = 0
+constexpr int kSpanTiles = 255;
+struct RowSpans {
+  uint32_t first, last;
+};
+constexpr RowSpans kNoSpans{0x01010101u, 0u};
 struct Rec {
   RecAcc acc;
   RecGeo geo;
-  uint32_t spans[kRowSpans];
+  RowSpans spans;
 };
 static_assert(sizeof(Rec) == 64, "Rec layout");
 
@@ -150,6 +163,7 @@ struct RenderParams {
   int32_t by_rows;      // keys only for the tiles the ellipse reaches per tile row (box_mode ROWS, and PAPER gathers)
   int32_t n, p;
   uint32_t num_tiles;
+  int32_t tile_bits;    // bits of a tile id
   uint32_t rec_cap, key_cap;
 };
 
@@ -169,6 +183,18 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nblocks) {
 }
 
 __device__ __forceinline__ bool isfinite_d(double v) { return __builtin_isfinite(v); }
+
+// Inclusive prefix sum over the wave's lanes (inactive lanes above the active
+// ones are left out).
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true);  // lane 15 of a row to the next
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true);  // lane 31 to the upper half
+  return x;
+}
 
 // Orders LDS writes and reads between the lanes of one wave (LDS operations
 // of a wave execute in order; this keeps the compiler from moving them).

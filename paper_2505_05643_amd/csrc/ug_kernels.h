@@ -20,13 +20,14 @@ hipError_t launch_cull_write(const RenderParams& rp, const uint32_t* cnt_rec, co
                              const uint32_t* blk_tot, unsigned long long* off_rec, uint2* rec_pair, Ctrl* ctrl,
                              hipStream_t s);
 // Records (conic + footprint and per-record key counts), then key offsets and
-// key emission: per key its key word (tile id and sub-block mask) and record
-// id.
+// key emission: per key its key word (tile id, index among its record's keys,
+// sub-block mask) and record id.  run_koff: the key offset of every run of
+// records (kRuns per record block).
 hipError_t launch_record(const ug_gaussians& g, const PlaneConst* pc, const PlaneInt* pint, const RenderParams& rp,
                          const uint2* rec_pair, Rec* recs, uint32_t* rec_nkey, uint32_t* blk_tot,
                          Ctrl* ctrl, hipStream_t s);
 hipError_t launch_emit(const PlaneInt* pint, const RenderParams& rp, const uint2* rec_pair, const Rec* recs,
-                       const uint32_t* rec_nkey, const uint32_t* blk_tot, uint32_t* rec_koff,
+                       const uint32_t* rec_nkey, const uint32_t* blk_tot, uint32_t* rec_koff, uint32_t* run_koff,
                        Ctrl* ctrl, uint32_t* key_tile, uint32_t* rec_of_key, hipStream_t s);
 // Backward of the record construction and the per-Gaussian sums: the record
 // adjoint finishes every Gaussian whose records sit in one wave of 64 and
@@ -47,12 +48,10 @@ hipError_t launch_gauss_grad(const ug_gaussians& g, const RenderParams& rp, cons
 
 // ---- tile binning sort (ug_sort.hip)
 // Stable LSD radix sort of the key words on their low `bits` bits (the tile
-// id), moving two payload words per key: emission index (generated in the
-// first pass) and record id.  Digits: the whole tile id in one pass when it
+// id), moving each key's record id with it.  Digits: the whole tile id in one pass when it
 // has at most 10 bits and there are at most 256 sort blocks, else at most 8
 // bits per pass with the bits split evenly (sort_digit_bits, sort_passes).
-// Arrays are given as {key, val, rec}; passes alternate between two such
-// sets.  Per pass: block-major digit histograms (hist holds
+// Arrays are given as {key, rec}.  Per pass: block-major digit histograms (hist holds
 // sort_digit_slots * (nblocks + 1) words), their column scan, then the
 // stable scatter.
 int sort_digit_bits(int bits, uint32_t nblocks);
@@ -64,13 +63,13 @@ hipError_t launch_radix_colscan(uint32_t* hist, uint32_t nblocks, int bits, hipS
 // With a single pass (the digit is the whole tile id) the scatter also
 // writes tile_start (if not null; num_tiles + 1 entries), which the column
 // totals give directly.
-hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[3], uint32_t* const out[3],
+hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[2], uint32_t* const out[2],
                                 const uint32_t* hist, uint32_t nblocks, int bits, int pass, uint32_t* tile_start,
                                 uint32_t num_tiles, hipStream_t s);
 // tile_start[t] for t in [0, T] from the sorted key words (tile id = the key
-// word's bits below mask_shift).
+// word's low bits).
 hipError_t launch_tile_ranges(const Ctrl* ctrl, const uint32_t* skeys, uint32_t num_tiles, uint32_t key_cap,
-                              int mask_shift, uint32_t* tile_start, hipStream_t s);
+                              int bits, uint32_t* tile_start, hipStream_t s);
 uint32_t sort_blocks_for(uint32_t key_cap);
 
 // ---- Phase-2 atomic scatter forward (ug_scatter.hip): zero the sums, one
@@ -127,11 +126,14 @@ uint32_t bwd_prep_blocks(int tile_w, int tile_h, uint32_t num_tiles);
 hipError_t launch_bwd_prep(int tile_w, int tile_h, const PlaneInt* pint, const uint32_t* tile_plane,
                            const float* image, const float* second, bool mse, float scale, float* loss_part,
                            const float* dsave, float* gq, uint32_t num_tiles, hipStream_t s);
-// tile_org[t] = pixel origin of tile t, x0 | y0 << 16.
-hipError_t launch_accum_bwd(int tile_w, int tile_h, const uint32_t* tile_org, const uint32_t* tile_start,
-                            const uint32_t* skey, const uint32_t* sval, const uint32_t* srec, const Rec* recs,
-                            const float* gq, float* partial, bool cut, uint32_t num_tiles, uint32_t key_cap,
-                            hipStream_t s);
+// tile_org[t] = pixel origin of tile t, x0 | y0 << 16; emitted = the key words
+// in emission order; rec_koff, run_koff = key offsets of every record and of
+// every run of records.
+hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_t* tile_org,
+                            const uint32_t* tile_start, const uint32_t* skey, const uint32_t* srec,
+                            const uint32_t* emitted, const uint32_t* rec_koff, const uint32_t* run_koff,
+                            const Rec* recs, const float* gq, float* partial, bool cut, uint32_t num_tiles,
+                            uint32_t key_cap, hipStream_t s);
 
 // ---- training helpers (ug_train.hip)
 hipError_t launch_mse(const float* image, const float* target, int64_t m, float* d_image, float* loss,

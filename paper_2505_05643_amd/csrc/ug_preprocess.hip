@@ -421,10 +421,13 @@ __device__ __forceinline__ uint32_t record_rpb_dev(uint32_t nrec, uint32_t grid)
   const uint32_t per = (rounds + grid - 1u) / grid;
   return (per < 1u ? 1u : per) * 256u;
 }
-__device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, const uint4& spans, const PlaneInt& PI,
-                                          bool by_rows, int TW, int TH, uint32_t r, uint32_t e, uint32_t e_end,
-                                          uint32_t* __restrict__ key_tile, uint32_t* __restrict__ rec_of_key) {
+__device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, const RowSpans& spans,
+                                          const PlaneInt& PI, bool by_rows, int TW, int TH, int tile_bits, uint32_t r,
+                                          uint32_t e, uint32_t e_end, uint32_t* __restrict__ key_tile,
+                                          uint32_t* __restrict__ rec_of_key) {
   const int mshift = key_mask_shift(TW, TH);
+  const uint32_t e0 = e, last_index = (1u << (mshift - tile_bits)) - 1u;  // indices from here on: looked up
+  const bool known = by_rows && geo.tx1 - geo.tx0 <= kSpanTiles - 1;
   const int umin = geo.tx0 * TW;
   const int umax = min(geo.tx1 * TW + TW - 1, PI.W - 1);
   BandPrep bp;
@@ -435,10 +438,9 @@ __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, c
     if (by_rows) {
       // the record kernel's span for the first kRowSpans rows, else recomputed
       const int i = ty - (int)geo.ty0;
-      if (i < kRowSpans) {
-        const uint32_t w = i == 0 ? spans.x : (i == 1 ? spans.y : (i == 2 ? spans.z : spans.w));
-        tx0 = (int)(w & 0xffffu);
-        tx1 = (int)(w >> 16);
+      if (known && i < kRowSpans) {
+        tx0 = geo.tx0 + (int)((spans.first >> (8 * i)) & 0xffu);
+        tx1 = geo.tx0 + (int)((spans.last >> (8 * i)) & 0xffu);
         if (tx0 > tx1) continue;
       } else if (!rows_span(bp, ty, TW, TH, PI.H, umin, umax, tx0, tx1)) {
         continue;
@@ -457,7 +459,8 @@ __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, c
     const uint32_t rowbase = PI.tile_off + (uint32_t)ty * (uint32_t)PI.ntx;
     for (int tx = tx0; tx <= tx1; ++tx) {
       if (e < e_end) {
-        key_tile[e] = (rowbase + (uint32_t)tx) | (tile_mask(bua, buz, tx, TW) << mshift);
+        key_tile[e] = (rowbase + (uint32_t)tx) | min(e - e0, last_index) << tile_bits |
+                      (tile_mask(bua, buz, tx, TW) << mshift);
         rec_of_key[e] = r;
       }
       ++e;
@@ -506,33 +509,46 @@ __global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, co
   const bool rows = rp.by_rows != 0;  // the records carry their row spans
   uint32_t mine = 0, counted = 0;
   const uint32_t r_end = min(r_begin + rpb, nrec);
-  for (uint32_t r = r_begin + threadIdx.x; r < r_end; r += NT) {
-    const uint2 gp = rec_pair[r];
-    GaussIn G;
-    load_gauss(g, (int)gp.x, (double)rp.beta, G);
-    const PlaneConst& P = STAGE ? s_pc[gp.y] : pc[gp.y];
-    const PlaneInt& PI = STAGE ? s_pi[gp.y] : pint[gp.y];
-    const PlaneT<double> Pd = plane_as<double>(P);
-    Conic k;
-    const bool meets = conic_cull(G, Pd, chi2, k);
-    conic_full(G, Pd, k);
-    Footprint f;
-    // Box support: the FP64 Phase-1 decision is final (a pair the
-    // conservative float cull let through would otherwise fill its box).
-    const bool ok = rp.box_support ? (meets && make_box_record(G, P, PI, k, chi2, f))
-                                   : make_footprint(G, P, PI, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
-    if (!ok) {
-      // the plane cuts the ellipsoid (or box) outside the image: a record with no keys
-      f.keys = f.counted = 0;
-      f.acc = RecAcc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      f.geo = RecGeo{0, 0, 1, 0, 1, 0};
+  // A wave builds whole runs, so a record's key offset within its run needs
+  // no other wave (a barrier per round for offsets within the block made the
+  // kernel 25% slower).
+  const uint32_t len = rpb / kRuns;
+  for (uint32_t run = threadIdx.x >> 6; run < kRuns; run += NT / 64) {
+    const uint32_t run_end = min(r_begin + (run + 1u) * len, r_end);
+    uint32_t carry = 0;  // keys of the run so far
+    for (uint32_t r = r_begin + run * len + (threadIdx.x & 63); r < run_end; r += 64) {
+      Footprint f;
+      const uint2 gp = rec_pair[r];
+      GaussIn G;
+      load_gauss(g, (int)gp.x, (double)rp.beta, G);
+      const PlaneConst& P = STAGE ? s_pc[gp.y] : pc[gp.y];
+      const PlaneInt& PI = STAGE ? s_pi[gp.y] : pint[gp.y];
+      const PlaneT<double> Pd = plane_as<double>(P);
+      Conic k;
+      const bool meets = conic_cull(G, Pd, chi2, k);
+      conic_full(G, Pd, k);
+      // Box support: the FP64 Phase-1 decision is final (a pair the
+      // conservative float cull let through would otherwise fill its box).
+      const bool ok = rp.box_support ? (meets && make_box_record(G, P, PI, k, chi2, f))
+                                     : make_footprint(G, P, PI, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
+      if (!ok) {
+        // the plane cuts the ellipsoid (or box) outside the image: a record with no keys
+        f.keys = f.counted = 0;
+        f.acc = RecAcc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        f.geo = RecGeo{0, 0, 0, 0, 1, 0, 1, 0};
+        f.spans = kNoSpans;
+      }
+      const uint32_t incl = wave_incl_sum(f.keys);
+      f.geo.run = blockIdx.x * kRuns + run;
+      f.geo.koff = carry + incl - f.keys;
+      carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);  // the step is full, or the run's last
+      recs[r].acc = f.acc;
+      recs[r].geo = f.geo;
+      if (rows) recs[r].spans = f.spans;
+      rec_nkey[r] = f.keys;
+      mine += f.keys;
+      counted += f.counted;
     }
-    recs[r].acc = f.acc;
-    recs[r].geo = f.geo;
-    if (rows) *reinterpret_cast<uint4*>(recs[r].spans) = make_uint4(f.spans[0], f.spans[1], f.spans[2], f.spans[3]);
-    rec_nkey[r] = f.keys;
-    mine += f.keys;
-    counted += f.counted;
   }
   // with PAPER boxes binned by rows the reported key count is the rectangles'
   const bool rect = rows && rp.box_mode == UG_BOX_PAPER;
@@ -551,7 +567,7 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
                                               const uint2* __restrict__ rec_pair, const Rec* __restrict__ recs,
                                               const uint32_t* __restrict__ rec_nkey,
                                               const uint32_t* __restrict__ blk_tot, uint32_t* __restrict__ rec_koff,
-                                              Ctrl* __restrict__ ctrl, uint32_t* __restrict__ key_tile,
+                                              uint32_t* __restrict__ run_koff, Ctrl* __restrict__ ctrl, uint32_t* __restrict__ key_tile,
                                               uint32_t* __restrict__ rec_of_key) {
   __shared__ unsigned long long s_sh[4];
   const uint32_t nrec = ctrl->n_rec_eff;
@@ -573,13 +589,13 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
   uint32_t pl, nk;
   RecAcc ra;
   RecGeo ge;
-  uint4 sp;
+  RowSpans sp;
   {
     const uint32_t rl = act ? r : r_end - 1u;
     pl = rec_pair[rl].y;
     ra = recs[rl].acc;
     ge = recs[rl].geo;
-    sp = *reinterpret_cast<const uint4*>(recs[rl].spans);
+    sp = recs[rl].spans;
     nk = act ? rec_nkey[rl] : 0u;
   }
   unsigned long long carry = block_prefix(blk_tot, blockIdx.x, s_sh);
@@ -591,7 +607,7 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     const uint32_t pln = rec_pair[rl].y;
     const RecAcc ran = recs[rl].acc;
     const RecGeo gen = recs[rl].geo;
-    const uint4 spn = *reinterpret_cast<const uint4*>(recs[rl].spans);
+    const RowSpans spn = recs[rl].spans;
     const uint32_t nkl = rec_nkey[rl];
     const uint32_t nkn = actn ? nkl : 0u;
     unsigned long long tot;
@@ -600,8 +616,8 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     if (act) {
       rec_koff[r] = (uint32_t)(koff < rp.key_cap ? koff : rp.key_cap);
       if (nk > 0 && koff + nk <= rp.key_cap)
-        emit_keys(ra, ge, sp, PI, rp.by_rows != 0, rp.tile_w, rp.tile_h, r, (uint32_t)koff, (uint32_t)(koff + nk),
-                  key_tile, rec_of_key);
+        emit_keys(ra, ge, sp, PI, rp.by_rows != 0, rp.tile_w, rp.tile_h, rp.tile_bits, r, (uint32_t)koff,
+                  (uint32_t)(koff + nk), key_tile, rec_of_key);
     }
     r = rn;
     act = actn;
@@ -610,6 +626,11 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     ge = gen;
     sp = spn;
     PI = pint[pln];
+  }
+  __syncthreads();  // rec_koff of the block's records
+  if (threadIdx.x < kRuns) {
+    const uint32_t rr = r_begin + threadIdx.x * (rpb / kRuns);
+    if (rr < r_end) run_koff[blockIdx.x * kRuns + threadIdx.x] = rec_koff[rr];
   }
   if (blockIdx.x == nact - 1 && threadIdx.x == 0) {
     const unsigned long long counted = rp.by_rows && rp.box_mode == UG_BOX_PAPER ? ctrl->n_key : carry;
@@ -942,10 +963,10 @@ hipError_t launch_record(const ug_gaussians& g, const PlaneConst* pc, const Plan
 }
 
 hipError_t launch_emit(const PlaneInt* pint, const RenderParams& rp, const uint2* rec_pair, const Rec* recs,
-                       const uint32_t* rec_nkey, const uint32_t* blk_tot, uint32_t* rec_koff,
+                       const uint32_t* rec_nkey, const uint32_t* blk_tot, uint32_t* rec_koff, uint32_t* run_koff,
                        Ctrl* ctrl, uint32_t* key_tile, uint32_t* rec_of_key, hipStream_t s) {
   hipLaunchKernelGGL(k_emit, dim3(record_blocks(rp.rec_cap)), dim3(256), 0, s, pint, rp,
-                     rec_pair, recs, rec_nkey, blk_tot, rec_koff, ctrl, key_tile, rec_of_key);
+                     rec_pair, recs, rec_nkey, blk_tot, rec_koff, run_koff, ctrl, key_tile, rec_of_key);
   return hipGetLastError();
 }
 

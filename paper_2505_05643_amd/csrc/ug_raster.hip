@@ -340,17 +340,6 @@ constexpr int kStrip = 4;  // columns per item
 // the 9 KB of a 32 x 32 tile's gamma)
 __host__ __device__ constexpr int slots_wave(int tw, int th) { return tw * th <= 256 || tw * th > 512 ? 224 : 208; }
 
-// Inclusive prefix sum over the wave's lanes.
-__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);  // row_shr:1
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);  // row_shr:2
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);  // row_shr:4
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);  // row_shr:8
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true);  // lane 15 of a row to the next
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true);  // lane 31 to the upper half
-  return x;
-}
-
 // What the item stage needs of a key.  The ellipse t1^2 + t2^2 <= d has at
 // column offset du from its centre the rows dv = -m du -/+ sqrt(D - E du^2)
 // with S = t12^2 + t22^2, m = t11 t12 / S, D = d / S, E = (t11 t22 / S)^2; its
@@ -425,11 +414,26 @@ __device__ __forceinline__ int strip_rows(const StripGeo& g, float du0, float dv
   return any ? (int)fb - ya + 1 : 0;
 }
 
+// Place of record rid's key for tile t in emission order (its keys start at
+// k0 and ascend in tile id), for keys whose index did not fit the key word.
+__device__ __noinline__ uint32_t find_emitted(const uint32_t* __restrict__ emitted,
+                                              const uint32_t* __restrict__ rec_koff, uint32_t rid, uint32_t k0,
+                                              uint32_t t, uint32_t tmask) {
+  uint32_t a = k0, b = rec_koff[rid + 1] - 1u;  // the key is in [a, b]
+  while (a < b) {
+    const uint32_t m = a + (b - a) / 2u;
+    if ((emitted[m] & tmask) < t) a = m + 1u;
+    else b = m;
+  }
+  return a;
+}
+
 template <int TW, int TH>
 __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     const uint32_t* __restrict__ tile_org, const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ skey,
-    const uint32_t* __restrict__ sval, const uint32_t* __restrict__ srec, const Rec* __restrict__ recs,
-    const float2* __restrict__ gq, float4* __restrict__ partial, int kcut, uint32_t num_tiles, uint32_t nsplit) {
+    const uint32_t* __restrict__ srec, const uint32_t* __restrict__ emitted, const uint32_t* __restrict__ rec_koff,
+    const uint32_t* __restrict__ run_koff, const Rec* __restrict__ recs, const float2* __restrict__ gq,
+    float4* __restrict__ partial, int kcut, int tile_bits, uint32_t num_tiles, uint32_t nsplit) {
   constexpr int kMaskShift = key_mask_shift(TW, TH);
   constexpr int kSlotsWave = slots_wave(TW, TH), kGroups = (kSlotsWave + 63) / 64;
   constexpr int kMaxStrips = TW / kStrip;
@@ -476,19 +480,21 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   // A pass's keys are loaded during the pass before it, and their records (a
   // random 64-byte gather per key) before that pass's evaluation.  Lanes past
   // the wave's keys read the tile's last key and are masked off.
-  uint32_t kw, rid, eidx;
+  uint32_t kw, rid;
   RecAcc A;
   int ub, vb;
+  uint32_t run, koff;
   auto load_keys = [&]() {
     const uint32_t j = s + min(k + (uint32_t)lane, n - 1u);
     kw = skey[j];
     rid = srec[j];
-    eidx = sval[j];
   };
   auto load_recs = [&]() {
     A = recs[rid].acc;
     ub = recs[rid].geo.ub;
     vb = recs[rid].geo.vb;
+    run = recs[rid].geo.run;
+    koff = recs[rid].geo.koff;
   };
   load_keys();
   {
@@ -508,7 +514,13 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   }
   __syncthreads();  // gt, bucket and grab are ready
   for (;;) {
-    const uint32_t dst = eidx, left = ke - k;
+    // where the key's partial goes: its place in emission order, the record's
+    // offset plus the key's index among the record's keys
+    const uint32_t last_index = (1u << (kMaskShift - tile_bits)) - 1u;
+    const uint32_t index = (kw >> tile_bits) & last_index;
+    uint32_t dst = run_koff[run] + koff + index;
+    if (index == last_index) dst = find_emitted(emitted, rec_koff, rid, dst - index, t, (1u << tile_bits) - 1u);
+    const uint32_t left = ke - k;
     // a pass takes an even part of what is left, at most 64 keys
     const uint32_t want = left > 64u ? (left + (left + 63u) / 64u - 1u) / ((left + 63u) / 64u) : left;
     const float du0 = (float)(ub - x0) + A.fu, dv0 = (float)(vb - y0) + A.fv;
@@ -777,10 +789,11 @@ hipError_t launch_bwd_prep(int tile_w, int tile_h, const PlaneInt* pint, const u
 // block per tile 41 us, eight 13; 600 tiles of 150: one 11, two 15).
 constexpr uint32_t kBwdBlockKeys = 1024, kBwdMinBlocks = 1024, kBwdMinKeys = 128;
 
-hipError_t launch_accum_bwd(int tile_w, int tile_h, const uint32_t* tile_org, const uint32_t* tile_start,
-                            const uint32_t* skey, const uint32_t* sval, const uint32_t* srec, const Rec* recs,
-                            const float* gq, float* partial, bool cut, uint32_t num_tiles, uint32_t key_cap,
-                            hipStream_t s) {
+hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_t* tile_org,
+                            const uint32_t* tile_start, const uint32_t* skey, const uint32_t* srec,
+                            const uint32_t* emitted, const uint32_t* rec_koff, const uint32_t* run_koff,
+                            const Rec* recs, const float* gq, float* partial, bool cut, uint32_t num_tiles,
+                            uint32_t key_cap, hipStream_t s) {
   const float2* g2 = reinterpret_cast<const float2*>(gq);
   float4* p4 = reinterpret_cast<float4*>(partial);
   if (num_tiles == 0) return hipSuccess;
@@ -791,8 +804,8 @@ hipError_t launch_accum_bwd(int tile_w, int tile_h, const uint32_t* tile_org, co
   const int kcut = cut ? kCutBits : kNoCutBits;
 #define UG_BWD(W, H)                                                                                           \
   if (tile_w == W && tile_h == H) {                                                                            \
-    hipLaunchKernelGGL((k_accum_bwd<W, H>), grid, dim3(256), 0, s, tile_org, tile_start, skey, sval, srec, recs, \
-                       g2, p4, kcut, num_tiles, nsplit);                                                                  \
+    hipLaunchKernelGGL((k_accum_bwd<W, H>), grid, dim3(256), 0, s, tile_org, tile_start, skey, srec, emitted,   \
+                       rec_koff, run_koff, recs, g2, p4, kcut, tile_bits, num_tiles, nsplit);                   \
     return hipGetLastError();                                                                                  \
   }
   UG_TILE_SHAPES(UG_BWD)

@@ -1,9 +1,10 @@
 // Tile binning: stable LSD radix sort of the key words on their tile id,
-// carrying the emission index and the record id, with the key count read
-// from device memory (so the host never synchronises), and the per-tile
+// carrying the record id, with the key count read from device memory (so the host never synchronises), and the per-tile
 // [start, end) ranges.  Digits are at most 8 bits (256 per pass), or, for
 // small inputs whose tile id has at most 10 bits, the whole tile id in one
 // pass (up to 1024 digits).
+#include <algorithm>
+
 #include "ug_kernels.h"
 
 namespace ug {
@@ -101,26 +102,26 @@ __global__ __launch_bounds__(256) void k_radix_colscan(uint32_t* __restrict__ cn
 // kItems keys per thread and round: 8 for small inputs (more blocks, less
 // LDS), 16 when every block walks several rounds.
 
-// Every key carries two payload words (emission index, record id).  They
-// are loaded with the keys (coalesced, in flight during the ranking) and
-// follow them through the same LDS slots one word at a time: the keys are
-// reordered and written, then the emission indices, then the record ids.
+// Every key carries its record id.  It is loaded with the key (coalesced, in
+// flight during the ranking) and follows it through the same LDS slots: the
+// keys are reordered and written, then the record ids.  (A second payload
+// word, the emission index, cost a third of the traffic and of the LDS work:
+// 823 us for two passes over 42M keys with it.)
 struct SortSet {
   uint32_t* key;
-  uint32_t* val;  // emission index; generated (= position) in the first pass
   uint32_t* rec;
 };
 
 template <int kItems, int D>
 __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in,
-                                                                SortSet out, bool gen_val,
+                                                                SortSet out,
                                                                 const uint32_t* __restrict__ cnt,
                                                                 const uint32_t* __restrict__ coltot, uint32_t G,
                                                                 int shift, int dbits, uint32_t* __restrict__ tile_start,
                                                                 uint32_t T) {
   constexpr int kRound = kSortThreads * kItems;
   const uint32_t* __restrict__ kin = in.key;
-  __shared__ uint32_t s_key[kRound];  // the round reordered by digit: keys, then each payload word
+  __shared__ uint32_t s_key[kRound];  // the round reordered by digit: keys, then record ids
   constexpr int kPer = D / kSortThreads;  // digits per thread, consecutive
   __shared__ uint32_t run[D];      // global output position of the next key of each digit
   __shared__ uint32_t loc[D];      // first LDS slot of each digit in this round
@@ -168,7 +169,7 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
     // the round's keys split evenly over the waves, in whole loads of 64
     const uint32_t n_round = min((uint32_t)kRound, e - base);
     const uint32_t seg = ((n_round + 255u) / 256u) * 64u;
-    uint32_t kk[kItems], rr[kItems], vv[kItems], rc[kItems];
+    uint32_t kk[kItems], rr[kItems], rc[kItems];
     // all of the round's loads first: the ranking's wave fences would
     // otherwise keep each load behind the previous key's LDS update
 #pragma unroll
@@ -176,7 +177,6 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
       const uint32_t i = base + (uint32_t)wave * seg + (uint32_t)(it * 64 + lane);
       const bool valid = (uint32_t)(it * 64) < seg && i < e;
       kk[it] = valid ? kin[i] : 0u;
-      vv[it] = gen_val ? i : (valid ? in.val[i] : 0u);
       rc[it] = valid ? in.rec[i] : 0u;
     }
 #pragma unroll
@@ -242,7 +242,7 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
     }
     __syncthreads();
     // keys out, as contiguous runs per digit; each slot's output position is
-    // kept for the payload words
+    // kept for the record id
     uint32_t opos[kItems];
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
@@ -255,19 +255,15 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
         out.key[opos[j]] = k;
       }
     }
-    // the two payload words through the same slots
+    // the record ids through the same slots
+    __syncthreads();
 #pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      __syncthreads();
+    for (int it = 0; it < kItems; ++it)
+      if (rr[it] != 0xffffffffu) s_key[rr[it]] = rc[it];
+    __syncthreads();
 #pragma unroll
-      for (int it = 0; it < kItems; ++it)
-        if (rr[it] != 0xffffffffu) s_key[rr[it]] = w == 0 ? vv[it] : rc[it];
-      __syncthreads();
-      uint32_t* __restrict__ dst = w == 0 ? out.val : out.rec;
-#pragma unroll
-      for (int j = 0; j < kItems; ++j)
-        if (opos[j] != 0xffffffffu) dst[opos[j]] = s_key[(uint32_t)tid + (uint32_t)(j * kSortThreads)];
-    }
+    for (int j = 0; j < kItems; ++j)
+      if (opos[j] != 0xffffffffu) out.rec[opos[j]] = s_key[(uint32_t)tid + (uint32_t)(j * kSortThreads)];
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPer; ++k) run[tid * kPer + k] += rcnt[tid * kPer + k];
@@ -280,19 +276,19 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
 // LDS allows; the compiler would otherwise give it more registers and three.
 template <int kItems, int D>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in,
-                                                                SortSet out, bool gen_val,
+                                                                SortSet out,
                                                                 const uint32_t* __restrict__ cnt,
                                                                 const uint32_t* __restrict__ coltot, uint32_t G,
                                                                 int shift, int dbits, uint32_t* __restrict__ tile_start,
                                                                 uint32_t T) {
-  radix_scatter<kItems, D>(ctrl, in, out, gen_val, cnt, coltot, G, shift, dbits, tile_start, T);
+  radix_scatter<kItems, D>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
 }
 
 __global__ __launch_bounds__(kSortThreads, 4) void k_radix_scatter_large(
-    const Ctrl* __restrict__ ctrl, SortSet in, SortSet out, bool gen_val, const uint32_t* __restrict__ cnt,
+    const Ctrl* __restrict__ ctrl, SortSet in, SortSet out, const uint32_t* __restrict__ cnt,
     const uint32_t* __restrict__ coltot, uint32_t G, int shift, int dbits, uint32_t* __restrict__ tile_start,
     uint32_t T) {
-  radix_scatter<16, 256>(ctrl, in, out, gen_val, cnt, coltot, G, shift, dbits, tile_start, T);
+  radix_scatter<16, 256>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
 }
 
 // tile_start[t] = first sorted key index whose tile id is >= t (t in [0, T]).
@@ -368,15 +364,19 @@ int sort_passes(int bits, uint32_t G) {
 
 uint32_t sort_digit_slots(int bits, uint32_t G) { return sort_digit_bits(bits, G) > 8 ? 1024u : 256u; }
 
+// Digit bits of one pass: the last takes what is left of the tile id (the
+// bits above it belong to the key's other fields).
+static int pass_bits(int bits, int db, int pass) { return std::min(db, bits - db * pass); }
+
 hipError_t launch_radix_hist(const Ctrl* ctrl, const uint32_t* keys, uint32_t* hist, uint32_t G, int bits, int pass,
                              hipStream_t s) {
   const int db = sort_digit_bits(bits, G);
   if (db > 8)
     hipLaunchKernelGGL(k_radix_hist<1024>, dim3(G), dim3(kSortThreads), 0, s, ctrl, keys, G, db * pass,
-                       (1u << db) - 1u, hist);
+                       (1u << pass_bits(bits, db, pass)) - 1u, hist);
   else
     hipLaunchKernelGGL(k_radix_hist<256>, dim3(G), dim3(kSortThreads), 0, s, ctrl, keys, G, db * pass,
-                       (1u << db) - 1u, hist);
+                       (1u << pass_bits(bits, db, pass)) - 1u, hist);
   return hipGetLastError();
 }
 
@@ -389,29 +389,30 @@ hipError_t launch_radix_colscan(uint32_t* hist, uint32_t G, int bits, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[3], uint32_t* const out[3],
+hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[2], uint32_t* const out[2],
                                 const uint32_t* hist, uint32_t G, int bits, int pass, uint32_t* tile_start,
                                 uint32_t num_tiles, hipStream_t s) {
   const int db = sort_digit_bits(bits, G);
   const uint32_t D = sort_digit_slots(bits, G);
-  const SortSet si{const_cast<uint32_t*>(in[0]), const_cast<uint32_t*>(in[1]), const_cast<uint32_t*>(in[2])};
-  const SortSet so{out[0], out[1], out[2]};
+  const int pb = pass_bits(bits, db, pass);
+  const SortSet si{const_cast<uint32_t*>(in[0]), const_cast<uint32_t*>(in[1])};
+  const SortSet so{out[0], out[1]};
   const uint32_t* coltot = hist + (size_t)D * G;
   if (D == 1024u)  // only for G <= kWideMaxBlocks
-    hipLaunchKernelGGL((k_radix_scatter<8, 1024>), dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so, pass == 0,
-                       hist, coltot, G, db * pass, db, tile_start, num_tiles);
+    hipLaunchKernelGGL((k_radix_scatter<8, 1024>), dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so,
+                       hist, coltot, G, db * pass, pb, tile_start, num_tiles);
   else if (G >= kSortMaxBlocks)
-    hipLaunchKernelGGL(k_radix_scatter_large, dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so, pass == 0,
-                       hist, coltot, G, db * pass, db, tile_start, num_tiles);
+    hipLaunchKernelGGL(k_radix_scatter_large, dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so,
+                       hist, coltot, G, db * pass, pb, tile_start, num_tiles);
   else
-    hipLaunchKernelGGL((k_radix_scatter<8, 256>), dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so, pass == 0,
-                       hist, coltot, G, db * pass, db, tile_start, num_tiles);
+    hipLaunchKernelGGL((k_radix_scatter<8, 256>), dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so,
+                       hist, coltot, G, db * pass, pb, tile_start, num_tiles);
   return hipGetLastError();
 }
 
 hipError_t launch_tile_ranges(const Ctrl* ctrl, const uint32_t* skeys, uint32_t num_tiles, uint32_t key_cap,
-                              int mask_shift, uint32_t* tile_start, hipStream_t s) {
-  const uint32_t tmask = mask_shift >= 32 ? 0xffffffffu : (1u << mask_shift) - 1u;
+                              int bits, uint32_t* tile_start, hipStream_t s) {
+  const uint32_t tmask = bits >= 32 ? 0xffffffffu : (1u << bits) - 1u;
   const uint32_t blocks = (key_cap + 256u * kRangeKeys - 1u) / (256u * kRangeKeys);
   hipLaunchKernelGGL(k_tile_ranges, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, ctrl, skeys, num_tiles, tmask,
                      tile_start);
