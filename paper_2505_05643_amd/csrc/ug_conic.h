@@ -22,6 +22,52 @@
 
 namespace ug {
 
+// Reciprocal and square root of the positive, normal values of the record
+// construction in double: the hardware's estimate (about 2^-23 off) and one
+// third-order step, within an ulp or two and rounded to float right after.
+// The exact division and square root take two to three times the
+// instructions, and the record kernel is bound by its FP64 arithmetic.  In
+// float the exact forms are kept.
+__device__ __forceinline__ double recip(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
+__device__ __forceinline__ float recip(float x) { return 1.f / x; }
+
+// root = sqrt(x), inv = 1 / sqrt(x).
+__device__ __forceinline__ void root_pair(double x, double& root, double& inv) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  inv = fma(y * e, fma(0.375, e, 0.5), y);
+  const double g = x * inv;
+  root = fma(fma(-g, g, x), 0.5 * inv, g);
+}
+__device__ __forceinline__ void root_pair(float x, float& root, float& inv) {
+  root = sqrtf(x);
+  inv = 1.f / root;
+}
+
+// max and min of two doubles in one instruction (the other operand for a NaN;
+// fmax and fmin also quiet each operand first).
+__device__ __forceinline__ double max64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double min64(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// sqrt(x) of x >= 0, kept within [1e-150, 1e150] (no cut-off: x is infinite).
+__device__ __forceinline__ double root(double x) {
+  double r, i;
+  root_pair(min64(max64(x, 1e-300), 1e300), r, i);
+  return r;
+}
+
 // Gaussian parameters in scalar type T (double for the record construction,
 // float for its adjoint, whose tolerance is far looser).
 template <typename T>
@@ -51,6 +97,14 @@ using Conic = ConicT<double>;
 template <typename T>
 struct PlaneT {
   T o[3], rinv[9], e1[3], e2[3], absdet, sx, sy;
+};
+
+// What the record construction reads of a plane: the pose, the pixel index of
+// its in-plane origin, the reciprocal spacings and the size.
+struct PlaneRec {
+  PlaneT<double> pose;
+  double cu, cv, isx, isy;
+  int W, H;
 };
 
 template <typename T>
@@ -111,9 +165,9 @@ __device__ __forceinline__ void gauss_setup(const GaussRaw& r, T beta, GaussT<T>
   G.L22 = G.l[3] * G.l[3] + beta;
   G.L32 = G.l[4];
   G.L33 = G.l[5] * G.l[5] + beta;
-  G.iL11 = (T)1 / G.L11;
-  G.iL22 = (T)1 / G.L22;
-  G.iL33 = (T)1 / G.L33;
+  G.iL11 = recip(G.L11);
+  G.iL22 = recip(G.L22);
+  G.iL33 = recip(G.L33);
   // alpha = sigmoid(a); log2(alpha) = -softplus(-a) / ln 2, stable for any
   // a.  In single precision for both types: the records hold it in float
   // (e0 and emin), so a double evaluation would only cost time.
@@ -164,7 +218,7 @@ __device__ __forceinline__ void conic_full(const GaussT<T>& G, const PlaneT<T>& 
   k.m2 = P.rinv[3] * d0 + P.rinv[4] * d1 + P.rinv[5] * d2;
   fsub(G, P.rinv[0], P.rinv[1], P.rinv[2], k.g1);
   fsub(G, P.rinv[3], P.rinv[4], P.rinv[5], k.g2);
-  const T iS = (T)1 / k.S33;
+  const T iS = recip(k.S33);
   k.iS = iS;
   k.r2 = k.m3 * k.m3 * iS;
   k.S11 = k.g1[0] * k.g1[0] + k.g1[1] * k.g1[1] + k.g1[2] * k.g1[2];
@@ -178,11 +232,11 @@ __device__ __forceinline__ void conic_full(const GaussT<T>& G, const PlaneT<T>& 
   k.b2[0] = G.L11 * P.e2[0] + G.L21 * P.e2[1] + G.L31 * P.e2[2];
   k.b2[1] = G.L22 * P.e2[1] + G.L32 * P.e2[2];
   k.b2[2] = G.L33 * P.e2[2];
-  k.T11 = sqrt(k.b1[0] * k.b1[0] + k.b1[1] * k.b1[1] + k.b1[2] * k.b1[2]);
-  const T iT11 = (T)1 / k.T11;
+  T iT11, in3;
+  root_pair(k.b1[0] * k.b1[0] + k.b1[1] * k.b1[1] + k.b1[2] * k.b1[2], k.T11, iT11);
   k.T12 = (k.b1[0] * k.b2[0] + k.b1[1] * k.b2[1] + k.b1[2] * k.b2[2]) * iT11;
   k.detL = G.L11 * G.L22 * G.L33;
-  k.n3 = sqrt(k.S33);
+  root_pair(k.S33, k.n3, in3);
   k.T22 = k.detL * P.absdet * k.n3 * iT11;
   k.c1 = k.m1 - k.m3 * k.S13 * iS;
   k.c2 = k.m2 - k.m3 * k.S23 * iS;
@@ -202,10 +256,8 @@ __device__ __forceinline__ bool pixel_range(double centre, double half, int32_t 
   double a = centre - half - pad, b = centre + half + pad;
   if (!(a <= b)) return false;  // NaN
   if (b < 0.0 || a > (double)(size - 1)) return false;
-  a = a > 0.0 ? a : 0.0;
-  b = b < (double)(size - 1) ? b : (double)(size - 1);
-  lo = (int)ceil(a);
-  hi = (int)floor(b);
+  lo = (int)ceil(max64(a, 0.0));
+  hi = (int)floor(min64(b, (double)(size - 1)));
   return lo <= hi;
 }
 
@@ -259,22 +311,16 @@ __device__ __forceinline__ bool band_cols(const BandPrep& b, int ya, int yb, int
     uz = umax;
     return umin <= umax;
   }
-  double lo = (double)ya - b.v0, hi = (double)yb - b.v0;
-  lo = lo > -b.vext ? lo : -b.vext;
-  hi = hi < b.vext ? hi : b.vext;
+  const double lo = max64((double)ya - b.v0, -b.vext), hi = min64((double)yb - b.v0, b.vext);
   if (!(lo <= hi)) return false;
-  const double dvr = b.dvr < lo ? lo : (b.dvr > hi ? hi : b.dvr);
-  const double dvl = -b.dvr < lo ? lo : (-b.dvr > hi ? hi : -b.dvr);
-  double qr = b.thr - b.t22 * b.t22 * dvr * dvr;
-  double ql = b.thr - b.t22 * b.t22 * dvl * dvl;
-  qr = qr > 0.0 ? qr : 0.0;
-  ql = ql > 0.0 ? ql : 0.0;
+  const double dvr = min64(max64(b.dvr, lo), hi);
+  const double dvl = min64(max64(-b.dvr, lo), hi);
+  const double qr = max64(b.thr - b.t22 * b.t22 * dvr * dvr, 0.0);
+  const double ql = max64(b.thr - b.t22 * b.t22 * dvl * dvl, 0.0);
   const double ur = b.u0 + (-b.t12 * dvr + (double)__builtin_amdgcn_sqrtf((float)qr)) * b.inv_t11;
   const double ul = b.u0 + (-b.t12 * dvl - (double)__builtin_amdgcn_sqrtf((float)ql)) * b.inv_t11;
   const double pad = 1e-3 + 1e-5 * (ur - ul);
-  double a = ul - pad, c = ur + pad;
-  a = a > (double)umin ? a : (double)umin;
-  c = c < (double)umax ? c : (double)umax;
+  const double a = max64(ul - pad, (double)umin), c = min64(ur + pad, (double)umax);
   if (!(a <= c)) return false;
   ua = (int)ceil(a);
   uz = (int)floor(c);
@@ -364,12 +410,12 @@ __device__ __forceinline__ uint32_t rows_count(const RecAcc& ra, const RecGeo& g
 // The float record of an accepted pair: the in-plane factor scaled to pixel
 // units, the conic centre (u0, v0) split into an integer base pixel and a
 // fraction, the exponent offset and cut-off, the intensity.
-__device__ __forceinline__ void record_conic(const GaussIn& G, const PlaneConst& P, const Conic& k, double chi2,
+__device__ __forceinline__ void record_conic(const GaussIn& G, const PlaneT<double>& P, const Conic& k, double chi2,
                                              double u0, double v0, Footprint& f) {
   const double ks = sqrt(kHalfLog2e);
   double ubd = floor(u0 + 0.5), vbd = floor(v0 + 0.5);
-  ubd = ubd < -1.0e9 ? -1.0e9 : (ubd > 1.0e9 ? 1.0e9 : ubd);
-  vbd = vbd < -1.0e9 ? -1.0e9 : (vbd > 1.0e9 ? 1.0e9 : vbd);
+  ubd = min64(max64(ubd, -1.0e9), 1.0e9);
+  vbd = min64(max64(vbd, -1.0e9), 1.0e9);
   f.acc.t11 = (float)(ks * k.T11 * P.sx);
   f.acc.t12 = (float)(ks * k.T12 * P.sy);
   f.acc.t22 = (float)(ks * k.T22 * P.sy);
@@ -402,12 +448,14 @@ __device__ __forceinline__ bool box_pixels(double centre, double half, int32_t s
 // -/+ sqrt(chi^2 Sigma'_kk), and the cut-off is -inf, so every pixel of the
 // rectangle takes its Eq. 8 weight.  Pixel u's centre is at
 // (u - cu) sx in the plane, hence the index interval below.  No keys.
-__device__ __forceinline__ bool make_box_record(const GaussIn& G, const PlaneConst& P, const PlaneInt& PI,
-                                                const Conic& k, double chi2, Footprint& f) {
+__device__ __forceinline__ bool make_box_record(const GaussIn& G, const PlaneRec& Q, const Conic& k, double chi2,
+                                                Footprint& f) {
+  const PlaneT<double>& P = Q.pose;
+  // exact divisions: a pixel centre on the box's edge decides here
   int ulo, uhi, vlo, vhi;
-  if (!box_pixels(k.m1 / P.sx + P.cu, sqrt(chi2 * k.S11) / P.sx, PI.W, ulo, uhi)) return false;
-  if (!box_pixels(k.m2 / P.sy + P.cv, sqrt(chi2 * k.S22) / P.sy, PI.H, vlo, vhi)) return false;
-  record_conic(G, P, k, chi2, k.c1 / P.sx + P.cu, k.c2 / P.sy + P.cv, f);
+  if (!box_pixels(k.m1 / P.sx + Q.cu, sqrt(chi2 * k.S11) / P.sx, Q.W, ulo, uhi)) return false;
+  if (!box_pixels(k.m2 / P.sy + Q.cv, sqrt(chi2 * k.S22) / P.sy, Q.H, vlo, vhi)) return false;
+  record_conic(G, P, k, chi2, k.c1 / P.sx + Q.cu, k.c2 / P.sy + Q.cv, f);
   f.acc.emin = -INFINITY;
   f.geo.tx0 = (uint16_t)ulo;
   f.geo.tx1 = (uint16_t)uhi;
@@ -423,31 +471,30 @@ __device__ __forceinline__ bool make_box_record(const GaussIn& G, const PlaneCon
 // it does not (their mask would be empty): at 1M Gaussians and 256 planes of
 // 256^2 69M tiles of 16 x 16, 41M of them reached; counting them here costs
 // the record kernel less than emitting, sorting and skipping the rest.
-__device__ __forceinline__ bool make_footprint(const GaussIn& G, const PlaneConst& P, const PlaneInt& PI,
-                                               const Conic& k, double chi2, int box_mode, bool by_rows, int TW, int TH,
-                                               Footprint& f) {
-  const double u0 = k.c1 / P.sx + P.cu;
-  const double v0 = k.c2 / P.sy + P.cv;
+__device__ __forceinline__ bool make_footprint(const GaussIn& G, const PlaneRec& Q, const Conic& k, double chi2,
+                                               int box_mode, bool by_rows, int TW, int TH, Footprint& f) {
+  const double isx = Q.isx, isy = Q.isy;
+  const double u0 = k.c1 * isx + Q.cu;
+  const double v0 = k.c2 * isy + Q.cv;
   int ulo, uhi, vlo, vhi;
   if (box_mode == UG_BOX_PAPER) {
     // Eq. 13: b_{1:2} = m_{1:2} -/+ sqrt(chi^2 Sigma'_kk).
-    if (!pixel_range(k.m1 / P.sx + P.cu, sqrt(chi2 * k.S11) / P.sx, PI.W, ulo, uhi)) return false;
-    if (!pixel_range(k.m2 / P.sy + P.cv, sqrt(chi2 * k.S22) / P.sy, PI.H, vlo, vhi)) return false;
+    if (!pixel_range(k.m1 * isx + Q.cu, root(chi2 * k.S11) * isx, Q.W, ulo, uhi)) return false;
+    if (!pixel_range(k.m2 * isy + Q.cv, root(chi2 * k.S22) * isy, Q.H, vlo, vhi)) return false;
   } else {
     // Box of the ellipse cut by the plane: conditional variances
     // Sigma'_kk - Sigma'_k3^2 / Sigma'_33 = |g_k x g3|^2 / |g3|^2.
-    double q = chi2 - k.r2;
-    q = q > 0.0 ? q : 0.0;
-    if (!pixel_range(u0, sqrt(q * cross_norm2(k.g1, k.g3) * k.iS) / P.sx, PI.W, ulo, uhi)) return false;
-    if (!pixel_range(v0, sqrt(q * cross_norm2(k.g2, k.g3) * k.iS) / P.sy, PI.H, vlo, vhi)) return false;
+    const double q = max64(chi2 - k.r2, 0.0);
+    if (!pixel_range(u0, root(q * cross_norm2(k.g1, k.g3) * k.iS) * isx, Q.W, ulo, uhi)) return false;
+    if (!pixel_range(v0, root(q * cross_norm2(k.g2, k.g3) * k.iS) * isy, Q.H, vlo, vhi)) return false;
   }
-  record_conic(G, P, k, chi2, u0, v0, f);
+  record_conic(G, Q.pose, k, chi2, u0, v0, f);
   f.geo.tx0 = (uint16_t)tile_of(ulo, TW);
   f.geo.tx1 = (uint16_t)tile_of(uhi, TW);
   f.geo.ty0 = (uint16_t)tile_of(vlo, TH);
   f.geo.ty1 = (uint16_t)tile_of(vhi, TH);
   f.counted = (uint32_t)(f.geo.tx1 - f.geo.tx0 + 1) * (uint32_t)(f.geo.ty1 - f.geo.ty0 + 1);
-  f.keys = by_rows ? rows_count(f.acc, f.geo, PI.W, PI.H, TW, TH, f.spans) : f.counted;
+  f.keys = by_rows ? rows_count(f.acc, f.geo, Q.W, Q.H, TW, TH, f.spans) : f.counted;
   if (box_mode == UG_BOX_ROWS) f.counted = f.keys;
   return f.counted > 0;
 }

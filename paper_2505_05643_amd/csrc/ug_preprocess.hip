@@ -474,34 +474,89 @@ __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, c
 // touch many planes, and those gathers queue on the vector-memory address
 // path.
 constexpr int kStagePlanes = 256;
-static_assert(sizeof(PlaneConst) % 8 == 0 && sizeof(PlaneInt) % 8 == 0, "LDS plane staging layout");
+
+// A plane's PlaneRec in LDS: an odd number of doubles, so that the lanes'
+// planes (mostly consecutive) start in different banks (24 of them put four
+// planes in all banks between them, and the conflicts set the record kernel's
+// time), then its size.
+constexpr int kPlaneDoubles = 25;
+constexpr size_t kPlaneLds = kPlaneDoubles * sizeof(double) + sizeof(int2);
+
+__device__ __forceinline__ PlaneRec plane_rec(const PlaneConst& c, const PlaneInt& i) {
+  return PlaneRec{plane_as<double>(c), c.cu, c.cv, 1.0 / c.sx, 1.0 / c.sy, i.W, i.H};
+}
+__device__ __forceinline__ void plane_rec_to_lds(const PlaneRec& q, double* d, int2* wh) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    d[k] = q.pose.o[k];
+    d[12 + k] = q.pose.e1[k];
+    d[15 + k] = q.pose.e2[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) d[3 + k] = q.pose.rinv[k];
+  d[18] = q.pose.absdet;
+  d[19] = q.pose.sx;
+  d[20] = q.pose.sy;
+  d[21] = q.cu;
+  d[22] = q.cv;
+  d[23] = q.isx;
+  d[24] = q.isy;
+  *wh = make_int2(q.W, q.H);
+}
+__device__ __forceinline__ PlaneRec plane_rec_from_lds(const double* d, const int2& wh) {
+  PlaneRec q;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    q.pose.o[k] = d[k];
+    q.pose.e1[k] = d[12 + k];
+    q.pose.e2[k] = d[15 + k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) q.pose.rinv[k] = d[3 + k];
+  q.pose.absdet = d[18];
+  q.pose.sx = d[19];
+  q.pose.sy = d[20];
+  q.cu = d[21];
+  q.cv = d[22];
+  q.isx = d[23];
+  q.isy = d[24];
+  q.W = wh.x;
+  q.H = wh.y;
+  return q;
+}
 
 // FP64 in-plane conic and footprint of each record; key counts and the
 // block's total.  STAGE (launches of up to kStagePlanes planes): the planes'
-// constants are copied to LDS once per block (512 threads, so the 56 KB of
-// a 256-plane launch still leaves the 16 waves per CU the registers allow)
+// constants are copied to LDS once per block (512 threads: the 52 KB of a
+// 256-plane launch and the slots' 20 KB leave the 16 waves per CU the
+// registers allow)
 // instead of being gathered per record from memory.
+//
+// Bound by its FP64 arithmetic (740 VALU instructions per 64 records, 77% of
+// the issue).  16.2M records on 256 planes: 575 us with exact divisions and
+// roots, plane constants 24 doubles apart and every lane storing its own
+// slot; 567 without the exact forms, 548 without the bank conflicts too, 446
+// with the slots stored through LDS (2.5 TB/s written).
 template <bool STAGE>
-__global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, const PlaneConst* __restrict__ pc,
+__global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_gaussians g, const PlaneConst* __restrict__ pc,
                                                               const PlaneInt* __restrict__ pint, RenderParams rp,
                                                               const uint2* __restrict__ rec_pair,
                                                               Rec* __restrict__ recs, uint32_t* __restrict__ rec_nkey,
                                                               uint32_t* __restrict__ blk_tot,
                                                               Ctrl* __restrict__ ctrl) {
   constexpr uint32_t NT = STAGE ? 512u : 256u;
-  extern __shared__ double s_planes[];  // STAGE: rp.p PlaneConst, then rp.p PlaneInt
+  extern __shared__ double s_planes[];  // STAGE: rp.p x kPlaneDoubles, then rp.p sizes
+  constexpr int kSlotPitch = 5;  // float4 per slot in LDS: four and one of padding
+  __shared__ float4 s_slot[NT / 64][32 * kSlotPitch];
   __shared__ uint32_t s_tot, s_counted;
   const uint32_t nrec = ctrl->n_rec_eff;
   const uint32_t rpb = record_rpb_dev(nrec, gridDim.x);
   const uint32_t r_begin = blockIdx.x * rpb;
   if (r_begin >= nrec) return;  // uniform
-  PlaneConst* s_pc = reinterpret_cast<PlaneConst*>(s_planes);
-  PlaneInt* s_pi = reinterpret_cast<PlaneInt*>(s_pc + rp.p);
+  int2* s_wh = reinterpret_cast<int2*>(s_planes + (size_t)kPlaneDoubles * rp.p);
   if (STAGE) {
-    for (int q = (int)threadIdx.x; q < rp.p; q += (int)NT) {
-      s_pc[q] = pc[q];
-      s_pi[q] = pint[q];
-    }
+    for (int q = (int)threadIdx.x; q < rp.p; q += (int)NT)
+      plane_rec_to_lds(plane_rec(pc[q], pint[q]), s_planes + kPlaneDoubles * q, s_wh + q);
   }
   if (threadIdx.x == 0) s_tot = s_counted = 0;
   __syncthreads();
@@ -513,46 +568,68 @@ __global__ __launch_bounds__(STAGE ? 512 : 256) void k_record(ug_gaussians g, co
   // no other wave (a barrier per round for offsets within the block made the
   // kernel 25% slower).
   const uint32_t len = rpb / kRuns;
-  for (uint32_t run = threadIdx.x >> 6; run < kRuns; run += NT / 64) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t run = (uint32_t)wave; run < kRuns; run += NT / 64) {
     const uint32_t run_end = min(r_begin + (run + 1u) * len, r_end);
     uint32_t carry = 0;  // keys of the run so far
-    for (uint32_t r = r_begin + run * len + (threadIdx.x & 63); r < run_end; r += 64) {
-      Footprint f;
-      const uint2 gp = rec_pair[r];
-      GaussIn G;
-      load_gauss(g, (int)gp.x, (double)rp.beta, G);
-      const PlaneConst& P = STAGE ? s_pc[gp.y] : pc[gp.y];
-      const PlaneInt& PI = STAGE ? s_pi[gp.y] : pint[gp.y];
-      const PlaneT<double> Pd = plane_as<double>(P);
-      Conic k;
-      const bool meets = conic_cull(G, Pd, chi2, k);
-      conic_full(G, Pd, k);
-      // Box support: the FP64 Phase-1 decision is final (a pair the
-      // conservative float cull let through would otherwise fill its box).
-      const bool ok = rp.box_support ? (meets && make_box_record(G, P, PI, k, chi2, f))
-                                     : make_footprint(G, P, PI, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
-      if (!ok) {
-        // the plane cuts the ellipsoid (or box) outside the image: a record with no keys
-        f.keys = f.counted = 0;
-        f.acc = RecAcc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f.geo = RecGeo{0, 0, 0, 0, 1, 0, 1, 0};
-        f.spans = kNoSpans;
+    for (uint32_t r0 = r_begin + run * len; r0 < run_end; r0 += 64) {
+      const uint32_t r = r0 + (uint32_t)lane;
+      Rec out{};
+      uint32_t nk = 0;
+      if (r < run_end) {
+        Footprint f;
+        const uint2 gp = rec_pair[r];
+        GaussIn G;
+        load_gauss(g, (int)gp.x, (double)rp.beta, G);
+        const PlaneRec Q = STAGE ? plane_rec_from_lds(s_planes + kPlaneDoubles * gp.y, s_wh[gp.y])
+                                 : plane_rec(pc[gp.y], pint[gp.y]);
+        Conic k;
+        const bool meets = conic_cull(G, Q.pose, chi2, k);
+        conic_full(G, Q.pose, k);
+        // Box support: the FP64 Phase-1 decision is final (a pair the
+        // conservative float cull let through would otherwise fill its box).
+        const bool ok = rp.box_support ? (meets && make_box_record(G, Q, k, chi2, f))
+                                       : make_footprint(G, Q, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
+        if (!ok) {
+          // the plane cuts the ellipsoid (or box) outside the image: a record with no keys
+          f.keys = f.counted = 0;
+          f.acc = RecAcc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          f.geo = RecGeo{0, 0, 0, 0, 1, 0, 1, 0};
+          f.spans = kNoSpans;
+        }
+        rec_nkey[r] = nk = f.keys;
+        counted += f.counted;
+        out = Rec{f.acc, f.geo, f.spans};
       }
-      const uint32_t incl = wave_incl_sum(f.keys);
-      f.geo.run = blockIdx.x * kRuns + run;
-      f.geo.koff = carry + incl - f.keys;
-      carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);  // the step is full, or the run's last
-      recs[r].acc = f.acc;
-      recs[r].geo = f.geo;
-      if (rows) recs[r].spans = f.spans;
-      rec_nkey[r] = f.keys;
-      mine += f.keys;
-      counted += f.counted;
+      const uint32_t incl = wave_incl_sum(nk);
+      out.geo.run = blockIdx.x * kRuns + run;
+      out.geo.koff = carry + incl - nk;
+      carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      // The slots go out through LDS, half the wave's at a time: every store
+      // then writes whole 64-byte slots side by side.  A lane storing its own
+      // slot sixteen bytes at a time makes four requests of it, and the L2's
+      // write requests set the kernel's time.
+      const float4* src = reinterpret_cast<const float4*>(&out);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        wave_lds_sync();
+        if ((lane >> 5) == h) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) s_slot[wave][(lane & 31) * kSlotPitch + q] = src[q];
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint32_t rr = (uint32_t)(i * 16 + (lane >> 2)), to = r0 + (uint32_t)(32 * h) + rr;
+          if (to < run_end) reinterpret_cast<float4*>(recs + to)[lane & 3] = s_slot[wave][rr * kSlotPitch + (lane & 3)];
+        }
+      }
     }
+    mine += carry;
   }
   // with PAPER boxes binned by rows the reported key count is the rectangles'
   const bool rect = rows && rp.box_mode == UG_BOX_PAPER;
-  if (mine) atomicAdd(&s_tot, mine);
+  if (lane == 0 && mine) atomicAdd(&s_tot, mine);
   if (rect && counted) atomicAdd(&s_counted, counted);
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -952,7 +1029,7 @@ hipError_t launch_record(const ug_gaussians& g, const PlaneConst* pc, const Plan
                          const uint2* rec_pair, Rec* recs, uint32_t* rec_nkey, uint32_t* blk_tot,
                          Ctrl* ctrl, hipStream_t s) {
   if (rp.p <= kStagePlanes) {
-    const size_t lds = (size_t)rp.p * (sizeof(PlaneConst) + sizeof(PlaneInt));
+    const size_t lds = (size_t)rp.p * kPlaneLds;
     hipLaunchKernelGGL(k_record<true>, dim3(record_blocks(rp.rec_cap)), dim3(512), lds, s, g, pc, pint, rp,
                        rec_pair, recs, rec_nkey, blk_tot, ctrl);
   } else {
