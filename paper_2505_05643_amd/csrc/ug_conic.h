@@ -327,39 +327,66 @@ __device__ __forceinline__ bool band_cols(const BandPrep& b, int ya, int yb, int
   return ua <= uz;
 }
 
-// Column ranges of the bands of tile row ty (TH / 8 <= kMaxBands bands) over
-// the record's column span [umin, umax].  Empty bands get ua > uz.
-constexpr int kMaxBands = 4;
-__device__ __forceinline__ void band_ranges(const BandPrep& bp, int ty, int TH, int H, int umin, int umax,
-                                            int (&ua)[kMaxBands], int (&uz)[kMaxBands]) {
-#pragma unroll
-  for (int b = 0; b < kMaxBands; ++b) {
-    const int ya = ty * TH + b * kSubBlock;
-    const int yb = min(ya + kSubBlock - 1, H - 1);
-    ua[b] = 1;
-    uz[b] = 0;
-    if (b * kSubBlock < TH && ya <= yb) {
-      int a, z;
-      if (band_cols(bp, ya, yb, umin, umax, a, z)) {
-        ua[b] = a;
-        uz[b] = z;
-      }
-    }
-  }
+// The same column ranges for the sub-block masks of the emission, in single
+// precision relative to the record's centre and widened further (a mask may
+// name a sub-block too many, whose pairs add exact zeros; it must not miss
+// one).  At row offset dv the ellipse spans -(t12 / t11) dv -/+
+// sqrt(d - t22^2 dv^2) / t11, with its right end at dvr and its left at -dvr.
+struct BandMask {
+  float t22, a, i11, d, dvr, fu, fv;
+  int ub, vb;
+  bool all;  // no cut-off, or a constant that is not finite
+};
+
+__device__ __forceinline__ bool band_mask_prep(const RecAcc& ra, int ub, int vb, BandMask& b) {
+  const float d = ra.e0 - ra.emin;
+  b.i11 = __builtin_amdgcn_rcpf(ra.t11);
+  b.t22 = ra.t22;
+  b.a = ra.t12 * b.i11;
+  b.d = d * 1.0001f;
+  const float iS = __builtin_amdgcn_rcpf(fmaf(ra.t12, ra.t12, ra.t22 * ra.t22));
+  b.dvr = -ra.t12 * __builtin_amdgcn_sqrtf(d * iS) * __builtin_amdgcn_rcpf(ra.t22);
+  b.fu = ra.fu;
+  b.fv = ra.fv;
+  b.ub = ub;
+  b.vb = vb;
+  b.all = !(d < 1e30f && fabsf(b.a) < 1e12f && fabsf(b.dvr) < 1e12f && b.i11 < 1e12f && ra.t22 < 1e12f);
+  return d >= 0.f;
 }
 
-// Mask of the sub-blocks of tile column tx touched by the band ranges
-// (TW / 8 column blocks per band).
-__device__ __forceinline__ uint32_t tile_mask(const int (&ua)[kMaxBands], const int (&uz)[kMaxBands], int tx, int TW) {
-  const int K = TW / kSubBlock;
-  const int x0 = tx * TW;
+// Sub-block columns [ca, cz] (of 8 pixels) the ellipse may reach in pixel rows
+// [ya, yb], cut to the pixel columns [umin, umax]; ca > cz if none.
+__device__ __forceinline__ void band_mask_cols(const BandMask& b, int ya, int yb, int umin, int umax, int& ca,
+                                               int& cz) {
+  const float lo = (float)(ya - b.vb) - b.fv, hi = (float)(yb - b.vb) - b.fv;
+  const float pv = fmaf(2e-6f, fmaxf(fabsf(lo), fabsf(hi)), 2e-3f);
+  const float vr = __builtin_amdgcn_fmed3f(b.dvr, lo - pv, hi + pv);
+  const float vl = __builtin_amdgcn_fmed3f(-b.dvr, lo - pv, hi + pv);
+  const float tr = b.t22 * vr, tl = b.t22 * vl;
+  const float qr = fmaf(-tr, tr, b.d), ql = fmaf(-tl, tl, b.d);
+  const float ur = fmaf(-b.a, vr, __builtin_amdgcn_sqrtf(fmaxf(qr, 0.f)) * b.i11);
+  const float ul = fmaf(-b.a, vl, -__builtin_amdgcn_sqrtf(fmaxf(ql, 0.f)) * b.i11);
+  const float pu = fmaf(1e-5f, fmaxf(fabsf(ur), fabsf(ul)), 3e-3f);
+  // columns relative to the centre's pixel, cut before the conversion
+  const float fl = fmaxf(ceilf(ul + b.fu - pu), (float)(umin - b.ub));
+  const float fr = fminf(floorf(ur + b.fu + pu), (float)(umax - b.ub));
+  const bool any = b.all || (qr >= 0.f && fl <= fr);  // qr < 0: the rows lie beside the ellipse
+  ca = any ? (b.all ? umin : (int)fl + b.ub) / kSubBlock : 1;
+  cz = any ? (b.all ? umax : (int)fr + b.ub) / kSubBlock : 0;
+}
+
+// Mask of the sub-blocks of tile column tx that the bands' columns reach
+// (K = TW / 8 column blocks per band, TH / 8 <= kMaxBands bands).
+constexpr int kMaxBands = 4;
+__device__ __forceinline__ uint32_t tile_mask(const int (&ca)[kMaxBands], const int (&cz)[kMaxBands], int nb, int tx,
+                                              int K) {
+  const int x0 = tx * K;
   uint32_t m = 0;
 #pragma unroll
   for (int b = 0; b < kMaxBands; ++b) {
-    const int lo = max(ua[b], x0) - x0, hi = min(uz[b], x0 + TW - 1) - x0;
-    if (lo <= hi) {
-      const uint32_t bits = ((2u << (hi / kSubBlock)) - 1u) & ~((1u << (lo / kSubBlock)) - 1u);
-      m |= bits << (b * K);
+    if (b < nb) {  // uniform
+      const int lo = max(ca[b] - x0, 0), n = max(min(cz[b] - x0, K - 1) - lo + 1, 0);
+      m |= ((1u << n) - 1u) << (lo + b * K);
     }
   }
   return m;

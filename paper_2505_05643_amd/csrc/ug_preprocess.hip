@@ -430,9 +430,12 @@ __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, c
   const bool known = by_rows && geo.tx1 - geo.tx0 <= kSpanTiles - 1;
   const int umin = geo.tx0 * TW;
   const int umax = min(geo.tx1 * TW + TW - 1, PI.W - 1);
-  BandPrep bp;
-  const bool ok = band_prep(ra, geo.ub, geo.vb, bp);
+  BandMask bm;
+  const bool ok = band_mask_prep(ra, geo.ub, geo.vb, bm);
   if (by_rows && !ok) return;
+  BandPrep bp;  // only for the rows whose spans the record does not hold
+  if (by_rows && (!known || geo.ty1 - geo.ty0 >= kRowSpans)) band_prep(ra, geo.ub, geo.vb, bp);
+  const int nb = TH / kSubBlock, K = TW / kSubBlock;
   for (int ty = geo.ty0; ty <= geo.ty1; ++ty) {
     int tx0 = geo.tx0, tx1 = geo.tx1;
     if (by_rows) {
@@ -446,21 +449,21 @@ __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, c
         continue;
       }
     }
-    int bua[kMaxBands], buz[kMaxBands];
-    if (ok) {
-      band_ranges(bp, ty, TH, PI.H, umin, umax, bua, buz);
-    } else {
+    int ca[kMaxBands], cz[kMaxBands];
 #pragma unroll
-      for (int b = 0; b < kMaxBands; ++b) {
-        bua[b] = 1;
-        buz[b] = 0;
+    for (int b = 0; b < kMaxBands; ++b) {
+      ca[b] = 1;
+      cz[b] = 0;
+      if (b < nb) {  // uniform
+        const int ya = ty * TH + b * kSubBlock, yb = min(ya + kSubBlock - 1, PI.H - 1);
+        if (ok && ya <= yb) band_mask_cols(bm, ya, yb, umin, umax, ca[b], cz[b]);
       }
     }
     const uint32_t rowbase = PI.tile_off + (uint32_t)ty * (uint32_t)PI.ntx;
     for (int tx = tx0; tx <= tx1; ++tx) {
       if (e < e_end) {
         key_tile[e] = (rowbase + (uint32_t)tx) | min(e - e0, last_index) << tile_bits |
-                      (tile_mask(bua, buz, tx, TW) << mshift);
+                      (tile_mask(ca, cz, nb, tx, K) << mshift);
         rec_of_key[e] = r;
       }
       ++e;
