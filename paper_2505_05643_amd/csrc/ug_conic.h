@@ -23,17 +23,20 @@
 namespace ug {
 
 // Reciprocal and square root of the positive, normal values of the record
-// construction in double: the hardware's estimate (about 2^-23 off) and one
-// third-order step, within an ulp or two and rounded to float right after.
-// The exact division and square root take two to three times the
-// instructions, and the record kernel is bound by its FP64 arithmetic.  In
-// float the exact forms are kept.
+// construction (double) and its adjoint (float): the hardware's estimate and
+// one step of third order (double, from 2^-23) or second (float, from an
+// ulp), within an ulp or two; the record is rounded to float right after.
+// The exact division and square root take two to four times the
+// instructions, and both kernels are bound by their arithmetic.
 __device__ __forceinline__ double recip(double x) {
   const double y = __builtin_amdgcn_rcp(x);
   const double e = fma(-x, y, 1.0);
   return fma(y, fma(e, e, e), y);
 }
-__device__ __forceinline__ float recip(float x) { return 1.f / x; }
+__device__ __forceinline__ float recip(float x) {
+  const float y = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, y, 1.f), y, y);
+}
 
 // root = sqrt(x), inv = 1 / sqrt(x).
 __device__ __forceinline__ void root_pair(double x, double& root, double& inv) {
@@ -44,8 +47,10 @@ __device__ __forceinline__ void root_pair(double x, double& root, double& inv) {
   root = fma(fma(-g, g, x), 0.5 * inv, g);
 }
 __device__ __forceinline__ void root_pair(float x, float& root, float& inv) {
-  root = sqrtf(x);
-  inv = 1.f / root;
+  const float y = __builtin_amdgcn_rsqf(x);
+  inv = fmaf(0.5f * y, fmaf(-x * y, y, 1.f), y);
+  const float g = x * inv;
+  root = fmaf(fmaf(-g, g, x), 0.5f * inv, g);
 }
 
 // max and min of two doubles in one instruction (the other operand for a NaN;
@@ -88,7 +93,8 @@ struct ConicT {
   T g1[3], g2[3], g3[3];
   T b1[3], b2[3];
   T S11, S22, S33, S13, S23, iS;  // iS = 1 / S33
-  T T11, T12, T22, detL, n3;
+  T T11, T12, T22, detL, n3;  // n3 = sqrt(S33)
+  T iT11, in3;                // reciprocals of T11, n3
   T c1, c2, r2;
 };
 using Conic = ConicT<double>;
@@ -141,8 +147,9 @@ __device__ __forceinline__ GaussRaw load_gauss_raw(const ug_gaussians& g, int i)
   return r;
 }
 
+// exact: divisions for the reciprocals (the cull's decisions rest on them).
 template <typename T>
-__device__ __forceinline__ void gauss_setup(const GaussRaw& r, T beta, GaussT<T>& G) {
+__device__ __forceinline__ void gauss_setup(const GaussRaw& r, T beta, GaussT<T>& G, bool exact = false) {
   bool fin = true;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -165,9 +172,9 @@ __device__ __forceinline__ void gauss_setup(const GaussRaw& r, T beta, GaussT<T>
   G.L22 = G.l[3] * G.l[3] + beta;
   G.L32 = G.l[4];
   G.L33 = G.l[5] * G.l[5] + beta;
-  G.iL11 = recip(G.L11);
-  G.iL22 = recip(G.L22);
-  G.iL33 = recip(G.L33);
+  G.iL11 = exact ? (T)1 / G.L11 : recip(G.L11);
+  G.iL22 = exact ? (T)1 / G.L22 : recip(G.L22);
+  G.iL33 = exact ? (T)1 / G.L33 : recip(G.L33);
   // alpha = sigmoid(a); log2(alpha) = -softplus(-a) / ln 2, stable for any
   // a.  In single precision for both types: the records hold it in float
   // (e0 and emin), so a double evaluation would only cost time.
@@ -178,8 +185,8 @@ __device__ __forceinline__ void gauss_setup(const GaussRaw& r, T beta, GaussT<T>
 }
 
 template <typename T>
-__device__ __forceinline__ void load_gauss(const ug_gaussians& g, int i, T beta, GaussT<T>& G) {
-  gauss_setup(load_gauss_raw(g, i), beta, G);
+__device__ __forceinline__ void load_gauss(const ug_gaussians& g, int i, T beta, GaussT<T>& G, bool exact = false) {
+  gauss_setup(load_gauss_raw(g, i), beta, G, exact);
 }
 
 // Forward substitution y = L^-1 q.
@@ -232,11 +239,11 @@ __device__ __forceinline__ void conic_full(const GaussT<T>& G, const PlaneT<T>& 
   k.b2[0] = G.L11 * P.e2[0] + G.L21 * P.e2[1] + G.L31 * P.e2[2];
   k.b2[1] = G.L22 * P.e2[1] + G.L32 * P.e2[2];
   k.b2[2] = G.L33 * P.e2[2];
-  T iT11, in3;
-  root_pair(k.b1[0] * k.b1[0] + k.b1[1] * k.b1[1] + k.b1[2] * k.b1[2], k.T11, iT11);
+  root_pair(k.b1[0] * k.b1[0] + k.b1[1] * k.b1[1] + k.b1[2] * k.b1[2], k.T11, k.iT11);
+  const T iT11 = k.iT11;
   k.T12 = (k.b1[0] * k.b2[0] + k.b1[1] * k.b2[1] + k.b1[2] * k.b2[2]) * iT11;
   k.detL = G.L11 * G.L22 * G.L33;
-  root_pair(k.S33, k.n3, in3);
+  root_pair(k.S33, k.n3, k.in3);
   k.T22 = k.detL * P.absdet * k.n3 * iT11;
   k.c1 = k.m1 - k.m3 * k.S13 * iS;
   k.c2 = k.m2 - k.m3 * k.S23 * iS;
@@ -537,15 +544,15 @@ __device__ __forceinline__ void footprint_adjoint(const GaussT<T>& G, const Plan
   const T dT11 = ks * P.sx * (T)dr[0];
   const T dT12 = ks * P.sy * (T)dr[1];
   const T dT22 = ks * P.sy * (T)dr[2];
-  const T dc1 = (T)dr[3] / P.sx;
-  const T dc2 = (T)dr[4] / P.sy;
+  const T dc1 = (T)dr[3] * recip(P.sx);
+  const T dc2 = (T)dr[4] * recip(P.sy);
   const T de0 = (T)dr[5];
   dc += (T)dr[6];
   // e0 = log2(sigmoid(a)) - kHalfLog2e r^2
-  da += de0 * ((T)1 - G.alpha) / (T)kLn2;
+  da += de0 * ((T)1 - G.alpha) * (T)(1.0 / kLn2);
   const T dr2 = -(T)kHalfLog2e * de0;
   // T22 = detM n3 / T11, T12 = b1.b2 / T11, T11 = |b1|
-  const T iT11 = (T)1 / k.T11;
+  const T iT11 = k.iT11;
   const T detM = k.detL * P.absdet;
   const T dT11t = dT11 - (dT12 * k.T12 + dT22 * k.T22) * iT11;
   const T ddetL = dT22 * P.absdet * k.n3 * iT11;
@@ -565,7 +572,7 @@ __device__ __forceinline__ void footprint_adjoint(const GaussT<T>& G, const Plan
   const T dS13 = -dc1 * k.m3 * iS;
   const T dS23 = -dc2 * k.m3 * iS;
   const T dS33 = (dc1 * k.m3 * k.S13 + dc2 * k.m3 * k.S23 - dr2 * k.m3 * k.m3) * iS * iS;
-  const T in3 = (T)1 / k.n3;
+  const T in3 = k.in3;
   T dg1[3], dg2[3], dg3[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) {

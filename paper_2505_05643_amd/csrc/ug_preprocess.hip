@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, const PlaneC
     const bool has = gi < rp.n;
     GaussT<float> G;
     G.finite = false;
-    if (has) load_gauss<float>(g, gi, rp.beta, G);
+    if (has) load_gauss<float>(g, gi, rp.beta, G, true);
     if (has && sub == 0 && !G.finite) atomicOr(&ctrl->flags, kFlagNonfinite);
     const bool live = has && G.finite;
     uint32_t count = 0;
@@ -423,8 +423,8 @@ __device__ __forceinline__ uint32_t record_rpb_dev(uint32_t nrec, uint32_t grid)
 }
 __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, const RowSpans& spans,
                                           const PlaneInt& PI, bool by_rows, int TW, int TH, int tile_bits, uint32_t r,
-                                          uint32_t e, uint32_t e_end, uint32_t* __restrict__ key_tile,
-                                          uint32_t* __restrict__ rec_of_key) {
+                                          uint32_t e, uint32_t e_end, uint32_t part, uint32_t parts,
+                                          uint32_t* __restrict__ key_tile, uint32_t* __restrict__ rec_of_key) {
   const int mshift = key_mask_shift(TW, TH);
   const uint32_t e0 = e, last_index = (1u << (mshift - tile_bits)) - 1u;  // indices from here on: looked up
   const bool known = by_rows && geo.tx1 - geo.tx0 <= kSpanTiles - 1;
@@ -448,6 +448,10 @@ __device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, c
       } else if (!rows_span(bp, ty, TW, TH, PI.H, umin, umax, tx0, tx1)) {
         continue;
       }
+    }
+    if (((uint32_t)(ty - (int)geo.ty0) & (parts - 1u)) != part) {
+      e += (uint32_t)(tx1 - tx0 + 1);
+      continue;
     }
     int ca[kMaxBands], cz[kMaxBands];
 #pragma unroll
@@ -641,8 +645,18 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
   }
 }
 
+// Launches of up to kEmitPartBlocks record blocks give every block's records
+// to kEmitParts blocks, each writing the tile rows i with i % kEmitParts ==
+// part: so few blocks leave most CUs idle, and a CU that has one spends its
+// time on the scattered stores of its records' keys.  9 K records with 90 K
+// keys (36 blocks): 40 us with one block each, 16 with four.  The line: at
+// 400 blocks the four repeat the prefix and the scan for nothing (12.1 us
+// against 15.1 at 79 K records with 160 K keys).
+constexpr uint32_t kEmitParts = 4, kEmitPartBlocks = 128;
+
 // Key offsets (block prefix + in-block scan) and key emission.  The last
 // active block publishes the key total and the capacity check.
+template <uint32_t PARTS>
 __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint, RenderParams rp,
                                               const uint2* __restrict__ rec_pair, const Rec* __restrict__ recs,
                                               const uint32_t* __restrict__ rec_nkey,
@@ -651,8 +665,9 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
                                               uint32_t* __restrict__ rec_of_key) {
   __shared__ unsigned long long s_sh[4];
   const uint32_t nrec = ctrl->n_rec_eff;
-  const uint32_t rpb = record_rpb_dev(nrec, gridDim.x);
-  const uint32_t r_begin = blockIdx.x * rpb;
+  const uint32_t blk = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+  const uint32_t rpb = record_rpb_dev(nrec, gridDim.x / PARTS);
+  const uint32_t r_begin = blk * rpb;
   if (r_begin >= nrec) return;  // uniform
   const uint32_t nact = (nrec + rpb - 1) / rpb;
   const uint32_t r_end = min(r_begin + rpb, nrec);
@@ -678,7 +693,7 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     sp = recs[rl].spans;
     nk = act ? rec_nkey[rl] : 0u;
   }
-  unsigned long long carry = block_prefix(blk_tot, blockIdx.x, s_sh);
+  unsigned long long carry = block_prefix(blk_tot, blk, s_sh);
   PlaneInt PI = pint[pl];
   for (uint32_t r0 = r_begin; r0 < r_end; r0 += 256) {
     const uint32_t rn = r + 256u;
@@ -694,10 +709,10 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     const unsigned long long koff = carry + block_exscan_256<unsigned long long>(nk, s_sh, tot);
     carry += tot;
     if (act) {
-      rec_koff[r] = (uint32_t)(koff < rp.key_cap ? koff : rp.key_cap);
+      if (part == 0) rec_koff[r] = (uint32_t)(koff < rp.key_cap ? koff : rp.key_cap);
       if (nk > 0 && koff + nk <= rp.key_cap)
         emit_keys(ra, ge, sp, PI, rp.by_rows != 0, rp.tile_w, rp.tile_h, rp.tile_bits, r, (uint32_t)koff,
-                  (uint32_t)(koff + nk), key_tile, rec_of_key);
+                  (uint32_t)(koff + nk), part, PARTS, key_tile, rec_of_key);
     }
     r = rn;
     act = actn;
@@ -707,12 +722,13 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     sp = spn;
     PI = pint[pln];
   }
+  if (part != 0) return;
   __syncthreads();  // rec_koff of the block's records
   if (threadIdx.x < kRuns) {
     const uint32_t rr = r_begin + threadIdx.x * (rpb / kRuns);
-    if (rr < r_end) run_koff[blockIdx.x * kRuns + threadIdx.x] = rec_koff[rr];
+    if (rr < r_end) run_koff[blk * kRuns + threadIdx.x] = rec_koff[rr];
   }
-  if (blockIdx.x == nact - 1 && threadIdx.x == 0) {
+  if (blk == nact - 1 && threadIdx.x == 0) {
     const unsigned long long counted = rp.by_rows && rp.box_mode == UG_BOX_PAPER ? ctrl->n_key : carry;
     ctrl->n_key = counted;
     const bool ok = counted <= rp.key_cap;
@@ -789,6 +805,43 @@ __device__ __forceinline__ PlaneT<float> plane_from_lds(const float* d) {
   return P;
 }
 
+
+// How a record's partials are added (always in emission order, so all three
+// give the same bits):
+//  - COOP, launches of up to kCoopBlocks waves of records: a block per 64
+//    records, whose four waves bring their keys through LDS and add them eight
+//    lanes to a record.  Few waves have the chip to themselves and the time is
+//    the longest one's: 9 K records with 90 K keys, some with hundreds each,
+//    29 us with a lane walking its record's keys, 15 here; at 79 K records with
+//    two keys each both take 9.5.
+//  - kStagedKeys or more keys per record on average: the wave brings its keys
+//    through LDS, loaded side by side while the ones before are added, a lane
+//    per record.  25M keys of 2.1M records 138 us (190 with each lane reading
+//    its record's from memory), 11.8M of 3.6M 124 (144).
+//  - else each lane reads its own, two per step: 33M keys of 16M records 395
+//    us, 420 through LDS (two round trips per wave there as well, and the LDS
+//    on top).
+// Bound by its 640 VALU instructions per 64 records (a third of them the
+// segmented scan) and the round trips before them: 16M records 410 us with
+// exact divisions and the scan over LDS shuffles.
+constexpr uint32_t kCoopBlocks = 2048;
+constexpr uint32_t kStagedKeys = 3;
+
+// Adds to every value that of the lane the DPP control names, where that lane
+// holds the same Gaussian (rows outside the mask, and lanes it names no lane
+// for, see id ~0).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ void seg_add(uint32_t gid, float (&v)[kGradFields]) {
+  const uint32_t gu = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)gid, kCtrl, kRows, 0xf, false);
+  const bool add = gu == gid;
+#pragma unroll
+  for (int j = 0; j < kGradFields; ++j) {
+    const float y = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v[j]), kCtrl, kRows, 0xf, true));
+    v[j] += add ? y : 0.f;
+  }
+}
+
+template <bool COOP>
 __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const PlaneConst* __restrict__ pc,
                                                         RenderParams rp, const Ctrl* __restrict__ ctrl,
                                                         const uint2* __restrict__ rec_pair,
@@ -800,6 +853,10 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
                                                         float* __restrict__ d_lraw, float* __restrict__ d_int,
                                                         float* __restrict__ d_op, int accumulate) {
   extern __shared__ float s_plane[];  // rp.p x kPlaneFloats when staged
+  constexpr int kKeyPitch = 3;        // float4 per key in LDS: two and one of padding (banks)
+  constexpr int kSumPitch = 9;
+  __shared__ float4 s_key[COOP ? 512 : 4 * 64 * kKeyPitch];
+  __shared__ float s_sum[COOP ? 64 * kSumPitch : 1];
   const bool staged = rp.p <= kStagePlanes;
   if (staged) {
     for (int q = threadIdx.x; q < rp.p; q += 256) plane_to_lds(plane_as<float>(pc[q]), s_plane + q * kPlaneFloats);
@@ -809,24 +866,82 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
   const uint32_t nrec = ok ? ctrl->n_rec_eff : 0u;
   const uint32_t nw = (nrec + 63u) / 64u;
   const float chi2 = rp.chi2;
-  const int lane = threadIdx.x & 63;
-  for (uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6); w < nw; w += gridDim.x * 4u) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool many = COOP || (unsigned long long)(ok ? ctrl->n_key_eff : 0u) >= (unsigned long long)kStagedKeys * nrec;
+  uint32_t w = COOP ? blockIdx.x : blockIdx.x * 4u + (uint32_t)wave;
+  for (; w < nw; w += COOP ? gridDim.x : gridDim.x * 4u) {
+    if (COOP) {
+      // 256 keys at a time go through LDS; eight neighbouring lanes add a
+      // record's keys, one value each, in order
+      const uint32_t rb = w * 64u;
+      const uint32_t ka = rec_koff[rb], kb = rec_koff[min(rb + 64u, nrec)];
+      const int fq = (int)(threadIdx.x & 7u), q0 = (int)(threadIdx.x >> 3);
+      uint32_t qa[2], qz[2];
+      float acc[2] = {0.f, 0.f};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t rq = min(rb + (uint32_t)(q0 + 32 * h), nrec);
+        qa[h] = rec_koff[rq];
+        qz[h] = rq < nrec ? rec_koff[rq + 1] : qa[h];
+      }
+      const float4* p4 = partial + 2 * (size_t)ka;
+      const uint32_t n4 = 2u * (kb - ka);
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+      if (threadIdx.x < n4) x = p4[threadIdx.x];
+      if (threadIdx.x + 256u < n4) y = p4[threadIdx.x + 256u];
+      for (uint32_t kc = ka; kc < kb; kc += 256) {
+        __syncthreads();  // the chunk before, and the block's sums before, are read
+        s_key[threadIdx.x] = x;
+        s_key[threadIdx.x + 256] = y;
+        __syncthreads();
+        const uint32_t nx = 2u * (kc + 256u - ka) + threadIdx.x;
+        if (nx < n4) x = p4[nx];
+        if (nx + 256u < n4) y = p4[nx + 256u];
+        const float* sk = reinterpret_cast<const float*>(s_key);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t ke = min(qz[h], kc + 256u);
+          uint32_t k = max(qa[h], kc);
+          for (; k + 8u <= ke; k += 8) {
+            float t[8];
+#pragma unroll
+            for (uint32_t u = 0; u < 8; ++u) t[u] = sk[8u * (k + u - kc) + (uint32_t)fq];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc[h] += t[u];
+          }
+          for (; k < ke; ++k) acc[h] += sk[8u * (k - kc) + (uint32_t)fq];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) s_sum[(q0 + 32 * h) * kSumPitch + fq] = acc[h];
+      __syncthreads();
+      if (wave != 0) continue;
+    }
     const uint32_t r = w * 64u + (uint32_t)lane;
     const bool act = r < nrec;
     float v[kGradFields];
 #pragma unroll
     for (int j = 0; j < kGradFields; ++j) v[j] = 0.f;
     uint32_t gid = 0xffffffffu;
-    if (act) {
-      const uint2 gp = rec_pair[r];
-      gid = gp.x;
-      const uint32_t k0 = rec_koff[r], k1 = rec_koff[r + 1];
-      // the Gaussian's parameters are loaded with the key range, so the two
-      // round trips overlap
-      const GaussRaw gr = load_gauss_raw(g, (int)gp.x);
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
-      // two keys per step, both loaded before either is added (same order
-      // of additions as one key at a time)
+    // lanes past the last record take it and no key of it; the Gaussian's
+    // parameters are loaded with the key range, so the two round trips overlap
+    const uint32_t rl = act ? r : nrec - 1u;
+    const uint2 gp = rec_pair[rl];
+    const uint32_t kend = rec_koff[rl + 1];
+    const uint32_t k0 = act ? rec_koff[rl] : kend, k1 = kend;
+    const GaussRaw gr = load_gauss_raw(g, (int)gp.x);
+    const uint64_t goff = off_rec[gp.x];
+    const uint32_t gcnt = cnt_rec[gp.x];
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
+    const uint32_t ka = (uint32_t)__builtin_amdgcn_readfirstlane((int)k0);
+    const uint32_t kb = (uint32_t)__builtin_amdgcn_readlane((int)k1, 63);
+    if constexpr (COOP) {
+      const float* f = s_sum + lane * kSumPitch;
+      a = make_float4(f[0], f[1], f[2], f[3]);
+      c = make_float4(f[4], f[5], f[6], 0.f);
+    } else if (!many) {
+      // two keys per step, both loaded before either is added
       for (uint32_t k = k0; k < k1; k += 2) {
         const float4 x0 = partial[2 * (size_t)k], y0 = partial[2 * (size_t)k + 1];
         const bool two = k + 1 < k1;
@@ -836,14 +951,37 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
           y1 = partial[2 * (size_t)k + 3];
         }
         a.x += x0.x; a.y += x0.y; a.z += x0.z; a.w += x0.w;
-        c.x += y0.x; c.y += y0.y; c.z += y0.z; c.w += y0.w;
-        if (two) {
-          a.x += x1.x; a.y += x1.y; a.z += x1.z; a.w += x1.w;
-          c.x += y1.x; c.y += y1.y; c.z += y1.z; c.w += y1.w;
-        }
+        c.x += y0.x; c.y += y0.y; c.z += y0.z;
+        a.x += x1.x; a.y += x1.y; a.z += x1.z; a.w += x1.w;
+        c.x += y1.x; c.y += y1.y; c.z += y1.z;
       }
+    } else if (ka < kb) {
+      // the wave's keys are contiguous: 64 at a time
+      float4* s_wave = s_key + wave * 64 * kKeyPitch;
+      const size_t j = min(ka + (uint32_t)lane, kb - 1u);
+      float4 x = partial[2 * j], y = partial[2 * j + 1];
+      for (uint32_t kc = ka; kc < kb; kc += 64) {
+        s_wave[lane * kKeyPitch] = x;
+        s_wave[lane * kKeyPitch + 1] = y;
+        if (kc + 64u < kb) {
+          const size_t jn = min(kc + 64u + (uint32_t)lane, kb - 1u);
+          x = partial[2 * jn];
+          y = partial[2 * jn + 1];
+        }
+        wave_lds_sync();
+        const uint32_t ke = min(k1, kc + 64u);
+        for (uint32_t k = max(k0, kc); k < ke; ++k) {
+          const float4 x0 = s_wave[(k - kc) * kKeyPitch], y0 = s_wave[(k - kc) * kKeyPitch + 1];
+          a.x += x0.x; a.y += x0.y; a.z += x0.z; a.w += x0.w;
+          c.x += y0.x; c.y += y0.y; c.z += y0.z;
+        }
+        wave_lds_sync();
+      }
+    }
+    if (act) {
+      gid = gp.x;
       if (k1 > k0) {
-        const float dr[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+        const float dr[7] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z};
         GaussT<float> G;
         gauss_setup(gr, rp.beta, G);
         const PlaneT<float> P = staged ? plane_from_lds(s_plane + gp.y * kPlaneFloats) : plane_as<float>(pc[gp.y]);
@@ -858,23 +996,19 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
         v[10] = dc;
       }
     }
-    // segmented inclusive scan over equal Gaussian ids (ids are sorted)
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t gu = __shfl_up(gid, o, 64);
-      const bool add = lane >= o && gu == gid;
-#pragma unroll
-      for (int j = 0; j < kGradFields; ++j) {
-        const float y = __shfl_up(v[j], o, 64);
-        if (add) v[j] += y;
-      }
-    }
+    // segmented inclusive scan over equal Gaussian ids (ids are sorted): within
+    // rows of 16 lanes, then over the rows
+    seg_add<0x111, 0xf>(gid, v);  // lane - 1
+    seg_add<0x112, 0xf>(gid, v);  // lane - 2
+    seg_add<0x114, 0xf>(gid, v);  // lane - 4
+    seg_add<0x118, 0xf>(gid, v);  // lane - 8
+    seg_add<0x142, 0xa>(gid, v);  // the previous row's last lane, rows 1 and 3
+    seg_add<0x143, 0xc>(gid, v);  // lane 31, rows 2 and 3
     const uint32_t gnext = __shfl_down(gid, 1, 64);
     const uint32_t g0 = __shfl(gid, 0, 64);
     const bool seg_end = act && (lane == 63 || gnext != gid);
     if (seg_end) {
-      const uint64_t o = off_rec[gid];
-      const uint64_t e = o + cnt_rec[gid];
+      const uint64_t o = goff, e = o + gcnt;
       if (o >= (uint64_t)w * 64u && e <= (uint64_t)w * 64u + 64u)
         write_gauss_grad(g, (int)gid, v, d_means, d_lraw, d_int, d_op, accumulate);
       float* sd = side + (size_t)w * 2 * kGradFields;
@@ -1045,8 +1179,13 @@ hipError_t launch_record(const ug_gaussians& g, const PlaneConst* pc, const Plan
 hipError_t launch_emit(const PlaneInt* pint, const RenderParams& rp, const uint2* rec_pair, const Rec* recs,
                        const uint32_t* rec_nkey, const uint32_t* blk_tot, uint32_t* rec_koff, uint32_t* run_koff,
                        Ctrl* ctrl, uint32_t* key_tile, uint32_t* rec_of_key, hipStream_t s) {
-  hipLaunchKernelGGL(k_emit, dim3(record_blocks(rp.rec_cap)), dim3(256), 0, s, pint, rp,
-                     rec_pair, recs, rec_nkey, blk_tot, rec_koff, run_koff, ctrl, key_tile, rec_of_key);
+  const uint32_t blocks = (uint32_t)record_blocks(rp.rec_cap);
+  if (blocks <= kEmitPartBlocks)
+    hipLaunchKernelGGL(k_emit<kEmitParts>, dim3(blocks * kEmitParts), dim3(256), 0, s, pint, rp, rec_pair, recs,
+                       rec_nkey, blk_tot, rec_koff, run_koff, ctrl, key_tile, rec_of_key);
+  else
+    hipLaunchKernelGGL(k_emit<1>, dim3(blocks), dim3(256), 0, s, pint, rp, rec_pair, recs, rec_nkey, blk_tot,
+                       rec_koff, run_koff, ctrl, key_tile, rec_of_key);
   return hipGetLastError();
 }
 
@@ -1063,9 +1202,15 @@ hipError_t launch_record_adjoint(const ug_gaussians& g, const PlaneConst* pc, co
   const uint32_t cap = staged ? 2048u : 8192u;
   const uint32_t blocks = want < 1 ? 1 : (want > cap ? cap : want);
   const size_t lds = staged ? (size_t)rp.p * kPlaneFloats * sizeof(float) : 0;
-  hipLaunchKernelGGL(k_record_adjoint, dim3(blocks), dim3(256), lds, s, g, pc, rp, ctrl, rec_pair, rec_koff,
-                     reinterpret_cast<const float4*>(partial), cnt_rec, off_rec, side, d_means, d_lraw, d_int, d_op,
-                     accumulate);
+  const uint32_t coop = (rp.rec_cap + 63u) / 64u;
+  if (coop <= kCoopBlocks)
+    hipLaunchKernelGGL(k_record_adjoint<true>, dim3(coop < 1 ? 1 : coop), dim3(256), lds, s, g, pc, rp, ctrl, rec_pair,
+                       rec_koff, reinterpret_cast<const float4*>(partial), cnt_rec, off_rec, side, d_means, d_lraw,
+                       d_int, d_op, accumulate);
+  else
+    hipLaunchKernelGGL(k_record_adjoint<false>, dim3(blocks), dim3(256), lds, s, g, pc, rp, ctrl, rec_pair, rec_koff,
+                       reinterpret_cast<const float4*>(partial), cnt_rec, off_rec, side, d_means, d_lraw, d_int, d_op,
+                       accumulate);
   return hipGetLastError();
 }
 
