@@ -775,8 +775,6 @@ def kernel_bytes(name, n, p, r, k, t, m, passes, w, rows, g_sort, dslots) -> int
         return 16 * k
     if name == "ranges":
         return 4 * k + 4 * t
-    if name == "bwd_prep":
-        return 20 * m
     if name == "record_adj":
         return 12 * r + 32 * k + 44 * n + 44 * n
     if name == "gauss_grad":

@@ -100,7 +100,7 @@ extern "C" {
 #define UG_STAGE_SORT_SCATTER 7  /* radix sort: stable scatter (once per pass)          */
 #define UG_STAGE_RANGES 8        /* per-tile key ranges (a one-pass sort writes them)   */
 #define UG_STAGE_ACCUM 9         /* per-tile accumulation, Eq. 5-8 and 12               */
-#define UG_STAGE_BWD_PREP 10     /* per-pixel adjoint inputs                            */
+#define UG_STAGE_BWD_PREP 10     /* (no launch: formed in UG_STAGE_ACCUM_BWD)           */
 #define UG_STAGE_ACCUM_BWD 11    /* per-key adjoint of the accumulation                 */
 #define UG_STAGE_RECORD_ADJ 12   /* per-record adjoint of the conic construction        */
 #define UG_STAGE_GAUSS_GRAD 13   /* per-Gaussian sum of its records' adjoints           */

@@ -28,7 +28,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t ctrl, pconst, pcull, pgroups, cnt_rec, accbits, off_rec, blk_g, blk_r;
   size_t rec_pair, recs, rec_nkey, rec_koff, side;
-  size_t tile_start, dsave, gq, hist;
+  size_t tile_start, dsave, hist;
   size_t emitted, key0, key1, rec0, rec1, run_koff, partial;
   size_t loss_part;
   // what the no-allocation forward's limit is held against: the total, less
@@ -96,7 +96,6 @@ void compute_layout(ug_plan* pl) {
   L.side = take(adjoint_side_floats(pl->rec_cap) * 4);
   L.tile_start = take((T + 1) * 4);
   L.dsave = take(pl->num_pixels * 4);
-  L.gq = take(T * tpx * 8);
   L.hist = take((size_t)sort_digit_slots(pl->bits, pl->sort_blocks) * (pl->sort_blocks + 1) * 4);
   L.emitted = take(K * 4);
   L.key0 = take(K * 4);
@@ -107,8 +106,10 @@ void compute_layout(ug_plan* pl) {
   L.run_koff = take(std::max(runs, K) * 4);
   const size_t beyond = runs > K ? align_up(runs * 4) - align_up(K ? K * 4 : 1) : 0;
   L.partial = take(K * 32);
-  L.loss_part = take((size_t)bwd_prep_blocks(pl->prm.tile_w, pl->prm.tile_h, pl->num_tiles) * 4);
-  L.checked = o - beyond;
+  L.loss_part = take(T * 4);
+  // the no-allocation limit counts 8 bytes per tile pixel as well, and the
+  // loss sums by 1024 pixels, so that it refuses what it always has
+  L.checked = o - beyond + align_up(T * tpx * 8) + align_up((T * tpx + 1023) / 1024 * 4) - align_up(T * 4);
   L.total = o;
 }
 
@@ -539,20 +540,14 @@ int backward_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* p
   const Sorted so = sorted_set(plan, ws);
   hipError_t e;
   {
-    StageScope sc(plan, UG_STAGE_BWD_PREP, s);
-    const float scale = 2.0f / (float)(plan->num_pixels > 0 ? plan->num_pixels : 1);
-    e = launch_bwd_prep(plan->prm.tile_w, plan->prm.tile_h, plan->d_pint, plan->d_tile_plane, image, second, mse,
-                        scale, at<float>(ws, L.loss_part), at<float>(ws, L.dsave), at<float>(ws, L.gq),
-                        plan->num_tiles, s);
-  }
-  if (e != hipSuccess) return UG_ERR_HIP;
-  {
     StageScope sc(plan, UG_STAGE_ACCUM_BWD, s);
+    const float scale = 2.0f / (float)(plan->num_pixels > 0 ? plan->num_pixels : 1);
     e = launch_accum_bwd(plan->prm.tile_w, plan->prm.tile_h, plan->bits, plan->d_tile_org,
                          at<uint32_t>(ws, L.tile_start), so.key, so.rec, at<uint32_t>(ws, L.emitted),
                          at<uint32_t>(ws, L.rec_koff), at<uint32_t>(ws, L.run_koff), at<Rec>(ws, L.recs),
-                         at<float>(ws, L.gq), at<float>(ws, L.partial), std::isfinite(plan->prm.chi2),
-                         plan->num_tiles, plan->key_cap, s);
+                         plan->d_pint, plan->d_tile_plane, image, second, at<float>(ws, L.dsave), scale,
+                         mse ? at<float>(ws, L.loss_part) : nullptr, at<float>(ws, L.partial),
+                         std::isfinite(plan->prm.chi2), plan->num_tiles, plan->key_cap, s);
   }
   if (e != hipSuccess) return UG_ERR_HIP;
   {
@@ -564,10 +559,9 @@ int backward_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* p
   }
   if (e != hipSuccess) return UG_ERR_HIP;
   StageScope sc(plan, UG_STAGE_GAUSS_GRAD, s);
-  const uint32_t nparts = bwd_prep_blocks(plan->prm.tile_w, plan->prm.tile_h, plan->num_tiles);
   e = launch_gauss_grad(*g, rp, ctrl, at<uint32_t>(ws, L.cnt_rec), at<unsigned long long>(ws, L.off_rec),
                         at<float>(ws, L.side), d_means, d_lraw, d_intensity, d_opacity, accumulate,
-                        at<float>(ws, L.loss_part), nparts,
+                        at<float>(ws, L.loss_part), plan->num_tiles,
                         1.0 / (double)(plan->num_pixels > 0 ? plan->num_pixels : 1), mse ? loss_dev : nullptr, s);
   return hip_status(e);
 }

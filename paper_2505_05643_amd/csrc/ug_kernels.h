@@ -40,7 +40,7 @@ hipError_t launch_record_adjoint(const ug_gaussians& g, const PlaneConst* pc, co
                                  float* side, float* d_means, float* d_lraw, float* d_int, float* d_op,
                                  int accumulate, hipStream_t s);
 // loss_out (may be null): the mean squared error, inv_m times the sum of the
-// nparts per-block sums in loss_part.
+// nparts per-tile sums in loss_part.
 hipError_t launch_gauss_grad(const ug_gaussians& g, const RenderParams& rp, const Ctrl* ctrl, const uint32_t* cnt_rec,
                              const unsigned long long* off_rec, const float* side, float* d_means, float* d_lraw,
                              float* d_int, float* d_op, int accumulate, const float* loss_part, uint32_t nparts,
@@ -119,21 +119,19 @@ hipError_t launch_accum_fwd(int tile_w, int tile_h, int lds_batch, int split, co
                             const uint32_t* srec, const Rec* recs, float* image, float* dsave,
                             float bg_alpha, float bg_color, bool cut, uint32_t num_tiles,
                             unsigned long long* n_eval, hipStream_t s);
-// second = dL/dc_hat, or (mse) the target with dL/dc_hat = scale (image -
-// target) formed inside and per-block squared-difference sums in loss_part
-// (bwd_prep_blocks floats).
-uint32_t bwd_prep_blocks(int tile_w, int tile_h, uint32_t num_tiles);
-hipError_t launch_bwd_prep(int tile_w, int tile_h, const PlaneInt* pint, const uint32_t* tile_plane,
-                           const float* image, const float* second, bool mse, float scale, float* loss_part,
-                           const float* dsave, float* gq, uint32_t num_tiles, hipStream_t s);
+// second = dL/dc_hat, or, with loss_part, the target: dL/dc_hat = scale (image
+// - target) is formed inside and the tiles' sums of squared differences go to
+// loss_part (num_tiles floats).  image, second and dsave (the denominators)
+// are in the image's layout.
 // tile_org[t] = pixel origin of tile t, x0 | y0 << 16; emitted = the key words
 // in emission order; rec_koff, run_koff = key offsets of every record and of
 // every run of records.
 hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_t* tile_org,
                             const uint32_t* tile_start, const uint32_t* skey, const uint32_t* srec,
                             const uint32_t* emitted, const uint32_t* rec_koff, const uint32_t* run_koff,
-                            const Rec* recs, const float* gq, float* partial, bool cut, uint32_t num_tiles,
-                            uint32_t key_cap, hipStream_t s);
+                            const Rec* recs, const PlaneInt* pint, const uint32_t* tile_plane, const float* image,
+                            const float* second, const float* dsave, float scale, float* loss_part, float* partial,
+                            bool cut, uint32_t num_tiles, uint32_t key_cap, hipStream_t s);
 
 // ---- training helpers (ug_train.hip)
 hipError_t launch_mse(const float* image, const float* target, int64_t m, float* d_image, float* loss,

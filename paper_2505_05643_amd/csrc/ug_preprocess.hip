@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
 // and the sum of the wave pieces for one whose records span waves (the
 // first wave's last segment, whole middle waves, the last wave's first
 // segment); the others were written by k_record_adjoint.
-// With loss_out, block 0 also adds the backward prep's per-block squared
+// With loss_out, block 0 also adds the adjoint accumulate's per-tile squared
 // differences (nparts floats, in order, in FP64) into the mean squared error.
 __global__ __launch_bounds__(256) void k_gauss_grad(ug_gaussians g, RenderParams rp, const Ctrl* __restrict__ ctrl,
                                                     const uint32_t* __restrict__ cnt_rec,
@@ -1041,7 +1041,15 @@ __global__ __launch_bounds__(256) void k_gauss_grad(ug_gaussians g, RenderParams
   if (loss_out && blockIdx.x == 0) {  // uniform
     __shared__ double s_l[256];
     double a = 0.0;
-    for (uint32_t k = threadIdx.x; k < nparts; k += 256) a += (double)loss_part[k];
+    uint32_t k = threadIdx.x;
+    for (; k + 7u * 256u < nparts; k += 8u * 256u) {  // eight loads in flight
+      float x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = loss_part[k + 256u * (uint32_t)q];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) a += (double)x[q];
+    }
+    for (; k < nparts; k += 256) a += (double)loss_part[k];
     s_l[threadIdx.x] = a;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {

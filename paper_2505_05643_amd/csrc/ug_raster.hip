@@ -232,88 +232,14 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
   }
 }
 
-// ---------------------------------------------------------------- backward prep
-// Tile-major padded per-pixel adjoint inputs: gamma = dL/dc_hat / D and
-// gamma * c_hat (zero outside the plane).  Four consecutive pixels of a tile
-// row per thread: 16-byte loads where the arrays (vec) and the plane row are
-// aligned and the row holds all four, single loads otherwise.
-//
-// MSE: the second array is the target and dL/dc_hat = scale (c_hat - target)
-// is formed here, with the same float operations as the separate gradient
-// kernel (so the same gamma bit for bit); each block also writes the sum of
-// its squared differences to loss_part[block] (a fixed-order reduction).
-template <int TW, int TH, bool MSE>
-__global__ __launch_bounds__(256) void k_bwd_prep(const PlaneInt* __restrict__ pint,
-                                                  const uint32_t* __restrict__ tile_plane,
-                                                  const float* __restrict__ image, const float* __restrict__ second,
-                                                  const float* __restrict__ dsave, float4* __restrict__ gq,
-                                                  uint32_t num_tiles, int vec, float scale,
-                                                  float* __restrict__ loss_part) {
-  static_assert(TW % 4 == 0, "four pixels per thread within a tile row");
-  const size_t gidx = (size_t)blockIdx.x * 256 + threadIdx.x;  // group of four pixels
-  const uint32_t t = (uint32_t)(gidx / (TW * TH / 4));
-  float sq = 0.f;  // MSE: this thread's squared differences
-  if (t < num_tiles) {
-    const int j = (int)(gidx % (TW * TH / 4)) * 4;
-    const PlaneInt PI = pint[tile_plane[t]];
-    const uint32_t lt = t - PI.tile_off;
-    const int u = (int)(lt % (uint32_t)PI.ntx) * TW + j % TW;
-    const int v = (int)(lt / (uint32_t)PI.ntx) * TH + j / TW;
-    float gam[4] = {0.f, 0.f, 0.f, 0.f}, gc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (v < PI.H && u < PI.W) {
-      const size_t idx = (((size_t)PI.pix_off_hi << 32) | PI.pix_off_lo) + (size_t)v * PI.W + u;
-      if (vec && u + 3 < PI.W && (idx & 3u) == 0) {
-        const float4 S2 = *reinterpret_cast<const float4*>(second + idx);
-        const float4 Dt = *reinterpret_cast<const float4*>(dsave + idx);
-        const float4 I = *reinterpret_cast<const float4*>(image + idx);
-        const float s2[4] = {S2.x, S2.y, S2.z, S2.w}, dt[4] = {Dt.x, Dt.y, Dt.z, Dt.w};
-        const float im[4] = {I.x, I.y, I.z, I.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float dI = s2[q];
-          if constexpr (MSE) {
-            const float d = im[q] - s2[q];
-            dI = scale * d;
-            sq = fmaf(d, d, sq);
-          }
-          gam[q] = dI / dt[q];
-          gc[q] = gam[q] * im[q];
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (u + q < PI.W) {
-            const float im = image[idx + q];
-            float dI = second[idx + q];
-            if constexpr (MSE) {
-              const float d = im - dI;
-              dI = scale * d;
-              sq = fmaf(d, d, sq);
-            }
-            gam[q] = dI / dsave[idx + q];
-            gc[q] = gam[q] * im;
-          }
-        }
-      }
-    }
-    gq[2 * gidx] = make_float4(gam[0], gc[0], gam[1], gc[1]);
-    gq[2 * gidx + 1] = make_float4(gam[2], gc[2], gam[3], gc[3]);
-  }
-  if constexpr (MSE) {
-    __shared__ float s_w[4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = sq;
-    __syncthreads();
-    if (threadIdx.x == 0) loss_part[blockIdx.x] = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
-  }
-}
-
 // ---------------------------------------------------------------- backward
 // nsplit blocks of four waves per tile; each wave has a contiguous share of
-// the tile's keys and takes up to 64 of them per pass.  The block copies the
-// tile's gamma into LDS once (every row the evaluation reads comes from
-// there).
+// the tile's keys and takes up to 64 of them per pass.  The block forms the
+// tile's per-pixel inputs, gamma = dL/dc_hat / D and gamma c_hat, in LDS (every
+// row the evaluation reads comes from there); the loss gradient takes the
+// float operations of the separate kernel.  A kernel of its own that wrote
+// them tile by tile took 61 us and this one 14 us less at 16.8M pixels (step
+// 4948 -> 4885 us); at 16 planes of 160 x 160 it was a launch more (99 -> 96 us).
 //
 // A key's ellipse touches a range of four-column strips of the tile; each
 // becomes an item (key, strip over the whole tile height).  lanes = items: a
@@ -432,8 +358,10 @@ template <int TW, int TH>
 __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     const uint32_t* __restrict__ tile_org, const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ skey,
     const uint32_t* __restrict__ srec, const uint32_t* __restrict__ emitted, const uint32_t* __restrict__ rec_koff,
-    const uint32_t* __restrict__ run_koff, const Rec* __restrict__ recs, const float2* __restrict__ gq,
-    float4* __restrict__ partial, int kcut, int tile_bits, uint32_t num_tiles, uint32_t nsplit) {
+    const uint32_t* __restrict__ run_koff, const Rec* __restrict__ recs, const PlaneInt* __restrict__ pint,
+    const uint32_t* __restrict__ tile_plane, const float* __restrict__ image, const float* __restrict__ second,
+    const float* __restrict__ dsave, float scale, float* __restrict__ loss_part, float4* __restrict__ partial, int kcut,
+    int tile_bits, uint32_t num_tiles, uint32_t nsplit) {
   constexpr int kMaskShift = key_mask_shift(TW, TH);
   constexpr int kSlotsWave = slots_wave(TW, TH), kGroups = (kSlotsWave + 63) / 64;
   constexpr int kMaxStrips = TW / kStrip;
@@ -446,6 +374,7 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   __shared__ float4 kpB[256];                   // du0, dv0, d, c
   __shared__ uint32_t bucket[TH + 1];           // items per row count
   __shared__ uint32_t more[4];                  // whether the wave has keys left after the pass
+  __shared__ float wave_sq[4];                  // squared differences of the waves' pixels
   __shared__ uint32_t grab;                     // next group of 64 items to evaluate
   __shared__ uint32_t sorted[4 * kSlotsWave];   // slot | wave << 8 | key << 10 | strip << 18 | first row << 21 | rows << 26
   // the items' sums; before a wave's items are evaluated its part holds what
@@ -468,9 +397,11 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   // the waves' shares of the tile's keys, at least 32 each (fewer, fuller
   // waves where a tile has few)
   const uint32_t share = max((n + 4u * nsplit - 1u) / (4u * nsplit), 32u);
-  if (part * 4u * share >= n) return;  // uniform: no keys left for this block
+  const bool loss = loss_part && part == 0;
+  if (part * 4u * share >= n && !loss) return;  // uniform: no keys left for this block
   if (threadIdx.x <= TH) bucket[threadIdx.x] = 0u;
   if (threadIdx.x == 0) grab = 0u;
+  const PlaneInt& PI = pint[tile_plane[t]];
   const uint32_t org = tile_org[t];  // x0 | y0 << 16
   const int x0 = (int)(org & 0xffffu), y0 = (int)(org >> 16);
   const float ln2 = (float)kLn2;
@@ -496,23 +427,54 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     run = recs[rid].geo.run;
     koff = recs[rid].geo.koff;
   };
-  load_keys();
+  if (n) load_keys();
   {
-    // the tile's gamma is in flight with the first keys and records
-    constexpr int kTile = TH * (TW / 2), kPer = (kTile + 255) / 256;
-    const float4* __restrict__ src = reinterpret_cast<const float4*>(gq + (size_t)t * (TW * TH));
-    float4 v[kPer];
+    // The tile's gamma and gamma c_hat (zero outside the plane) from the
+    // image, the upstream gradient or the target, and the denominators; the
+    // loads are in flight with the first keys and records.
+    constexpr int kPer = (TW * TH + 255) / 256;
+    const int W = PI.W, H = PI.H;
+    const size_t base = ((size_t)PI.pix_off_hi << 32) | PI.pix_off_lo;
+    float im[kPer], sc[kPer], dt[kPer];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) v[i] = src[min((int)threadIdx.x + 256 * i, kTile - 1)];
-    load_recs();
+    for (int i = 0; i < kPer; ++i) {
+      const int j = (int)threadIdx.x + 256 * i, u = x0 + j % TW, v = y0 + j / TW;
+      im[i] = sc[i] = 0.f;
+      dt[i] = 1.f;
+      if (j < TW * TH && u < W && v < H) {
+        const size_t idx = base + (size_t)v * W + u;
+        im[i] = image[idx];
+        sc[i] = second[idx];
+        dt[i] = dsave[idx];
+      }
+    }
+    if (n) load_recs();
+    float2* g2 = reinterpret_cast<float2*>(gt);
+    float sq = 0.f;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int j = (int)threadIdx.x + 256 * i;
-      if (j < kTile) gt[j / (TW / 2) * kRow + j % (TW / 2)] = v[i];
+      float dI = sc[i];
+      if (loss_part) {  // uniform
+        const float d = im[i] - dI;
+        dI = scale * d;
+        sq = fmaf(d, d, sq);
+      }
+      const float gam = dI / dt[i];
+      if (j < TW * TH) g2[j / TW * (2 * kRow) + j % TW] = make_float2(gam, gam * im[i]);
     }
     if (threadIdx.x < kRow) gt[TH * kRow + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (loss) {  // uniform
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+      if (lane == 0) wave_sq[wave] = sq;
+    }
   }
   __syncthreads();  // gt, bucket and grab are ready
+  if (loss) {  // uniform
+    if (threadIdx.x == 0) loss_part[t] = ((wave_sq[0] + wave_sq[1]) + wave_sq[2]) + wave_sq[3];
+    if (n == 0) return;
+  }
   for (;;) {
     // where the key's partial goes: its place in emission order, the record's
     // offset plus the key's index among the record's keys
@@ -755,33 +717,6 @@ hipError_t launch_accum_fwd(int tile_w, int tile_h, int lds_batch, int split, co
   return hipErrorInvalidValue;
 }
 
-uint32_t bwd_prep_blocks(int tile_w, int tile_h, uint32_t num_tiles) {
-  const size_t groups = (size_t)num_tiles * tile_w * tile_h / 4;  // four pixels per thread
-  return (uint32_t)((groups + 255) / 256);
-}
-
-hipError_t launch_bwd_prep(int tile_w, int tile_h, const PlaneInt* pint, const uint32_t* tile_plane,
-                           const float* image, const float* second, bool mse, float scale, float* loss_part,
-                           const float* dsave, float* gq, uint32_t num_tiles, hipStream_t s) {
-  const dim3 grid(bwd_prep_blocks(tile_w, tile_h, num_tiles));
-  float4* g4 = reinterpret_cast<float4*>(gq);
-  const int vec = (reinterpret_cast<uintptr_t>(image) | reinterpret_cast<uintptr_t>(second) |
-                   reinterpret_cast<uintptr_t>(dsave)) % 16 == 0;
-#define UG_PREP(W, H)                                                                                              \
-  if (tile_w == W && tile_h == H) {                                                                                \
-    if (mse)                                                                                                       \
-      hipLaunchKernelGGL((k_bwd_prep<W, H, true>), grid, dim3(256), 0, s, pint, tile_plane, image, second, dsave,  \
-                         g4, num_tiles, vec, scale, loss_part);                                                    \
-    else                                                                                                           \
-      hipLaunchKernelGGL((k_bwd_prep<W, H, false>), grid, dim3(256), 0, s, pint, tile_plane, image, second, dsave, \
-                         g4, num_tiles, vec, scale, loss_part);                                                    \
-    return hipGetLastError();                                                                                      \
-  }
-  UG_TILE_SHAPES(UG_PREP)
-#undef UG_PREP
-  return hipErrorInvalidValue;
-}
-
 // Blocks per tile: about 1,024 keys each (four passes of a block, so its
 // start-up is a small part; measured at 3,700 keys per tile: one block per
 // tile 787 us, four 739, sixteen 824), and where that leaves fewer than 1,024
@@ -792,9 +727,9 @@ constexpr uint32_t kBwdBlockKeys = 1024, kBwdMinBlocks = 1024, kBwdMinKeys = 128
 hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_t* tile_org,
                             const uint32_t* tile_start, const uint32_t* skey, const uint32_t* srec,
                             const uint32_t* emitted, const uint32_t* rec_koff, const uint32_t* run_koff,
-                            const Rec* recs, const float* gq, float* partial, bool cut, uint32_t num_tiles,
-                            uint32_t key_cap, hipStream_t s) {
-  const float2* g2 = reinterpret_cast<const float2*>(gq);
+                            const Rec* recs, const PlaneInt* pint, const uint32_t* tile_plane, const float* image,
+                            const float* second, const float* dsave, float scale, float* loss_part, float* partial,
+                            bool cut, uint32_t num_tiles, uint32_t key_cap, hipStream_t s) {
   float4* p4 = reinterpret_cast<float4*>(partial);
   if (num_tiles == 0) return hipSuccess;
   const uint32_t avg = key_cap / num_tiles;
@@ -805,7 +740,8 @@ hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_
 #define UG_BWD(W, H)                                                                                           \
   if (tile_w == W && tile_h == H) {                                                                            \
     hipLaunchKernelGGL((k_accum_bwd<W, H>), grid, dim3(256), 0, s, tile_org, tile_start, skey, srec, emitted,   \
-                       rec_koff, run_koff, recs, g2, p4, kcut, tile_bits, num_tiles, nsplit);                   \
+                       rec_koff, run_koff, recs, pint, tile_plane, image, second, dsave, scale, loss_part, p4,  \
+                       kcut, tile_bits, num_tiles, nsplit);                                                     \
     return hipGetLastError();                                                                                  \
   }
   UG_TILE_SHAPES(UG_BWD)
