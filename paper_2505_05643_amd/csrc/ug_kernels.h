@@ -96,10 +96,11 @@ struct QualityConst {
   double taps[11];  // normalised 1D Gaussian window
   double c1, c2;
 };
-uint32_t quality_strips(int32_t max_width);  // 8-pixel column strips of the widest plane
-// part: p x max_strips double2 of workspace
-hipError_t launch_quality(const PlaneInt* pint, int32_t p, uint32_t max_strips, const float* img, const float* ref,
-                          const QualityConst& q, double2* part, double* ssim, double* mse, hipStream_t s);
+// max_w, max_h: widest and highest plane; part: p x quality_parts double2 of workspace
+uint32_t quality_parts(int32_t p, int32_t max_w, int32_t max_h);
+hipError_t launch_quality(const PlaneInt* pint, int32_t p, int32_t max_w, int32_t max_h, const float* img,
+                          const float* ref, const QualityConst& q, double2* part, double* ssim, double* mse,
+                          hipStream_t s);
 
 // ---- covariance parameterisation study (ug_params.hip)
 hipError_t launch_param_eval(int32_t kind, bool fp64, const float* raw, const float* z, const float* delta,
