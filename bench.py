@@ -361,10 +361,12 @@ def main():
 
     # ---- roofline of every kernel; the dominant one is the headline ----
     # sort passes as launched (one histogram launch per pass); digit slots
-    # per block histogram: 2^ceil(bits / passes) rounded up to 256 or 1024
+    # per block histogram: 2^ceil(bits / passes) rounded up to 256 or 1024, 2048, 4096
     passes = max(1, round(stages["sort_hist"][1] / args.steps)) if "sort_hist" in stages else 1
-    g_sort = min(2048, max(1, (plan.key_capacity + 2047) // 2048))
-    dslots = 1024 if -(-plan_bits(plan) // passes) > 8 else 256
+    chunk = 1024 if plan.key_capacity <= 1024 * 1024 else 2048
+    g_sort = min(2048, max(1, -(-plan.key_capacity // chunk)))
+    dbits = -(-plan_bits(plan) // passes)
+    dslots = 256 if dbits <= 8 else max(1024, 1 << dbits)
     sizes = dict(n=g.n, p=pl.p, r=n_rec, k=n_key, t=plan.num_tiles, m=int(pl.npix), passes=passes,
                  w=(pl.p + 63) // 64, rows=params.box_mode == 2, g_sort=g_sort, dslots=dslots)
     kernels = {}

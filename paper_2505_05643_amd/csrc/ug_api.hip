@@ -47,7 +47,7 @@ struct ug_plan {
   uint64_t num_pixels = 0;
   int bits = 1;
   uint32_t rec_cap = 0, key_cap = 0;
-  uint32_t sort_blocks = 1;
+  SortShape sort{};
   int device = 0;
   PlaneInt* d_pint = nullptr;
   uint32_t* d_tile_plane = nullptr;
@@ -96,7 +96,6 @@ void compute_layout(ug_plan* pl) {
   L.side = take(adjoint_side_floats(pl->rec_cap) * 4);
   L.tile_start = take((T + 1) * 4);
   L.dsave = take(pl->num_pixels * 4);
-  L.hist = take((size_t)sort_digit_slots(pl->bits, pl->sort_blocks) * (pl->sort_blocks + 1) * 4);
   L.emitted = take(K * 4);
   L.key0 = take(K * 4);
   L.key1 = take(K * 4);
@@ -106,10 +105,18 @@ void compute_layout(ug_plan* pl) {
   L.run_koff = take(std::max(runs, K) * 4);
   const size_t beyond = runs > K ? align_up(runs * 4) - align_up(K ? K * 4 : 1) : 0;
   L.partial = take(K * 32);
+  // the sort's histograms are dead before the adjoint writes its partials
+  const size_t hist = pl->sort.hist_words() * 4;
+  const bool apart = hist > K * 32;  // a few keys only
+  L.hist = apart ? take(hist) : L.partial;
   L.loss_part = take(T * 4);
-  // the no-allocation limit counts 8 bytes per tile pixel as well, and the
-  // loss sums by 1024 pixels, so that it refuses what it always has
-  L.checked = o - beyond + align_up(T * tpx * 8) + align_up((T * tpx + 1023) / 1024 * 4) - align_up(T * 4);
+  // What the no-allocation limit counts, so that it refuses what it always
+  // has: 8 bytes per tile pixel, the loss sums by 1024 pixels, and the
+  // histograms apart, by blocks of 2048 keys and at most 1024 digits.
+  const size_t g = std::min<size_t>(std::max<size_t>((K + 2047) / 2048, 1), 2048);
+  const size_t slots = pl->bits > 8 && pl->bits <= 10 && g <= 256 ? 1024 : 256;
+  L.checked = o - beyond - (apart ? align_up(hist) : 0) + align_up(slots * (g + 1) * 4) + align_up(T * tpx * 8) +
+              align_up((T * tpx + 1023) / 1024 * 4) - align_up(T * 4);
   L.total = o;
 }
 
@@ -249,7 +256,7 @@ Sorted sorted_set(const ug_plan* plan, void* ws, int done) {
           at<uint32_t>(ws, done & 1 ? L.rec1 : L.rec0)};
 }
 Sorted sorted_set(const ug_plan* plan, void* ws) {
-  return sorted_set(plan, ws, sort_passes(plan->bits, plan->sort_blocks));
+  return sorted_set(plan, ws, plan->sort.passes);
 }
 
 // The radix sort of the emitted keys, one launch per kernel and pass.
@@ -257,25 +264,24 @@ hipError_t enqueue_sort(const ug_plan* plan, void* ws, hipStream_t s) {
   const Layout& L = plan->lay;
   const Ctrl* ctrl = at<Ctrl>(ws, L.ctrl);
   uint32_t* hist = at<uint32_t>(ws, L.hist);
-  const uint32_t G = plan->sort_blocks;
-  const int passes = sort_passes(plan->bits, G);
+  const int passes = plan->sort.passes;
   hipError_t e = hipSuccess;
   for (int pass = 0; pass < passes && e == hipSuccess; ++pass) {
     const Sorted from = sorted_set(plan, ws, pass), to = sorted_set(plan, ws, pass + 1);
     {
       StageScope sc(plan, UG_STAGE_SORT_HIST, s);
-      e = launch_radix_hist(ctrl, from.key, hist, G, plan->bits, pass, s);
+      e = launch_radix_hist(ctrl, from.key, hist, plan->sort, pass, s);
     }
     if (e != hipSuccess) break;
     {
       StageScope sc(plan, UG_STAGE_SORT_SCAN, s);
-      e = launch_radix_colscan(hist, G, plan->bits, s);
+      e = launch_radix_colscan(hist, plan->sort, s);
     }
     if (e != hipSuccess) break;
     StageScope sc(plan, UG_STAGE_SORT_SCATTER, s);
     const uint32_t* in[2] = {from.key, from.rec};
     uint32_t* out[2] = {to.key, to.rec};
-    e = launch_radix_scatter(ctrl, in, out, hist, G, plan->bits, pass,
+    e = launch_radix_scatter(ctrl, in, out, hist, plan->sort, pass,
                              passes == 1 ? at<uint32_t>(ws, L.tile_start) : nullptr, plan->num_tiles, s);
   }
   return e;
@@ -376,7 +382,7 @@ int ug_plan_create(int32_t n, int32_t p, const int32_t* wh_host, const ug_params
   pl->device = dev;
   pl->rec_cap = (uint32_t)record_capacity;
   pl->key_cap = (uint32_t)key_capacity;
-  pl->sort_blocks = sort_blocks_for(pl->key_cap);
+  pl->sort = sort_shape(pl->bits, pl->key_cap);
   std::vector<uint32_t> tile_plane((size_t)tiles), tile_org((size_t)tiles);
   for (int32_t i = 0; i < p; ++i) {
     const PlaneInt& q = pint[(size_t)i];
@@ -411,7 +417,7 @@ int ug_plan_reserve(ug_plan* plan, int64_t record_capacity, int64_t key_capacity
     return UG_ERR_INVALID_ARG;
   plan->rec_cap = (uint32_t)record_capacity;
   plan->key_cap = (uint32_t)key_capacity;
-  plan->sort_blocks = sort_blocks_for(plan->key_cap);
+  plan->sort = sort_shape(plan->bits, plan->key_cap);
   compute_layout(plan);
   if (plan->step_exec) {  // its kernels were captured with the old layout
     (void)hipGraphExecDestroy(plan->step_exec);
@@ -507,7 +513,7 @@ int render_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* pla
   e = enqueue_sort(plan, ws, s);
   if (e != hipSuccess) return UG_ERR_HIP;
   const Sorted so = sorted_set(plan, ws);
-  if (sort_passes(plan->bits, plan->sort_blocks) > 1) {  // one pass wrote the ranges itself
+  if (plan->sort.passes > 1) {  // one pass wrote the ranges itself
     StageScope sc(plan, UG_STAGE_RANGES, s);
     e = launch_tile_ranges(ctrl, so.key, plan->num_tiles, plan->key_cap, plan->bits, at<uint32_t>(ws, L.tile_start),
                            s);

@@ -47,30 +47,32 @@ hipError_t launch_gauss_grad(const ug_gaussians& g, const RenderParams& rp, cons
                              double inv_m, float* loss_out, hipStream_t s);
 
 // ---- tile binning sort (ug_sort.hip)
-// Stable LSD radix sort of the key words on their low `bits` bits (the tile
-// id), moving each key's record id with it.  Digits: the whole tile id in one pass when it
-// has at most 10 bits and there are at most 256 sort blocks, else at most 8
-// bits per pass with the bits split evenly (sort_digit_bits, sort_passes).
-// Arrays are given as {key, rec}.  Per pass: block-major digit histograms (hist holds
-// sort_digit_slots * (nblocks + 1) words), their column scan, then the
-// stable scatter.
-int sort_digit_bits(int bits, uint32_t nblocks);
-int sort_passes(int bits, uint32_t nblocks);
-uint32_t sort_digit_slots(int bits, uint32_t nblocks);
-hipError_t launch_radix_hist(const Ctrl* ctrl, const uint32_t* keys, uint32_t* hist, uint32_t nblocks, int bits,
-                             int pass, hipStream_t s);
-hipError_t launch_radix_colscan(uint32_t* hist, uint32_t nblocks, int bits, hipStream_t s);
+// Stable LSD radix sort of the key words on their low bits (the tile id),
+// moving each key's record id with it.  Arrays are given as {key, rec}.  Per
+// pass: block-major digit histograms (hist holds hist_words words), their
+// column scan, then the stable scatter.
+struct SortShape {
+  int bits;          // of the tile id
+  uint32_t blocks;
+  bool small;        // one round per block
+  int passes, digit_bits;
+  uint32_t slots;    // digits of a histogram row
+  size_t hist_words() const { return (size_t)slots * (blocks + 1u); }
+};
+SortShape sort_shape(int bits, uint32_t key_cap);
+hipError_t launch_radix_hist(const Ctrl* ctrl, const uint32_t* keys, uint32_t* hist, const SortShape& shape, int pass,
+                             hipStream_t s);
+hipError_t launch_radix_colscan(uint32_t* hist, const SortShape& shape, hipStream_t s);
 // With a single pass (the digit is the whole tile id) the scatter also
 // writes tile_start (if not null; num_tiles + 1 entries), which the column
 // totals give directly.
 hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[2], uint32_t* const out[2],
-                                const uint32_t* hist, uint32_t nblocks, int bits, int pass, uint32_t* tile_start,
+                                const uint32_t* hist, const SortShape& shape, int pass, uint32_t* tile_start,
                                 uint32_t num_tiles, hipStream_t s);
 // tile_start[t] for t in [0, T] from the sorted key words (tile id = the key
 // word's low bits).
 hipError_t launch_tile_ranges(const Ctrl* ctrl, const uint32_t* skeys, uint32_t num_tiles, uint32_t key_cap,
                               int bits, uint32_t* tile_start, hipStream_t s);
-uint32_t sort_blocks_for(uint32_t key_cap);
 
 // ---- Phase-2 atomic scatter forward (ug_scatter.hip): zero the sums, one
 // wave per record adds w c and w over its box, normalise in place.

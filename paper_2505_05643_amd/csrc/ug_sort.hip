@@ -1,8 +1,9 @@
 // Tile binning: stable LSD radix sort of the key words on their tile id,
-// carrying the record id, with the key count read from device memory (so the host never synchronises), and the per-tile
-// [start, end) ranges.  Digits are at most 8 bits (256 per pass), or, for
-// small inputs whose tile id has at most 10 bits, the whole tile id in one
-// pass (up to 1024 digits).
+// carrying the record id, with the key count read from device memory (so the
+// host never synchronises), and the per-tile [start, end) ranges.  Small
+// inputs are latency bound: blocks of 1024 keys, walked once, and the whole
+// tile id in one pass where it has at most 12 bits.  Otherwise digits are at
+// most 8 bits (256 per pass).
 #include <algorithm>
 
 #include "ug_kernels.h"
@@ -11,7 +12,16 @@ namespace ug {
 
 constexpr int kSortThreads = 256;
 constexpr uint32_t kSortMaxBlocks = 2048;
-constexpr uint32_t kWideMaxBlocks = 256;  // one wide pass only up to this many blocks
+
+// Small inputs: up to kSmallKeys keys (by capacity) take blocks of 1024 keys,
+// each walked once, and the whole tile id in one pass where it has at most 11
+// bits, or 12 up to kWideKeys keys.  Times of the sort's kernels with the
+// ranges kernel that one pass does not need (launch gaps included): 11 bits,
+// 315 K keys 53 us in two passes with blocks of 2048, 26 so; 950 K keys 53 and
+// 37 (the wide histograms' column scan grows with the keys: 15 of the 37);
+// 12 bits, 78 K keys 45 and 24, 640 K keys 53 and 48, 950 K keys 54 and 57.
+constexpr uint32_t kSmallKeys = 1024u * 1024u, kWideKeys = 512u * 1024u;
+constexpr uint32_t kSmallChunk = 1024;
 
 // Contiguous chunk of the n keys owned by block b of G (multiple of 256).
 __device__ __forceinline__ void sort_chunk(uint32_t n, uint32_t G, uint32_t b, uint32_t& s, uint32_t& e) {
@@ -28,12 +38,13 @@ template <int D>
 __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Ctrl* __restrict__ ctrl,
                                                               const uint32_t* __restrict__ keys, uint32_t G,
                                                               int shift, uint32_t dmask, uint32_t* __restrict__ cnt) {
-  __shared__ uint32_t h[4][D];
-  for (int j = threadIdx.x; j < 4 * D; j += kSortThreads) (&h[0][0])[j] = 0u;
+  constexpr int kCopies = D > 256 ? 1 : 4;  // counts per wave where that is cheap
+  __shared__ uint32_t h[kCopies][D];
+  for (int j = threadIdx.x; j < kCopies * D; j += kSortThreads) (&h[0][0])[j] = 0u;
   __syncthreads();
   uint32_t s, e;
   sort_chunk(ctrl->n_key_eff, G, blockIdx.x, s, e);
-  const int wave = threadIdx.x >> 6;
+  const int copy = kCopies > 1 ? (int)(threadIdx.x >> 6) : 0;
   // eight loads in flight per thread, then their counts
   for (uint32_t i0 = s + threadIdx.x; i0 < e; i0 += 8 * kSortThreads) {
     uint32_t kv[8];
@@ -44,52 +55,55 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Ctrl* __restr
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if (i0 + (uint32_t)(j * kSortThreads) < e) atomicAdd(&h[wave][(kv[j] >> shift) & dmask], 1u);
+      if (i0 + (uint32_t)(j * kSortThreads) < e) atomicAdd(&h[copy][(kv[j] >> shift) & dmask], 1u);
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < D; d += kSortThreads)
-    cnt[(size_t)blockIdx.x * D + d] = h[0][d] + h[1][d] + h[2][d] + h[3][d];
+  for (int d = threadIdx.x; d < D; d += kSortThreads) {
+    uint32_t c = h[0][d];
+#pragma unroll
+    for (int q = 1; q < kCopies; ++q) c += h[q][d];
+    cnt[(size_t)blockIdx.x * D + d] = c;
+  }
 }
 
-// One block per digit d: exclusive scan of column d over the G blocks
-// (in place), and the column total coltot[d].  G <= 4096.
-constexpr int kColPer = 16;
-template <int D>
-__global__ __launch_bounds__(256) void k_radix_colscan(uint32_t* __restrict__ cnt, uint32_t G,
-                                                       uint32_t* __restrict__ coltot) {
-  __shared__ uint32_t sh[4];
-  const uint32_t d = blockIdx.x, t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
-  uint32_t v[kColPer];
+// Exclusive scan of every digit's column over the G blocks (in place), and
+// the column totals.  A block takes eight neighbouring digits, so a row of
+// theirs is 32 bytes; its threads are (row group, digit), each with up to
+// kScanRows consecutive rows in flight at once.  Bound by that round trip and
+// the one of the stores.  (A block per digit read four bytes of every row:
+// 2048 rows of 256 digits 15 us, 11 so.)
+constexpr int kScanDigits = 8, kScanGroups = 128;
+constexpr int kScanRows = kSortMaxBlocks / kScanGroups;
+__global__ __launch_bounds__(kScanDigits* kScanGroups) void k_radix_colscan(uint32_t* __restrict__ cnt, uint32_t G,
+                                                                          uint32_t D, uint32_t* __restrict__ coltot) {
+  __shared__ uint32_t sh[kScanDigits][kScanGroups + 1];
+  const uint32_t d = threadIdx.x % kScanDigits, grp = threadIdx.x / kScanDigits;
+  const uint32_t rows = (G + kScanGroups - 1u) / kScanGroups, r0 = grp * rows;
+  uint32_t* col = cnt + blockIdx.x * kScanDigits + d;
+  uint32_t v[kScanRows];
   uint32_t sum = 0;
 #pragma unroll
-  for (int j = 0; j < kColPer; ++j) {
-    const uint32_t b = kColPer * t + j;
-    v[j] = b < G ? cnt[(size_t)b * D + d] : 0u;
-    sum += v[j];
-  }
-  uint32_t x = sum;
+  for (uint32_t j = 0; j < (uint32_t)kScanRows; ++j) v[j] = j < rows && r0 + j < G ? col[(size_t)(r0 + j) * D] : 0u;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sh[wave] = x;
+  for (int j = 0; j < kScanRows; ++j) sum += v[j];
+  sh[d][grp] = sum;
   __syncthreads();
-  uint32_t before = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) before += sh[w];
-    total += sh[w];
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  if (wave < (uint32_t)kScanDigits) {
+    static_assert(kScanGroups == 128, "two groups per lane");
+    const uint32_t a = sh[wave][2 * lane], b = sh[wave][2 * lane + 1];
+    const uint32_t incl = wave_incl_sum(a + b);
+    sh[wave][2 * lane] = incl - b - a;
+    sh[wave][2 * lane + 1] = incl - b;
+    if (lane == 63) coltot[blockIdx.x * kScanDigits + wave] = incl;
   }
-  uint32_t run = before + x - sum;
+  __syncthreads();
+  uint32_t run = sh[d][grp];
 #pragma unroll
-  for (int j = 0; j < kColPer; ++j) {
-    const uint32_t b = kColPer * t + j;
-    if (b < G) cnt[(size_t)b * D + d] = run;
+  for (uint32_t j = 0; j < (uint32_t)kScanRows; ++j) {
+    if (j < rows && r0 + j < G) col[(size_t)(r0 + j) * D] = run;
     run += v[j];
   }
-  if (t == 0) coltot[d] = total;
 }
 
 // Stable scatter.  The block's chunk is walked in rounds of up to 4096 keys;
@@ -112,14 +126,14 @@ struct SortSet {
   uint32_t* rec;
 };
 
-template <int kItems, int D>
+template <int kItems>
 __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in,
                                                                 SortSet out,
                                                                 const uint32_t* __restrict__ cnt,
                                                                 const uint32_t* __restrict__ coltot, uint32_t G,
                                                                 int shift, int dbits, uint32_t* __restrict__ tile_start,
                                                                 uint32_t T) {
-  constexpr int kRound = kSortThreads * kItems;
+  constexpr int kRound = kSortThreads * kItems, D = 256;
   const uint32_t* __restrict__ kin = in.key;
   __shared__ uint32_t s_key[kRound];  // the round reordered by digit: keys, then record ids
   constexpr int kPer = D / kSortThreads;  // digits per thread, consecutive
@@ -271,24 +285,131 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
   }
 }
 
+// The same for small inputs: a block's at most kSmallChunk keys in one round,
+// up to 4096 digits.  Everything the block reads is in flight at once (keys,
+// record ids, its row of the column scan, the totals), the digits' first
+// positions and the round's LDS slots come out of one packed block scan, and
+// keys and record ids are reordered together: four barriers in all.
+template <int D>
+__global__ __launch_bounds__(kSortThreads) void k_radix_scatter_small(
+    const Ctrl* __restrict__ ctrl, SortSet in, SortSet out, const uint32_t* __restrict__ cnt,
+    const uint32_t* __restrict__ coltot, uint32_t G, int shift, int dbits, uint32_t* __restrict__ tile_start,
+    uint32_t T) {
+  constexpr int kItems = kSmallChunk / kSortThreads, kPer = D / kSortThreads;
+  constexpr int kSlotBits = 11;  // a round's slot count, 0 .. 1024
+  static_assert(kSmallChunk < (1u << kSlotBits) && ((uint64_t)kSmallKeys << kSlotBits) < (1ull << 32), "packed scan");
+  __shared__ uint32_t s_key[kSmallChunk], s_rec[kSmallChunk];
+  __shared__ uint32_t first[D];                       // output position of a digit's keys, less their first slot
+  __shared__ __align__(16) uint16_t wcnt[4][D];       // per-wave digit counts, then the slots of their first keys
+  __shared__ uint32_t sh[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t dmask = (1u << dbits) - 1u;
+  const uint32_t n = ctrl->n_key_eff;
+  uint32_t s, e;
+  sort_chunk(n, G, blockIdx.x, s, e);
+  const uint32_t n_round = e - s, seg = ((n_round + 255u) / 256u) * 64u;
+  uint32_t kk[kItems], rc[kItems], rr[kItems], tot[kPer], row[kPer];
+#pragma unroll
+  for (int it = 0; it < kItems; ++it) {
+    const uint32_t i = s + (uint32_t)wave * seg + (uint32_t)(it * 64 + lane);
+    const bool valid = (uint32_t)(it * 64) < seg && i < e;
+    kk[it] = valid ? in.key[i] : 0u;
+    rc[it] = valid ? in.rec[i] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    tot[k] = coltot[tid * kPer + k];
+    row[k] = cnt[(size_t)blockIdx.x * D + tid * kPer + k];
+  }
+#pragma unroll
+  for (int j = 0; j < D / 128; ++j) reinterpret_cast<uint32_t*>(wcnt[wave])[lane + 64 * j] = 0u;
+  wave_lds_sync();
+#pragma unroll
+  for (int it = 0; it < kItems; ++it) {
+    const uint32_t i = s + (uint32_t)wave * seg + (uint32_t)(it * 64 + lane);
+    const bool valid = (uint32_t)(it * 64) < seg && i < e;
+    const uint32_t d = (kk[it] >> shift) & dmask;
+    unsigned long long peers = __ballot(valid);
+    for (int bit = 0; bit < dbits; ++bit) {
+      const bool on = (d >> bit) & 1u;
+      const unsigned long long bm = __ballot(on);
+      peers &= on ? bm : ~bm;
+    }
+    const uint32_t before = valid ? wcnt[wave][d] : 0u;
+    wave_lds_sync();
+    if (valid && lanemask_lt_popc(peers) == 0) wcnt[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+    wave_lds_sync();
+    rr[it] = valid ? before + lanemask_lt_popc(peers) : 0xffffffffu;
+  }
+  __syncthreads();
+  uint32_t c[4][kPer], sum = 0u;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) c[w][k] = wcnt[w][tid * kPer + k];
+    sum += tot[k] << kSlotBits | (c[0][k] + c[1][k] + c[2][k] + c[3][k]);
+  }
+  const uint32_t incl = wave_incl_sum(sum);
+  if (lane == 63) sh[wave] = incl;
+  __syncthreads();
+  uint32_t at = incl - sum;
+  for (int w = 0; w < wave; ++w) at += sh[w];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int d = tid * kPer + k;
+    const uint32_t pos = at >> kSlotBits;
+    uint32_t slot = at & ((1u << kSlotBits) - 1u);
+    // one pass over the whole tile id: a digit's first output position is its
+    // tile's start
+    if (tile_start && blockIdx.x == 0 && (uint32_t)d < T) tile_start[d] = pos;
+    first[d] = pos + row[k] - slot;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      wcnt[w][d] = (uint16_t)slot;
+      slot += c[w][k];
+    }
+    at += tot[k] << kSlotBits | (c[0][k] + c[1][k] + c[2][k] + c[3][k]);
+  }
+  if (tile_start && blockIdx.x == 0 && tid == 0) tile_start[T] = n;
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kItems; ++it) {
+    if (rr[it] != 0xffffffffu) {
+      const uint32_t slot = rr[it] + wcnt[wave][(kk[it] >> shift) & dmask];
+      s_key[slot] = kk[it];
+      s_rec[slot] = rc[it];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t i = (uint32_t)(tid + j * kSortThreads);
+    if (i < n_round) {
+      const uint32_t k = s_key[i];
+      const uint32_t o = first[(k >> shift) & dmask] + i;
+      out.key[o] = k;
+      out.rec[o] = s_rec[i];
+    }
+  }
+}
+
 // Kernels around the scatter body.  The large-input variant (16 keys per
 // thread and round, 256 digits) is held to four workgroups per CU, which its
 // LDS allows; the compiler would otherwise give it more registers and three.
-template <int kItems, int D>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in,
                                                                 SortSet out,
                                                                 const uint32_t* __restrict__ cnt,
                                                                 const uint32_t* __restrict__ coltot, uint32_t G,
                                                                 int shift, int dbits, uint32_t* __restrict__ tile_start,
                                                                 uint32_t T) {
-  radix_scatter<kItems, D>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
+  radix_scatter<8>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
 }
 
 __global__ __launch_bounds__(kSortThreads, 4) void k_radix_scatter_large(
     const Ctrl* __restrict__ ctrl, SortSet in, SortSet out, const uint32_t* __restrict__ cnt,
     const uint32_t* __restrict__ coltot, uint32_t G, int shift, int dbits, uint32_t* __restrict__ tile_start,
     uint32_t T) {
-  radix_scatter<16, 256>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
+  radix_scatter<16>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
 }
 
 // tile_start[t] = first sorted key index whose tile id is >= t (t in [0, T]).
@@ -335,78 +456,71 @@ __global__ __launch_bounds__(256) void k_tile_ranges(const Ctrl* __restrict__ ct
   }
 }
 
-// Blocks of the sort: chunks of at least 2048 keys (half a round), at most
-// 2048 blocks (larger inputs walk several full rounds per block).
-uint32_t sort_blocks_for(uint32_t key_cap) {
-  uint32_t g = (key_cap + 2047u) / 2048u;
-  if (g < 1) g = 1;
-  if (g > kSortMaxBlocks) g = kSortMaxBlocks;
-  return g;
-}
-
-// Digit width of every pass: the whole tile id in one pass when it has at
-// most 10 bits and the input is small (at most kWideMaxBlocks blocks, so the
-// block-major histograms stay small); otherwise the bits split evenly over
-// passes of at most 8 bits, so small tile counts get fewer digits and longer
-// runs per digit.
-int sort_digit_bits(int bits, uint32_t G) {
+// Small inputs (see kSmallKeys): chunks of kSmallChunk keys.  Otherwise
+// chunks of at least 2048 keys (half a round), at most 2048 blocks (larger
+// inputs walk several full rounds per block), and the tile id's bits split
+// evenly over passes of at most 8 bits, so small tile counts get fewer digits
+// and longer runs per digit.
+SortShape sort_shape(int bits, uint32_t key_cap) {
   if (bits < 1) bits = 1;
-  if (bits <= 10 && G <= kWideMaxBlocks) return bits;
-  const int p = (bits + 7) / 8;
-  return (bits + p - 1) / p;
+  SortShape S;
+  S.bits = bits;
+  S.small = key_cap <= kSmallKeys;
+  const uint32_t chunk = S.small ? kSmallChunk : 2048u;
+  S.blocks = std::min(std::max((key_cap + chunk - 1u) / chunk, 1u), kSortMaxBlocks);
+  const bool one = S.small && (bits <= 11 || (bits == 12 && key_cap <= kWideKeys));
+  S.passes = one ? 1 : (bits + 7) / 8;
+  S.digit_bits = (bits + S.passes - 1) / S.passes;
+  S.slots = S.digit_bits <= 8 ? 256u : S.digit_bits <= 10 ? 1024u : S.digit_bits <= 11 ? 2048u : 4096u;
+  return S;
 }
-
-int sort_passes(int bits, uint32_t G) {
-  if (bits < 1) bits = 1;
-  const int d = sort_digit_bits(bits, G);
-  return (bits + d - 1) / d;
-}
-
-uint32_t sort_digit_slots(int bits, uint32_t G) { return sort_digit_bits(bits, G) > 8 ? 1024u : 256u; }
 
 // Digit bits of one pass: the last takes what is left of the tile id (the
 // bits above it belong to the key's other fields).
-static int pass_bits(int bits, int db, int pass) { return std::min(db, bits - db * pass); }
+static int pass_bits(const SortShape& S, int pass) { return std::min(S.digit_bits, S.bits - S.digit_bits * pass); }
 
-hipError_t launch_radix_hist(const Ctrl* ctrl, const uint32_t* keys, uint32_t* hist, uint32_t G, int bits, int pass,
+hipError_t launch_radix_hist(const Ctrl* ctrl, const uint32_t* keys, uint32_t* hist, const SortShape& S, int pass,
                              hipStream_t s) {
-  const int db = sort_digit_bits(bits, G);
-  if (db > 8)
-    hipLaunchKernelGGL(k_radix_hist<1024>, dim3(G), dim3(kSortThreads), 0, s, ctrl, keys, G, db * pass,
-                       (1u << pass_bits(bits, db, pass)) - 1u, hist);
-  else
-    hipLaunchKernelGGL(k_radix_hist<256>, dim3(G), dim3(kSortThreads), 0, s, ctrl, keys, G, db * pass,
-                       (1u << pass_bits(bits, db, pass)) - 1u, hist);
+  const int shift = S.digit_bits * pass;
+  const uint32_t dmask = (1u << pass_bits(S, pass)) - 1u;
+#define UG_HIST(D) \
+  if (S.slots == D) hipLaunchKernelGGL(k_radix_hist<D>, dim3(S.blocks), dim3(kSortThreads), 0, s, ctrl, keys, S.blocks, shift, dmask, hist);
+  UG_HIST(256)
+  UG_HIST(1024)
+  UG_HIST(2048)
+  UG_HIST(4096)
+#undef UG_HIST
   return hipGetLastError();
 }
 
-hipError_t launch_radix_colscan(uint32_t* hist, uint32_t G, int bits, hipStream_t s) {
-  const uint32_t D = sort_digit_slots(bits, G);
-  if (D == 1024u)
-    hipLaunchKernelGGL(k_radix_colscan<1024>, dim3(D), dim3(256), 0, s, hist, G, hist + (size_t)D * G);
-  else
-    hipLaunchKernelGGL(k_radix_colscan<256>, dim3(D), dim3(256), 0, s, hist, G, hist + (size_t)D * G);
+hipError_t launch_radix_colscan(uint32_t* hist, const SortShape& S, hipStream_t s) {
+  hipLaunchKernelGGL(k_radix_colscan, dim3(S.slots / kScanDigits), dim3(kScanDigits * kScanGroups), 0, s, hist,
+                     S.blocks, S.slots, hist + (size_t)S.slots * S.blocks);
   return hipGetLastError();
 }
 
 hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[2], uint32_t* const out[2],
-                                const uint32_t* hist, uint32_t G, int bits, int pass, uint32_t* tile_start,
+                                const uint32_t* hist, const SortShape& S, int pass, uint32_t* tile_start,
                                 uint32_t num_tiles, hipStream_t s) {
-  const int db = sort_digit_bits(bits, G);
-  const uint32_t D = sort_digit_slots(bits, G);
-  const int pb = pass_bits(bits, db, pass);
+  const int shift = S.digit_bits * pass, pb = pass_bits(S, pass);
   const SortSet si{const_cast<uint32_t*>(in[0]), const_cast<uint32_t*>(in[1])};
   const SortSet so{out[0], out[1]};
-  const uint32_t* coltot = hist + (size_t)D * G;
-  if (D == 1024u)  // only for G <= kWideMaxBlocks
-    hipLaunchKernelGGL((k_radix_scatter<8, 1024>), dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so,
-                       hist, coltot, G, db * pass, pb, tile_start, num_tiles);
-  else if (G >= kSortMaxBlocks)
-    hipLaunchKernelGGL(k_radix_scatter_large, dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so,
-                       hist, coltot, G, db * pass, pb, tile_start, num_tiles);
+  const uint32_t* coltot = hist + (size_t)S.slots * S.blocks;
+#define UG_SCATTER(kernel) \
+  hipLaunchKernelGGL(kernel, dim3(S.blocks), dim3(kSortThreads), 0, s, ctrl, si, so, hist, coltot, S.blocks, shift, pb, tile_start, num_tiles)
+  if (S.small && S.slots == 4096u)
+    UG_SCATTER(k_radix_scatter_small<4096>);
+  else if (S.small && S.slots == 2048u)
+    UG_SCATTER(k_radix_scatter_small<2048>);
+  else if (S.small && S.slots == 1024u)
+    UG_SCATTER(k_radix_scatter_small<1024>);
+  else if (S.small)
+    UG_SCATTER(k_radix_scatter_small<256>);
+  else if (S.blocks >= kSortMaxBlocks)
+    UG_SCATTER(k_radix_scatter_large);
   else
-    hipLaunchKernelGGL((k_radix_scatter<8, 256>), dim3(G), dim3(kSortThreads), 0, s, ctrl, si, so,
-                       hist, coltot, G, db * pass, pb, tile_start, num_tiles);
+    UG_SCATTER(k_radix_scatter);
+#undef UG_SCATTER
   return hipGetLastError();
 }
 
