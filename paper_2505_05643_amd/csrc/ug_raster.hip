@@ -16,7 +16,7 @@
 // list: per pixel-record pair two FMAs give the exponent, one compare
 // applies the cut-off and one v_exp_f32 gives the weight.
 //
-// Adjoint: a block takes keys of one tile, four waves of up to 64 at a time,
+// Adjoint: a block takes keys of one tile, its waves up to 64 each at a time,
 // and expands them into (key, four-column strip) items; lanes = items, each
 // walking its strip's rows and accumulating the record's seven partial
 // derivatives in registers.  The items of a key are summed in strip order
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
 }
 
 // ---------------------------------------------------------------- backward
-// nsplit blocks of four waves per tile; each wave has a contiguous share of
+// nsplit blocks of NW waves per tile; each wave has a contiguous share of
 // the tile's keys and takes up to 64 of them per pass.  The block forms the
 // tile's per-pixel inputs, gamma = dL/dc_hat / D and gamma c_hat, in LDS (every
 // row the evaluation reads comes from there); the loss gradient takes the
@@ -354,8 +354,8 @@ __device__ __noinline__ uint32_t find_emitted(const uint32_t* __restrict__ emitt
   return a;
 }
 
-template <int TW, int TH>
-__global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
+template <int TW, int TH, int NW>
+__global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     const uint32_t* __restrict__ tile_org, const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ skey,
     const uint32_t* __restrict__ srec, const uint32_t* __restrict__ emitted, const uint32_t* __restrict__ rec_koff,
     const uint32_t* __restrict__ run_koff, const Rec* __restrict__ recs, const PlaneInt* __restrict__ pint,
@@ -364,19 +364,19 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     int tile_bits, uint32_t num_tiles, uint32_t nsplit) {
   constexpr int kMaskShift = key_mask_shift(TW, TH);
   constexpr int kSlotsWave = slots_wave(TW, TH), kGroups = (kSlotsWave + 63) / 64;
-  constexpr int kMaxStrips = TW / kStrip;
+  constexpr int kMaxStrips = TW / kStrip, kThreads = 64 * NW;
   // float4 per tile row of (gamma, gamma c_hat) in LDS: one more than it
   // needs, so that the rows of a column strip start in different banks
   constexpr int kRow = TW / 2 + 1;
   static_assert(kMaxStrips <= 8 && TH <= 32 && kSlotsWave <= 256, "item fields");
   __shared__ float4 gt[(TH + 1) * kRow];        // the tile's gamma, then a row of zeros
-  __shared__ float4 kpA[256];                   // t11, t12, t22, -t11 du0
-  __shared__ float4 kpB[256];                   // du0, dv0, d, c
+  __shared__ float4 kpA[kThreads];                   // t11, t12, t22, -t11 du0
+  __shared__ float4 kpB[kThreads];                   // du0, dv0, d, c
   __shared__ uint32_t bucket[TH + 1];           // items per row count
-  __shared__ uint32_t more[4];                  // whether the wave has keys left after the pass
-  __shared__ float wave_sq[4];                  // squared differences of the waves' pixels
+  __shared__ uint32_t more[NW];                 // whether the wave has keys left after the pass
+  __shared__ float wave_sq[NW];                 // squared differences of the waves' pixels
   __shared__ uint32_t grab;                     // next group of 64 items to evaluate
-  __shared__ uint32_t sorted[4 * kSlotsWave];   // slot | wave << 8 | key << 10 | strip << 18 | first row << 21 | rows << 26
+  __shared__ uint32_t sorted[NW * kSlotsWave];   // slot | wave << 8 | key << 10 | strip << 18 | first row << 21 | rows << 26
   // the items' sums; before a wave's items are evaluated its part holds what
   // the item stage needs of its keys (read by the same wave only)
   struct ItemStage {
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     float f[7][kSlotsWave];
     ItemStage in;
   };
-  __shared__ Slots slot[4];
+  __shared__ Slots slot[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // all tiles' first parts, then their second ...: the blocks left without
   // keys come last, instead of every few (which left the same CUs idle)
@@ -396,9 +396,9 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   const uint32_t s = tile_start[t], n = tile_start[t + 1] - s;
   // the waves' shares of the tile's keys, at least 32 each (fewer, fuller
   // waves where a tile has few)
-  const uint32_t share = max((n + 4u * nsplit - 1u) / (4u * nsplit), 32u);
+  const uint32_t share = max((n + NW * nsplit - 1u) / (NW * nsplit), 32u);
   const bool loss = loss_part && part == 0;
-  if (part * 4u * share >= n && !loss) return;  // uniform: no keys left for this block
+  if (part * NW * share >= n && !loss) return;  // uniform: no keys left for this block
   if (threadIdx.x <= TH) bucket[threadIdx.x] = 0u;
   if (threadIdx.x == 0) grab = 0u;
   const PlaneInt& PI = pint[tile_plane[t]];
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   const int x0 = (int)(org & 0xffffu), y0 = (int)(org >> 16);
   const float ln2 = (float)kLn2;
   const bool cut = kcut != kNoCutBits;
-  uint32_t k = min((part * 4u + (uint32_t)wave) * share, n);  // the wave's next key
+  uint32_t k = min((part * NW + (uint32_t)wave) * share, n);  // the wave's next key
   const uint32_t ke = min(k + share, n);                      // its last
   // A pass's keys are loaded during the pass before it, and their records (a
   // random 64-byte gather per key) before that pass's evaluation.  Lanes past
@@ -432,13 +432,13 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     // The tile's gamma and gamma c_hat (zero outside the plane) from the
     // image, the upstream gradient or the target, and the denominators; the
     // loads are in flight with the first keys and records.
-    constexpr int kPer = (TW * TH + 255) / 256;
+    constexpr int kPer = (TW * TH + kThreads - 1) / kThreads;
     const int W = PI.W, H = PI.H;
     const size_t base = ((size_t)PI.pix_off_hi << 32) | PI.pix_off_lo;
     float im[kPer], sc[kPer], dt[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int j = (int)threadIdx.x + 256 * i, u = x0 + j % TW, v = y0 + j / TW;
+      const int j = (int)threadIdx.x + kThreads * i, u = x0 + j % TW, v = y0 + j / TW;
       im[i] = sc[i] = 0.f;
       dt[i] = 1.f;
       if (j < TW * TH && u < W && v < H) {
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
     float sq = 0.f;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int j = (int)threadIdx.x + 256 * i;
+      const int j = (int)threadIdx.x + kThreads * i;
       float dI = sc[i];
       if (loss_part) {  // uniform
         const float d = im[i] - dI;
@@ -472,7 +472,12 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
   }
   __syncthreads();  // gt, bucket and grab are ready
   if (loss) {  // uniform
-    if (threadIdx.x == 0) loss_part[t] = ((wave_sq[0] + wave_sq[1]) + wave_sq[2]) + wave_sq[3];
+    if (threadIdx.x == 0) {
+      float sq = wave_sq[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) sq += wave_sq[w];
+      loss_part[t] = sq;
+    }
     if (n == 0) return;
   }
   for (;;) {
@@ -545,7 +550,10 @@ __global__ __launch_bounds__(256, TW * TH > 512 ? 3 : 4) void k_accum_bwd(
       const uint32_t f = __shfl(bx - bv, TH - (int)(ent[i] >> 26), 64);
       if (rank[i] != 0xffffffffu) sorted[f + rank[i]] = ent[i];
     }
-    const bool again = (more[0] | more[1] | more[2] | more[3]) != 0u;
+    uint32_t any_more = more[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) any_more |= more[w];
+    const bool again = any_more != 0u;
     __syncthreads();
     if (threadIdx.x <= TH) bucket[threadIdx.x] = 0u;
     if (k < ke) load_recs();  // in flight during the evaluation
@@ -724,6 +732,19 @@ hipError_t launch_accum_fwd(int tile_w, int tile_h, int lds_batch, int split, co
 // block per tile 41 us, eight 13; 600 tiles of 150: one 11, two 15).
 constexpr uint32_t kBwdBlockKeys = 1024, kBwdMinBlocks = 1024, kBwdMinKeys = 128;
 
+// One wave per block where a tile has few keys: 40 KB of LDS let four blocks
+// of four waves on a CU, and with a wave's worth of keys in a tile their time
+// is the block's start-up, which a block of one wave (10 to 18 KB) repeats
+// less and overlaps more.  With many keys the four waves win: they form the
+// tile's per-pixel inputs once for all and rank their items together.  Both
+// ways, keys per tile at many tiles: 16x16 pixels 16 140 us / 69, 100 157 /
+// 120, 240 184 / 207; 32x16 57 91 / 61, 174 103 / 117; 8x8 24 410 / 138, 240
+// 563 / 432; 32x32 168 85 / 102.  The lines lie near 3584 / sqrt(pixels) keys
+// of capacity.  With fewer tiles than kBwdOneTiles the chip is not full and
+// the four waves shorten each tile.
+constexpr uint32_t kBwdOneTiles = 1024;
+constexpr uint64_t kBwdOneKeys = 3584;
+
 hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_t* tile_org,
                             const uint32_t* tile_start, const uint32_t* skey, const uint32_t* srec,
                             const uint32_t* emitted, const uint32_t* rec_koff, const uint32_t* run_koff,
@@ -733,19 +754,27 @@ hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_
   float4* p4 = reinterpret_cast<float4*>(partial);
   if (num_tiles == 0) return hipSuccess;
   const uint32_t avg = key_cap / num_tiles;
+  const uint64_t px = (uint64_t)(tile_w * tile_h);
+  const bool one = num_tiles >= kBwdOneTiles && (uint64_t)avg * avg * px < kBwdOneKeys * kBwdOneKeys;
   const uint32_t fill = std::min((kBwdMinBlocks + num_tiles - 1u) / num_tiles, avg / kBwdMinKeys);
   const uint32_t nsplit = std::max(std::max(avg / kBwdBlockKeys, fill), 1u);
   const dim3 grid(num_tiles * nsplit);
   const int kcut = cut ? kCutBits : kNoCutBits;
-#define UG_BWD(W, H)                                                                                           \
-  if (tile_w == W && tile_h == H) {                                                                            \
-    hipLaunchKernelGGL((k_accum_bwd<W, H>), grid, dim3(256), 0, s, tile_org, tile_start, skey, srec, emitted,   \
-                       rec_koff, run_koff, recs, pint, tile_plane, image, second, dsave, scale, loss_part, p4,  \
-                       kcut, tile_bits, num_tiles, nsplit);                                                     \
-    return hipGetLastError();                                                                                  \
+#define UG_BWD_NW(W, H, NW)                                                                                     \
+  hipLaunchKernelGGL((k_accum_bwd<W, H, NW>), grid, dim3(64 * NW), 0, s, tile_org, tile_start, skey, srec,      \
+                     emitted, rec_koff, run_koff, recs, pint, tile_plane, image, second, dsave, scale,          \
+                     loss_part, p4, kcut, tile_bits, num_tiles, nsplit)
+#define UG_BWD(W, H)                                                                                            \
+  if (tile_w == W && tile_h == H) {                                                                             \
+    if (one)                                                                                                    \
+      UG_BWD_NW(W, H, 1);                                                                                       \
+    else                                                                                                        \
+      UG_BWD_NW(W, H, 4);                                                                                       \
+    return hipGetLastError();                                                                                   \
   }
   UG_TILE_SHAPES(UG_BWD)
 #undef UG_BWD
+#undef UG_BWD_NW
   return hipErrorInvalidValue;
 }
 
