@@ -212,8 +212,8 @@ hipError_t enqueue_preprocess(const ug_plan* plan, const ug_gaussians& g, const 
                               const RenderParams& rp, hipStream_t s, bool emit = true) {
   const Layout& L = plan->lay;
   Ctrl* ctrl = at<Ctrl>(ws, L.ctrl);
-  hipError_t e;
-  {
+  hipError_t e = hipSuccess;
+  if (!cull_inits(rp.n, rp.p)) {
     StageScope sc(plan, UG_STAGE_SETUP, s);
     e = launch_init(pl, plan->d_pint, at<PlaneConst>(ws, L.pconst), at<PlaneCull>(ws, L.pcull),
                     at<PlaneGroups>(ws, L.pgroups), (plan->prm.flags & UG_FLAG_CULL_EACH_PLANE) == 0, ctrl, s);
@@ -221,7 +221,7 @@ hipError_t enqueue_preprocess(const ug_plan* plan, const ug_gaussians& g, const 
   if (e != hipSuccess) return e;
   {
     StageScope sc(plan, UG_STAGE_CULL_COUNT, s);
-    e = launch_cull_count(g, at<PlaneCull>(ws, L.pcull), at<PlaneGroups>(ws, L.pgroups), rp, at<uint32_t>(ws, L.cnt_rec),
+    e = launch_cull_count(g, pl, plan->d_pint, at<PlaneConst>(ws, L.pconst), at<PlaneCull>(ws, L.pcull), at<PlaneGroups>(ws, L.pgroups), rp, at<uint32_t>(ws, L.cnt_rec),
                           at<unsigned long long>(ws, L.accbits), at<uint32_t>(ws, L.blk_g), ctrl, s);
   }
   if (e != hipSuccess) return e;

@@ -13,9 +13,10 @@ hipError_t launch_init(const ug_planes& pl, const PlaneInt* pint, PlaneConst* pc
 // Phase-1 cull: per-(Gaussian, plane) acceptance bits and per-Gaussian record
 // counts, then record offsets and the compact (Gaussian, plane) pair list.
 size_t accbits_words(int n, int p);
-hipError_t launch_cull_count(const ug_gaussians& g, const PlaneCull* pcf, const PlaneGroups* pg,
-                             const RenderParams& rp, uint32_t* cnt_rec, unsigned long long* accbits, uint32_t* blk_tot,
-                             Ctrl* ctrl, hipStream_t s);
+bool cull_inits(int n, int p);  // the cull passes do the setup kernel's work
+hipError_t launch_cull_count(const ug_gaussians& g, const ug_planes& pl, const PlaneInt* pint, PlaneConst* pc,
+                             const PlaneCull* pcf, const PlaneGroups* pg, const RenderParams& rp, uint32_t* cnt_rec,
+                             unsigned long long* accbits, uint32_t* blk_tot, Ctrl* ctrl, hipStream_t s);
 hipError_t launch_cull_write(const RenderParams& rp, const uint32_t* cnt_rec, const unsigned long long* accbits,
                              const uint32_t* blk_tot, unsigned long long* off_rec, uint2* rec_pair, Ctrl* ctrl,
                              hipStream_t s);

@@ -19,7 +19,7 @@ namespace ug {
 // FP64 constants of plane p's pose (an invalid pose is marked and skipped; the
 // cull raises the flag) and the float constants of its cull.
 __device__ __forceinline__ PlaneCull plane_setup(const ug_planes& pl, const PlaneInt* __restrict__ pint, int p,
-                                                 PlaneConst* __restrict__ pc, PlaneCull* __restrict__ pcf) {
+                                                 PlaneConst* __restrict__ pc, bool write) {
   double R[9];
   bool fin = true;
 #pragma unroll
@@ -58,7 +58,7 @@ __device__ __forceinline__ PlaneCull plane_setup(const ug_planes& pl, const Plan
   c.cv = 0.5 * (double)pint[p].H - 0.5;
   c.valid = fin ? 1 : 0;
   c.pad = 0;
-  pc[p] = c;
+  if (write) pc[p] = c;
   PlaneCull q;
   for (int k = 0; k < 3; ++k) {
     q.o[k] = pl.origin[3 * p + k];
@@ -66,7 +66,6 @@ __device__ __forceinline__ PlaneCull plane_setup(const ug_planes& pl, const Plan
   }
   q.valid = c.valid;
   q.pad = 0;
-  pcf[p] = q;
   return q;
 }
 
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(256) void k_init(ug_planes pl, const PlaneInt* __re
   const int p = (int)gid;
   const bool mine = p < pl.p;
   PlaneCull q{};
-  if (mine) q = plane_setup(pl, pint, p, pc, pcf);
+  if (mine) pcf[p] = q = plane_setup(pl, pint, p, pc, true);
   if (!group) {  // uniform (a launch argument)
     if (gid == 0) pg->use = 0u;
     return;
@@ -244,9 +243,9 @@ __device__ __forceinline__ T block_exscan_256(T v, T* sh /*[4]*/, T& total) {
 
 // Sum of the first b block totals, by the whole block (coalesced reads).
 __device__ __forceinline__ unsigned long long block_prefix(const uint32_t* __restrict__ tot, uint32_t b,
-                                                           unsigned long long* sh /*[4]*/) {
+                                                           unsigned long long* sh /*[4]*/, uint32_t mask = ~0u) {
   unsigned long long s = 0;
-  for (uint32_t i = threadIdx.x; i < b; i += 256) s += tot[i];
+  for (uint32_t i = threadIdx.x; i < b; i += 256) s += tot[i] & mask;
   unsigned long long t;
   block_exscan_256<unsigned long long>(s, sh, t);
   return t;
@@ -264,18 +263,30 @@ __device__ __forceinline__ unsigned long long block_prefix(const uint32_t* __res
 // pair whose plane narrowly misses the ellipsoid, and such a record has an
 // empty support, so it adds exactly zero everywhere.  Acceptance is kept as
 // one bit per (Gaussian, plane), 64 planes per word.
-template <int LPG>
-__global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, const PlaneCull* __restrict__ pcf,
+//
+// INIT (up to kInitPlanes planes, and no groups to search): the launch's
+// planes are set up here, by every block for itself, instead of by a kernel
+// before it (3 us and the wait for it: the setup takes the time of the
+// Gaussians' loads).  The first block writes the constants the later kernels
+// read, and what the setup kernel would have cleared, the control block, is
+// written whole by the write pass; until then a block's flag travels in the
+// top bit of its total.
+constexpr int kInitPlanes = 64;
+constexpr uint32_t kTotFlag = 0x80000000u;
+template <int LPG, bool INIT>
+__global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, ug_planes pl, const PlaneInt* __restrict__ pint,
+                                                    PlaneConst* __restrict__ pc, const PlaneCull* __restrict__ pcf,
                                                     const PlaneGroups* __restrict__ pg, RenderParams rp, int gpb,
                                                     uint32_t* __restrict__ cnt_rec,
                                                     unsigned long long* __restrict__ accbits,
                                                     uint32_t* __restrict__ blk_tot, Ctrl* __restrict__ ctrl) {
-  __shared__ uint32_t s_tot;
+  __shared__ uint32_t s_tot, s_flag;
+  __shared__ PlaneCull s_pcf[INIT ? kInitPlanes : 1];
   // grouped planes (one lane per Gaussian): each group is searched for the
   // window of planes the pre-test can accept, and only those are tested
   __shared__ uint16_t s_perm[kGroupMaxPlanes], s_end[kGroupMaxPlanes];
   __shared__ float s_oz[kGroupMaxPlanes];
-  const bool grouped = LPG == 1 && pg->use != 0u;  // uniform
+  const bool grouped = !INIT && LPG == 1 && pg->use != 0u;  // uniform
   if (grouped) {
     for (int j = (int)threadIdx.x; j < rp.p; j += 256) {
       s_perm[j] = (uint16_t)pg->perm[j];
@@ -283,8 +294,15 @@ __global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, const PlaneC
       s_oz[j] = pg->oz[j];
     }
   }
-  if (threadIdx.x == 0) s_tot = 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (threadIdx.x == 0) s_tot = s_flag = 0;
+  if (INIT) {
+    __syncthreads();
+    const int p = (int)threadIdx.x;
+    if (p < rp.p) {
+      s_pcf[p] = plane_setup(pl, pint, p, pc, blockIdx.x == 0);
+      if (!s_pcf[p].valid) s_flag = 1u;
+    }
+  } else if (blockIdx.x == 0 && threadIdx.x == 0) {
     for (int p = 0; p < rp.p; ++p)
       if (!pcf[p].valid) {
         atomicOr(&ctrl->flags, kFlagNonfinite);
@@ -301,7 +319,10 @@ __global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, const PlaneC
     GaussT<float> G;
     G.finite = false;
     if (has) load_gauss<float>(g, gi, rp.beta, G, true);
-    if (has && sub == 0 && !G.finite) atomicOr(&ctrl->flags, kFlagNonfinite);
+    if (has && sub == 0 && !G.finite) {
+      if (INIT) s_flag = 1u;
+      else atomicOr(&ctrl->flags, kFlagNonfinite);
+    }
     const bool live = has && G.finite;
     uint32_t count = 0;
     if (grouped) {
@@ -344,7 +365,7 @@ __global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, const PlaneC
       const int pend = min(64, rp.p - c * 64);
       unsigned long long bits = 0;
       for (int j = sub; j < pend; j += LPG) {
-        const PlaneCull pf = pcf[c * 64 + j];
+        const PlaneCull pf = INIT ? s_pcf[j] : pcf[c * 64 + j];
         if (live && pf.valid && cull_maybe(G, pf, rp.chi2)) bits |= 1ull << j;
       }
 #pragma unroll
@@ -359,13 +380,15 @@ __global__ __launch_bounds__(256) void k_cull_count(ug_gaussians g, const PlaneC
   }
   if (mine) atomicAdd(&s_tot, mine);
   __syncthreads();
-  if (threadIdx.x == 0) blk_tot[blockIdx.x] = s_tot;
+  if (threadIdx.x == 0) blk_tot[blockIdx.x] = s_tot | (s_flag ? kTotFlag : 0u);
 }
 
 // Offsets and the compact (Gaussian, plane) list, Gaussian-major with planes
 // ascending.  A block covers m consecutive count blocks (gpb Gaussians in
-// all).  The last block publishes the total and the capacity check.
-__global__ __launch_bounds__(256) void k_cull_write(RenderParams rp, int gpb, uint32_t m, uint32_t nblk,
+// all).  The last block publishes the total and the capacity check; with INIT
+// (see the count pass) it writes the whole control block.
+template <bool INIT>
+__global__ __launch_bounds__(256) void k_cull_write(RenderParams rp, int gpb, uint32_t m, uint32_t nblk, uint32_t ncnt,
                                                     const uint32_t* __restrict__ cnt_rec,
                                                     const unsigned long long* __restrict__ accbits,
                                                     const uint32_t* __restrict__ blk_tot,
@@ -379,7 +402,7 @@ __global__ __launch_bounds__(256) void k_cull_write(RenderParams rp, int gpb, ui
   const bool has0 = (int)threadIdx.x < gpb && gi0 < rp.n;
   const unsigned long long cnt0 = has0 ? cnt_rec[gi0] : 0ull;
   const unsigned long long bits0 = has0 ? accbits[(size_t)gi0 * nch] : 0ull;
-  unsigned long long carry = block_prefix(blk_tot, blockIdx.x * m, s_sh);
+  unsigned long long carry = block_prefix(blk_tot, blockIdx.x * m, s_sh, INIT ? ~kTotFlag : ~0u);
   for (int r0 = 0; r0 < gpb; r0 += 256) {
     const int gi = blockIdx.x * gpb + r0 + threadIdx.x;
     const bool has = r0 + (int)threadIdx.x < gpb && gi < rp.n;
@@ -400,9 +423,22 @@ __global__ __launch_bounds__(256) void k_cull_write(RenderParams rp, int gpb, ui
       }
     }
   }
+  uint32_t flag = 0u;
+  if (INIT && blockIdx.x == nblk - 1) {  // uniform
+    for (uint32_t i = threadIdx.x; i < ncnt; i += 256) flag |= blk_tot[i] & kTotFlag;
+    flag = __syncthreads_or((int)flag) ? kFlagNonfinite : 0u;
+  }
   if (blockIdx.x == nblk - 1 && threadIdx.x == 0) {
     ctrl->n_rec = carry;
-    if (carry > rp.rec_cap) atomicOr(&ctrl->flags, kFlagRecCap);
+    if (INIT) {
+      ctrl->n_key = 0;
+      ctrl->n_eval = 0;
+      ctrl->n_exec = 0;
+      ctrl->n_key_eff = 0;
+      ctrl->flags = flag | (carry > rp.rec_cap ? kFlagRecCap : 0u);
+    } else if (carry > rp.rec_cap) {
+      atomicOr(&ctrl->flags, kFlagRecCap);
+    }
     ctrl->n_rec_eff = carry <= rp.rec_cap ? (uint32_t)carry : 0u;
   }
 }
@@ -1130,17 +1166,28 @@ hipError_t launch_init(const ug_planes& pl, const PlaneInt* pint, PlaneConst* pc
 
 size_t accbits_words(int n, int p) { return (size_t)n * (size_t)((p + 63) / 64); }
 
-hipError_t launch_cull_count(const ug_gaussians& g, const PlaneCull* pcf, const PlaneGroups* pg,
-                             const RenderParams& rp, uint32_t* cnt_rec, unsigned long long* accbits, uint32_t* blk_tot,
-                             Ctrl* ctrl, hipStream_t s) {
+// The count pass sets the planes up itself (and the write pass the control
+// block) where it tests every plane for every Gaussian anyway.
+bool cull_inits(int n, int p) {
+  return n > 0 && p <= kInitPlanes && (cull_lpg_log2(n, p) > 0 || p < (int)kGroupSearch);
+}
+
+hipError_t launch_cull_count(const ug_gaussians& g, const ug_planes& pl, const PlaneInt* pint, PlaneConst* pc,
+                             const PlaneCull* pcf, const PlaneGroups* pg, const RenderParams& rp, uint32_t* cnt_rec,
+                             unsigned long long* accbits, uint32_t* blk_tot, Ctrl* ctrl, hipStream_t s) {
   const uint32_t nb = cull_blocks(rp.n, rp.p);
   if (nb == 0) return hipGetLastError();  // no Gaussians: the zeroed totals stand
   const int gpb = cull_gpb(rp.n, rp.p);
+  const bool init = cull_inits(rp.n, rp.p);
   switch (cull_lpg_log2(rp.n, rp.p)) {
-#define UG_CULL(L)                                                                                              \
-  case L:                                                                                                       \
-    hipLaunchKernelGGL(k_cull_count<(1 << L)>, dim3(nb), dim3(256), 0, s, g, pcf, pg, rp, gpb, cnt_rec, accbits, \
-                       blk_tot, ctrl);                                                                              \
+#define UG_CULL(L)                                                                                                    \
+  case L:                                                                                                             \
+    if (init)                                                                                                         \
+      hipLaunchKernelGGL((k_cull_count<(1 << L), true>), dim3(nb), dim3(256), 0, s, g, pl, pint, pc, pcf, pg, rp,     \
+                         gpb, cnt_rec, accbits, blk_tot, ctrl);                                                       \
+    else                                                                                                              \
+      hipLaunchKernelGGL((k_cull_count<(1 << L), false>), dim3(nb), dim3(256), 0, s, g, pl, pint, pc, pcf, pg, rp,    \
+                         gpb, cnt_rec, accbits, blk_tot, ctrl);                                                       \
     break;
     UG_CULL(0)
     UG_CULL(1)
@@ -1165,8 +1212,12 @@ hipError_t launch_cull_write(const RenderParams& rp, const uint32_t* cnt_rec, co
   const int gpb = cull_gpb(rp.n, rp.p);
   const uint32_t m = gpb < 256 ? (uint32_t)(256 / gpb) : 1u;
   const uint32_t nbw = (nb + m - 1) / m;
-  hipLaunchKernelGGL(k_cull_write, dim3(nbw), dim3(256), 0, s, rp, gpb * (int)m, m, nbw, cnt_rec, accbits, blk_tot,
-                     off_rec, rec_pair, ctrl);
+  if (cull_inits(rp.n, rp.p))
+    hipLaunchKernelGGL(k_cull_write<true>, dim3(nbw), dim3(256), 0, s, rp, gpb * (int)m, m, nbw, nb, cnt_rec, accbits,
+                       blk_tot, off_rec, rec_pair, ctrl);
+  else
+    hipLaunchKernelGGL(k_cull_write<false>, dim3(nbw), dim3(256), 0, s, rp, gpb * (int)m, m, nbw, nb, cnt_rec,
+                       accbits, blk_tot, off_rec, rec_pair, ctrl);
   return hipGetLastError();
 }
 
