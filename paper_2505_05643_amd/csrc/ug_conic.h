@@ -361,11 +361,11 @@ __device__ __forceinline__ bool band_mask_prep(const RecAcc& ra, int ub, int vb,
   return d >= 0.f;
 }
 
-// Sub-block columns [ca, cz] (of 8 pixels) the ellipse may reach in pixel rows
-// [ya, yb], cut to the pixel columns [umin, umax]; ca > cz if none.
-__device__ __forceinline__ void band_mask_cols(const BandMask& b, int ya, int yb, int umin, int umax, int& ca,
+// Sub-block columns [ca, cz] (of 8 pixels) the ellipse may reach in the rows
+// [lo, hi] below the centre's pixel row, cut to the pixel columns [umin, umax]
+// (>= 0); ca > cz if none.
+__device__ __forceinline__ void band_mask_cols(const BandMask& b, float lo, float hi, int umin, int umax, int& ca,
                                                int& cz) {
-  const float lo = (float)(ya - b.vb) - b.fv, hi = (float)(yb - b.vb) - b.fv;
   const float pv = fmaf(2e-6f, fmaxf(fabsf(lo), fabsf(hi)), 2e-3f);
   const float vr = __builtin_amdgcn_fmed3f(b.dvr, lo - pv, hi + pv);
   const float vl = __builtin_amdgcn_fmed3f(-b.dvr, lo - pv, hi + pv);
@@ -377,24 +377,26 @@ __device__ __forceinline__ void band_mask_cols(const BandMask& b, int ya, int yb
   // columns relative to the centre's pixel, cut before the conversion
   const float fl = fmaxf(ceilf(ul + b.fu - pu), (float)(umin - b.ub));
   const float fr = fminf(floorf(ur + b.fu + pu), (float)(umax - b.ub));
-  const bool any = b.all || (qr >= 0.f && fl <= fr);  // qr < 0: the rows lie beside the ellipse
-  ca = any ? (b.all ? umin : (int)fl + b.ub) / kSubBlock : 1;
-  cz = any ? (b.all ? umax : (int)fr + b.ub) / kSubBlock : 0;
+  const bool any = qr >= 0.f && fl <= fr;  // qr < 0: the rows lie beside the ellipse
+  ca = any ? ((int)fl + b.ub) >> 3 : 1;
+  cz = any ? ((int)fr + b.ub) >> 3 : 0;
+  static_assert(kSubBlock == 8, "shift");
+  if (b.all) {
+    ca = umin >> 3;
+    cz = umax >> 3;
+  }
 }
 
-// Mask of the sub-blocks of tile column tx that the bands' columns reach
-// (K = TW / 8 column blocks per band, TH / 8 <= kMaxBands bands).
-constexpr int kMaxBands = 4;
-__device__ __forceinline__ uint32_t tile_mask(const int (&ca)[kMaxBands], const int (&cz)[kMaxBands], int nb, int tx,
-                                              int K) {
+// Mask of the sub-blocks of tile column tx that the bands' columns reach (K =
+// TW / 8 column blocks per band, NB bands).
+template <int NB, int K>
+__device__ __forceinline__ uint32_t tile_mask(const int (&ca)[NB], const int (&cz)[NB], int tx) {
   const int x0 = tx * K;
   uint32_t m = 0;
 #pragma unroll
-  for (int b = 0; b < kMaxBands; ++b) {
-    if (b < nb) {  // uniform
-      const int lo = max(ca[b] - x0, 0), n = max(min(cz[b] - x0, K - 1) - lo + 1, 0);
-      m |= ((1u << n) - 1u) << (lo + b * K);
-    }
+  for (int b = 0; b < NB; ++b) {
+    const int lo = max(ca[b] - x0, 0), n = max(min(cz[b] - x0, K - 1) - lo + 1, 0);
+    m |= ((1u << n) - 1u) << (lo + b * K);
   }
   return m;
 }
@@ -417,25 +419,29 @@ __device__ __forceinline__ bool rows_span(const BandPrep& bp, int ty, int TW, in
 }
 
 // Key count of a record binned by rows over its tile rectangle (rows_span summed
-// over its tile rows), and the spans of its first kRowSpans tile rows.
+// over its tile rows), and the spans of its first tile rows (RowSpans).
 __device__ __forceinline__ uint32_t rows_count(const RecAcc& ra, const RecGeo& geo, int W, int H, int TW, int TH,
                                                RowSpans& spans) {
-  spans = kNoSpans;
+  spans = RowSpans{0u, 0u};
+  const int bits = span_bits(geo.tx1 - geo.tx0);
   const int umin = geo.tx0 * TW;
   const int umax = min(geo.tx1 * TW + TW - 1, W - 1);
   BandPrep bp;
   if (!band_prep(ra, geo.ub, geo.vb, bp)) return 0;
   uint32_t keys = 0;
+  int at = 0;
   for (int ty = geo.ty0; ty <= geo.ty1; ++ty) {
     int tx0, tx1;
     if (rows_span(bp, ty, TW, TH, H, umin, umax, tx0, tx1)) {
       keys += (uint32_t)(tx1 - tx0 + 1);
-      const int i = 8 * (ty - geo.ty0);
-      if (i < 8 * kRowSpans) {
-        const uint32_t keep = ~(0xffu << i);
-        spans.first = (spans.first & keep) | ((uint32_t)(tx0 - geo.tx0) & 0xffu) << i;
-        spans.last = (spans.last & keep) | ((uint32_t)(tx1 - geo.tx0) & 0xffu) << i;
-      }
+    } else {
+      tx0 = geo.tx0 + 1;
+      tx1 = geo.tx0;
+    }
+    if (at + bits <= 32) {
+      spans.first |= (uint32_t)(tx0 - geo.tx0) << at;
+      spans.last |= (uint32_t)(tx1 - geo.tx0) << at;
+      at += bits;
     }
   }
   return keys;

@@ -132,16 +132,17 @@ static_assert(sizeof(RecGeo) == 24, "RecGeo layout");
 // kernels' gathers (one record per key, in tile order: random in record
 // order) fetch one 64-byte segment per key instead of two.  The slot's last
 // 8 bytes carry, for binning by rows, the tile spans of the record's first
-// kRowSpans tile rows as counted by the record kernel (first and last tile
-// of row i relative to the rectangle's first, byte i of each word; first >
-// last for a row the ellipse misses), so the emission reuses them instead of
-// recomputing them; rectangles wider than kSpanTiles tiles don't.
-constexpr int kRowSpans = 4;
-constexpr int kSpanTiles = 255;
+// tile rows as counted by the record kernel: first and last tile of row i
+// relative to the rectangle's first, in bits [b i, b i + b) of each word with
+// b = span_bits of the rectangle's width, for as many rows as 32 bits hold
+// (first > last for a row the ellipse misses), so the emission reuses them
+// instead of recomputing them.
 struct RowSpans {
   uint32_t first, last;
 };
-constexpr RowSpans kNoSpans{0x01010101u, 0u};
+// Bits of a tile column relative to the first of a rectangle of w + 1 columns
+// (one at least: a missed row is first 1, last 0).
+__device__ __forceinline__ int span_bits(int w) { return w > 0 ? 32 - __builtin_clz((unsigned)w) : 1; }
 struct Rec {
   RecAcc acc;
   RecGeo geo;
@@ -193,6 +194,17 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);  // row_shr:8
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true);  // lane 15 of a row to the next
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true);  // lane 31 to the upper half
+  return x;
+}
+
+// Inclusive prefix maximum over the wave's lanes.
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true));
   return x;
 }
 

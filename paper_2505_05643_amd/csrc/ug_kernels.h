@@ -112,6 +112,17 @@ hipError_t launch_param_eval(int32_t kind, bool fp64, const float* raw, const fl
 // ---- throughput probes (ug_probe.hip)
 hipError_t launch_probe(int kind, int blocks, int iters, const float* src, float* dst, int64_t n, hipStream_t s);
 
+// Tile shapes compiled in (multiples of the 8x8 sub-block).
+#define UG_TILE_SHAPES(X) \
+  X(8, 8)                 \
+  X(16, 8)                \
+  X(8, 16)                \
+  X(16, 16)               \
+  X(32, 8)                \
+  X(32, 16)               \
+  X(16, 32)               \
+  X(32, 32)
+
 // ---- accumulate (ug_raster.hip)
 int accum_default_ppl(int tile_w, int tile_h);
 bool accum_config_supported(int tile_w, int tile_h, int ppl, int lds_batch);

@@ -457,56 +457,99 @@ __device__ __forceinline__ uint32_t record_rpb_dev(uint32_t nrec, uint32_t grid)
   const uint32_t per = (rounds + grid - 1u) / grid;
   return (per < 1u ? 1u : per) * 256u;
 }
-__device__ __forceinline__ void emit_keys(const RecAcc& ra, const RecGeo& geo, const RowSpans& spans,
-                                          const PlaneInt& PI, bool by_rows, int TW, int TH, int tile_bits, uint32_t r,
-                                          uint32_t e, uint32_t e_end, uint32_t part, uint32_t parts,
-                                          uint32_t* __restrict__ key_tile, uint32_t* __restrict__ rec_of_key) {
-  const int mshift = key_mask_shift(TW, TH);
-  const uint32_t e0 = e, last_index = (1u << (mshift - tile_bits)) - 1u;  // indices from here on: looked up
-  const bool known = by_rows && geo.tx1 - geo.tx0 <= kSpanTiles - 1;
-  const int umin = geo.tx0 * TW;
-  const int umax = min(geo.tx1 * TW + TW - 1, PI.W - 1);
-  BandMask bm;
-  const bool ok = band_mask_prep(ra, geo.ub, geo.vb, bm);
-  if (by_rows && !ok) return;
-  BandPrep bp;  // only for the rows whose spans the record does not hold
-  if (by_rows && (!known || geo.ty1 - geo.ty0 >= kRowSpans)) band_prep(ra, geo.ub, geo.vb, bp);
-  const int nb = TH / kSubBlock, K = TW / kSubBlock;
-  for (int ty = geo.ty0; ty <= geo.ty1; ++ty) {
-    int tx0 = geo.tx0, tx1 = geo.tx1;
-    if (by_rows) {
-      // the record kernel's span for the first kRowSpans rows, else recomputed
-      const int i = ty - (int)geo.ty0;
-      if (known && i < kRowSpans) {
-        tx0 = geo.tx0 + (int)((spans.first >> (8 * i)) & 0xffu);
-        tx1 = geo.tx0 + (int)((spans.last >> (8 * i)) & 0xffu);
-        if (tx0 > tx1) continue;
-      } else if (!rows_span(bp, ty, TW, TH, PI.H, umin, umax, tx0, tx1)) {
-        continue;
+
+// What the emission's items need of a record, in LDS (80 bytes, read 16 at a
+// time).
+struct EmitRec {
+  float4 mask0;  // BandMask: t22, a, i11, d
+  float4 mask1;  // dvr, fu, fv, and ub's bits
+  uint4 at;      // vb's bits, first key, one past the last, first item
+  uint4 geo;     // tx0 | tx1 << 16, ty0, RowSpans
+  uint4 plane;   // first tile, tile columns, W | H << 16, flags: 1 no cut-off, 2 has support
+};
+
+// Writes the keys of a wave's records (its lanes'): lanes = items (record,
+// tile row), 64 at a time in record order, so a record with many rows does
+// not hold up the others and the keys of neighbouring lanes are neighbours in
+// memory.  A lane walking its record's rows took 418 us at 16.2M records with
+// 33.5M keys (398 so, 2.8 TB/s of slots read and keys written), 198 at 3.6M
+// needles with 11.8M keys (135), 123 at 2.1M with 25M (96); bound by its VALU
+// instructions (80% of the issue) beside those stores.  The tile shape is a
+// template argument: band loops and masks without run-time bounds gave 475 ->
+// 441 us at 69M keys.  nr = the lane's record's tile rows (0: no keys), key = the wave's
+// first key; an item's first key is the number of keys of the items before
+// it.  Of every PARTS chunks of 64 items only the part-th is written.
+template <uint32_t PARTS, int TW, int TH>
+__device__ __forceinline__ void emit_items(const EmitRec* __restrict__ s_rec, uint32_t* __restrict__ s_mark,
+                                           const Rec* __restrict__ recs, const RenderParams& rp, uint32_t r0,
+                                           uint32_t nr, uint32_t first_item, uint32_t items, uint32_t key,
+                                           uint32_t part, uint32_t* __restrict__ key_tile,
+                                           uint32_t* __restrict__ rec_of_key) {
+  constexpr int NB = TH / kSubBlock, K = TW / kSubBlock;
+  constexpr int mshift = key_mask_shift(TW, TH);
+  const uint32_t last_index = (1u << (mshift - rp.tile_bits)) - 1u;  // indices from here on: looked up
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t open = 0u;  // 1 + the record whose items the chunk starts with
+  for (uint32_t base = 0, chunk = 0; base < items; base += 64, ++chunk) {
+    // the lane's record: the last one that starts at or before its item
+    s_mark[lane] = 0u;
+    wave_lds_sync();
+    if (nr > 0 && first_item - base < 64u) s_mark[first_item - base] = lane + 1u;
+    wave_lds_sync();
+    uint32_t m = s_mark[lane];
+    if (lane == 0) m = max(m, open);
+    m = wave_incl_max(m);
+    open = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    wave_lds_sync();
+    const bool has = base + lane < items;
+    const uint32_t rl = m - 1u;  // the first item starts a record: m > 0
+    const EmitRec& R = s_rec[rl];
+    const uint4 at = R.at, geo = R.geo, plane = R.plane;
+    const int gx0 = (int)(geo.x & 0xffffu), gx1 = (int)(geo.x >> 16);
+    const int W = (int)(plane.z & 0xffffu), H = (int)(plane.z >> 16);
+    const int i = (int)(base + lane - at.w), ty = (int)geo.y + i;
+    const int umin = gx0 * TW, umax = min(gx1 * TW + TW - 1, W - 1);
+    int tx0 = gx0, tx1 = has ? gx1 : gx0 - 1;
+    if (rp.by_rows && has) {
+      // the record kernel's span for the rows it kept, else recomputed
+      const int bits = span_bits(gx1 - gx0), at_bit = bits * i;
+      if (at_bit + bits <= 32) {
+        const uint32_t mask = (1u << bits) - 1u;
+        tx0 = gx0 + (int)(geo.z >> at_bit & mask);
+        tx1 = gx0 + (int)(geo.w >> at_bit & mask);
+      } else {
+        BandPrep bp;
+        if (!band_prep(recs[r0 + rl].acc, (int)__float_as_uint(R.mask1.w), (int)at.x, bp) ||
+            !rows_span(bp, ty, TW, TH, H, umin, umax, tx0, tx1))
+          tx1 = tx0 - 1;
       }
     }
-    if (((uint32_t)(ty - (int)geo.ty0) & (parts - 1u)) != part) {
-      e += (uint32_t)(tx1 - tx0 + 1);
-      continue;
-    }
-    int ca[kMaxBands], cz[kMaxBands];
+    const uint32_t len = (uint32_t)max(tx1 - tx0 + 1, 0);
+    const uint32_t incl = wave_incl_sum(len);
+    uint32_t e = key + incl - len;
+    key += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    if (PARTS > 1 && chunk % PARTS != part) continue;  // uniform
+    const float4 m0 = R.mask0, m1 = R.mask1;
+    const BandMask bm{m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, (int)__float_as_uint(m1.w), (int)at.x,
+                      (plane.w & 1u) != 0u};
+    // rows below the centre's: the tile row's first and the plane's last
+    const float y0 = (float)(ty * TH - bm.vb) - bm.fv, yl = (float)(H - 1 - bm.vb) - bm.fv;
+    int ca[NB], cz[NB];
 #pragma unroll
-    for (int b = 0; b < kMaxBands; ++b) {
-      ca[b] = 1;
-      cz[b] = 0;
-      if (b < nb) {  // uniform
-        const int ya = ty * TH + b * kSubBlock, yb = min(ya + kSubBlock - 1, PI.H - 1);
-        if (ok && ya <= yb) band_mask_cols(bm, ya, yb, umin, umax, ca[b], cz[b]);
-      }
+    for (int b = 0; b < NB; ++b) {
+      const float ya = y0 + (float)(b * kSubBlock), yb = fminf(ya + (float)(kSubBlock - 1), yl);
+      band_mask_cols(bm, ya, yb, umin, umax, ca[b], cz[b]);
+      if (!(plane.w & 2u) || ty * TH + b * kSubBlock >= H) cz[b] = ca[b] - 1;
     }
-    const uint32_t rowbase = PI.tile_off + (uint32_t)ty * (uint32_t)PI.ntx;
-    for (int tx = tx0; tx <= tx1; ++tx) {
-      if (e < e_end) {
-        key_tile[e] = (rowbase + (uint32_t)tx) | min(e - e0, last_index) << tile_bits |
-                      (tile_mask(ca, cz, nb, tx, K) << mshift);
+    const uint32_t tile0 = plane.x + (uint32_t)ty * plane.y;
+    const uint32_t r = r0 + rl;
+    for (int tx = tx0; tx <= tx1; ++tx, ++e) {
+      const uint32_t index = e - at.y;
+      if (index < at.z - at.y) {
+        key_tile[e] = (tile0 + (uint32_t)tx) | min(index, last_index) << rp.tile_bits |
+                      (tile_mask<NB, K>(ca, cz, tx) << mshift);
         rec_of_key[e] = r;
       }
-      ++e;
     }
   }
 }
@@ -638,7 +681,7 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
           f.keys = f.counted = 0;
           f.acc = RecAcc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
           f.geo = RecGeo{0, 0, 0, 0, 1, 0, 1, 0};
-          f.spans = kNoSpans;
+          f.spans = RowSpans{0u, 0u};
         }
         rec_nkey[r] = nk = f.keys;
         counted += f.counted;
@@ -682,17 +725,17 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
 }
 
 // Launches of up to kEmitPartBlocks record blocks give every block's records
-// to kEmitParts blocks, each writing the tile rows i with i % kEmitParts ==
-// part: so few blocks leave most CUs idle, and a CU that has one spends its
-// time on the scattered stores of its records' keys.  9 K records with 90 K
-// keys (36 blocks): 40 us with one block each, 16 with four.  The line: at
-// 400 blocks the four repeat the prefix and the scan for nothing (12.1 us
-// against 15.1 at 79 K records with 160 K keys).
+// to kEmitParts blocks, each writing the part-th of every kEmitParts chunks of
+// items: so few blocks leave most CUs idle, and a CU that has one spends its
+// time on the stores of its records' keys.  9 K records with 90 K keys (36
+// blocks): 14 us with one block each, 9.5 with four.  The line: at 400 blocks
+// the four repeat the prefix and the scan for nothing (10.8 us against 14.7 at
+// 79 K records with 160 K keys).
 constexpr uint32_t kEmitParts = 4, kEmitPartBlocks = 128;
 
 // Key offsets (block prefix + in-block scan) and key emission.  The last
 // active block publishes the key total and the capacity check.
-template <uint32_t PARTS>
+template <uint32_t PARTS, int TW, int TH>
 __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint, RenderParams rp,
                                               const uint2* __restrict__ rec_pair, const Rec* __restrict__ recs,
                                               const uint32_t* __restrict__ rec_nkey,
@@ -700,6 +743,8 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
                                               uint32_t* __restrict__ run_koff, Ctrl* __restrict__ ctrl, uint32_t* __restrict__ key_tile,
                                               uint32_t* __restrict__ rec_of_key) {
   __shared__ unsigned long long s_sh[4];
+  __shared__ EmitRec s_rec[256];
+  __shared__ uint32_t s_mark[256];
   const uint32_t nrec = ctrl->n_rec_eff;
   const uint32_t blk = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
   const uint32_t rpb = record_rpb_dev(nrec, gridDim.x / PARTS);
@@ -746,9 +791,24 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
     carry += tot;
     if (act) {
       if (part == 0) rec_koff[r] = (uint32_t)(koff < rp.key_cap ? koff : rp.key_cap);
-      if (nk > 0 && koff + nk <= rp.key_cap)
-        emit_keys(ra, ge, sp, PI, rp.by_rows != 0, rp.tile_w, rp.tile_h, rp.tile_bits, r, (uint32_t)koff,
-                  (uint32_t)(koff + nk), part, PARTS, key_tile, rec_of_key);
+    }
+    // (key offsets only grow: the records that fit come first)
+    const uint32_t nr = act && nk > 0 && koff + nk <= rp.key_cap ? (uint32_t)(ge.ty1 - ge.ty0 + 1) : 0u;
+    const uint32_t rows_incl = wave_incl_sum(nr);
+    const uint32_t items = (uint32_t)__builtin_amdgcn_readlane((int)rows_incl, 63);
+    if (items) {  // uniform over the wave
+      BandMask bm;
+      const bool ok = band_mask_prep(ra, ge.ub, ge.vb, bm);
+      EmitRec& R = s_rec[threadIdx.x];
+      R.mask0 = make_float4(bm.t22, bm.a, bm.i11, bm.d);
+      R.mask1 = make_float4(bm.dvr, bm.fu, bm.fv, __uint_as_float((uint32_t)ge.ub));
+      R.at = make_uint4((uint32_t)ge.vb, (uint32_t)koff, (uint32_t)koff + nk, rows_incl - nr);
+      R.geo = make_uint4((uint32_t)ge.tx0 | (uint32_t)ge.tx1 << 16, ge.ty0, sp.first, sp.last);
+      R.plane = make_uint4(PI.tile_off, (uint32_t)PI.ntx, (uint32_t)PI.W | (uint32_t)PI.H << 16,
+                           (bm.all ? 1u : 0u) | (ok ? 2u : 0u));
+      const uint32_t w0 = threadIdx.x & ~63u;
+      emit_items<PARTS, TW, TH>(s_rec + w0, s_mark + w0, recs, rp, r0 + w0, nr, rows_incl - nr, items,
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)koff), part, key_tile, rec_of_key);
     }
     r = rn;
     act = actn;
@@ -1239,13 +1299,21 @@ hipError_t launch_emit(const PlaneInt* pint, const RenderParams& rp, const uint2
                        const uint32_t* rec_nkey, const uint32_t* blk_tot, uint32_t* rec_koff, uint32_t* run_koff,
                        Ctrl* ctrl, uint32_t* key_tile, uint32_t* rec_of_key, hipStream_t s) {
   const uint32_t blocks = (uint32_t)record_blocks(rp.rec_cap);
-  if (blocks <= kEmitPartBlocks)
-    hipLaunchKernelGGL(k_emit<kEmitParts>, dim3(blocks * kEmitParts), dim3(256), 0, s, pint, rp, rec_pair, recs,
-                       rec_nkey, blk_tot, rec_koff, run_koff, ctrl, key_tile, rec_of_key);
-  else
-    hipLaunchKernelGGL(k_emit<1>, dim3(blocks), dim3(256), 0, s, pint, rp, rec_pair, recs, rec_nkey, blk_tot,
-                       rec_koff, run_koff, ctrl, key_tile, rec_of_key);
-  return hipGetLastError();
+#define UG_EMIT_PARTS(PARTS, W, H)                                                                                   \
+  hipLaunchKernelGGL((k_emit<PARTS, W, H>), dim3(blocks * PARTS), dim3(256), 0, s, pint, rp, rec_pair, recs, rec_nkey, \
+                     blk_tot, rec_koff, run_koff, ctrl, key_tile, rec_of_key)
+#define UG_EMIT(W, H)                            \
+  if (rp.tile_w == W && rp.tile_h == H) {        \
+    if (blocks <= kEmitPartBlocks)               \
+      UG_EMIT_PARTS(kEmitParts, W, H);           \
+    else                                         \
+      UG_EMIT_PARTS(1, W, H);                    \
+    return hipGetLastError();                    \
+  }
+  UG_TILE_SHAPES(UG_EMIT)
+#undef UG_EMIT
+#undef UG_EMIT_PARTS
+  return hipErrorInvalidValue;
 }
 
 size_t adjoint_side_floats(uint32_t rec_cap) { return ((size_t)rec_cap + 63) / 64 * 2 * kGradFields; }

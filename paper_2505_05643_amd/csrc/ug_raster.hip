@@ -656,17 +656,6 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
 }
 
 // ---------------------------------------------------------------- dispatch
-// Tile shapes compiled in (multiples of the 8x8 sub-block).
-#define UG_TILE_SHAPES(X) \
-  X(8, 8)                 \
-  X(16, 8)                \
-  X(8, 16)                \
-  X(16, 16)               \
-  X(32, 8)                \
-  X(32, 16)               \
-  X(16, 32)               \
-  X(32, 32)
-
 template <int TW, int TH, int SPLIT>
 static hipError_t fwd_bg(int bg, dim3 grid, hipStream_t s, const PlaneInt* pint, const uint32_t* tp,
                          const uint32_t* ts, const uint32_t* skey, const uint32_t* srec, const Rec* rc,
