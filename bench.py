@@ -775,8 +775,8 @@ def kernel_bytes(name, n, p, r, k, t, m, passes, w, rows, g_sort, dslots) -> int
         return 8 * dslots * g_sort
     if name == "sort_scatter":
         return 16 * k
-    if name == "ranges":
-        return 4 * k + 4 * t
+    if name == "ranges":  # eight probes per step and tile
+        return 32 * t * max(1, int(np.ceil(np.log(max(k, 2)) / np.log(9)))) + 4 * t
     if name == "record_adj":
         return 12 * r + 32 * k + 44 * n + 44 * n
     if name == "gauss_grad":

@@ -515,7 +515,7 @@ int render_impl(const ug_plan* plan, const ug_gaussians* g, const ug_planes* pla
   const Sorted so = sorted_set(plan, ws);
   if (plan->sort.passes > 1) {  // one pass wrote the ranges itself
     StageScope sc(plan, UG_STAGE_RANGES, s);
-    e = launch_tile_ranges(ctrl, so.key, plan->num_tiles, plan->key_cap, plan->bits, at<uint32_t>(ws, L.tile_start),
+    e = launch_tile_ranges(ctrl, so.key, plan->num_tiles, plan->bits, at<uint32_t>(ws, L.tile_start),
                            s);
   }
   if (e != hipSuccess) return UG_ERR_HIP;

@@ -72,8 +72,8 @@ hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[2], u
                                 uint32_t num_tiles, hipStream_t s);
 // tile_start[t] for t in [0, T] from the sorted key words (tile id = the key
 // word's low bits).
-hipError_t launch_tile_ranges(const Ctrl* ctrl, const uint32_t* skeys, uint32_t num_tiles, uint32_t key_cap,
-                              int bits, uint32_t* tile_start, hipStream_t s);
+hipError_t launch_tile_ranges(const Ctrl* ctrl, const uint32_t* skeys, uint32_t num_tiles, int bits,
+                              uint32_t* tile_start, hipStream_t s);
 
 // ---- Phase-2 atomic scatter forward (ug_scatter.hip): zero the sums, one
 // wave per record adds w c and w over its box, normalise in place.
