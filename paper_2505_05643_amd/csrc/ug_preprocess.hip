@@ -95,6 +95,13 @@ __device__ __forceinline__ uint32_t group_key_hash(const PlaneCull& q) {
   return h;
 }
 
+// Sum over the quad of lanes, in every lane of it.
+__device__ __forceinline__ uint32_t quad_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xb1, 0xf, 0xf, true);  // lanes 1 0 3 2
+  x += (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4e, 0xf, 0xf, true);  // lanes 2 3 0 1
+  return x;
+}
+
 // Groups of at least this many planes are searched by the cull.
 constexpr uint32_t kGroupSearch = 8;
 
@@ -105,9 +112,16 @@ constexpr uint32_t kGroupSearch = 8;
 // (its group's first position) and those with its hash (the group's size).
 // Every plane then checks that its key equals that of its group's first
 // plane; if two keys ever share a hash, the cull tests every plane instead.
-__global__ __launch_bounds__(256) void k_init(ug_planes pl, const PlaneInt* __restrict__ pint,
-                                              PlaneConst* __restrict__ pc, PlaneCull* __restrict__ pcf,
-                                              PlaneGroups* __restrict__ pg, int group, Ctrl* __restrict__ ctrl) {
+// Four neighbouring lanes share a plane's counts (a quarter of the planes
+// each), which are the kernel's longest chain: 256 planes 16 us with one lane
+// per plane, 12.9 so.
+template <bool GROUP>
+__global__ __launch_bounds__(GROUP ? 4 * kGroupMaxPlanes : 256) void k_init(ug_planes pl,
+                                                                         const PlaneInt* __restrict__ pint,
+                                                                         PlaneConst* __restrict__ pc,
+                                                                         PlaneCull* __restrict__ pcf,
+                                                                         PlaneGroups* __restrict__ pg,
+                                                                         Ctrl* __restrict__ ctrl) {
   __shared__ PlaneCull s_q[kGroupMaxPlanes];
   __shared__ unsigned long long s_hz[kGroupMaxPlanes];  // hash << 32 | order bits of o[2]
   __shared__ uint32_t s_first[kGroupMaxPlanes];         // plane at each group's first position
@@ -122,11 +136,13 @@ __global__ __launch_bounds__(256) void k_init(ug_planes pl, const PlaneInt* __re
     ctrl->n_rec_eff = 0;
     ctrl->n_key_eff = 0;
   }
-  const int p = (int)gid;
-  const bool mine = p < pl.p;
+  const int p = (int)(GROUP ? gid / 4u : gid);
+  const uint32_t part = GROUP ? gid % 4u : 0u;
+  const bool has = p < pl.p, mine = has && part == 0;
   PlaneCull q{};
-  if (mine) pcf[p] = q = plane_setup(pl, pint, p, pc, true);
-  if (!group) {  // uniform (a launch argument)
+  if (has) q = plane_setup(pl, pint, p, pc, mine);
+  if (mine) pcf[p] = q;
+  if (!GROUP) {
     if (gid == 0) pg->use = 0u;
     return;
   }
@@ -142,15 +158,20 @@ __global__ __launch_bounds__(256) void k_init(ug_planes pl, const PlaneInt* __re
   }
   __syncthreads();
   uint32_t rank = 0u, below = 0u, same = 0u;
-  if (mine) {
+  if (has) {
 #pragma unroll 8
-    for (int j = 0; j < pl.p; ++j) {  // the same j in every lane: broadcast reads
+    for (int j = (int)part; j < pl.p; j += 4) {
       const unsigned long long o = s_hz[j];
       rank += (o < hz || (o == hz && j < p)) ? 1u : 0u;
       const uint32_t oh = (uint32_t)(o >> 32);
       below += oh < h ? 1u : 0u;
       same += oh == h ? 1u : 0u;
     }
+  }
+  rank = quad_sum(rank);
+  below = quad_sum(below);
+  same = quad_sum(same);
+  if (mine) {
     pg->perm[rank] = (uint32_t)p;
     pg->oz[rank] = q.o[2];
     pg->end[rank] = below + same;
@@ -1137,15 +1158,23 @@ __global__ __launch_bounds__(256) void k_gauss_grad(ug_gaussians g, RenderParams
   if (loss_out && blockIdx.x == 0) {  // uniform
     __shared__ double s_l[256];
     double a = 0.0;
+    // 16 bytes per load (the array is aligned), eight loads in flight: the
+    // block's round trips are the kernel's tail
+    const float4* part4 = reinterpret_cast<const float4*>(loss_part);
+    const uint32_t n4 = nparts / 4u;
     uint32_t k = threadIdx.x;
-    for (; k + 7u * 256u < nparts; k += 8u * 256u) {  // eight loads in flight
-      float x[8];
+    for (; k + 7u * 256u < n4; k += 8u * 256u) {
+      float4 x[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) x[q] = loss_part[k + 256u * (uint32_t)q];
+      for (int q = 0; q < 8; ++q) x[q] = part4[k + 256u * (uint32_t)q];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) a += (double)x[q];
+      for (int q = 0; q < 8; ++q) a += ((double)x[q].x + (double)x[q].y) + ((double)x[q].z + (double)x[q].w);
     }
-    for (; k < nparts; k += 256) a += (double)loss_part[k];
+    for (; k < n4; k += 256) {
+      const float4 x = part4[k];
+      a += ((double)x.x + (double)x.y) + ((double)x.z + (double)x.w);
+    }
+    if (threadIdx.x < nparts % 4u) a += (double)loss_part[4u * n4 + threadIdx.x];
     s_l[threadIdx.x] = a;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
@@ -1219,8 +1248,10 @@ hipError_t launch_init(const ug_planes& pl, const PlaneInt* pint, PlaneConst* pc
                        bool group, Ctrl* ctrl, hipStream_t s) {
   const bool grp = group && pl.p >= 1 && pl.p <= kGroupMaxPlanes;  // one block
   const uint32_t blocks = grp ? 1u : ((uint32_t)pl.p + 255) / 256;
-  hipLaunchKernelGGL(k_init, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, pl, pint, pc, pcf, pg, grp ? 1 : 0,
-                     ctrl);
+  if (grp)
+    hipLaunchKernelGGL(k_init<true>, dim3(1), dim3(4 * kGroupMaxPlanes), 0, s, pl, pint, pc, pcf, pg, ctrl);
+  else
+    hipLaunchKernelGGL(k_init<false>, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, pl, pint, pc, pcf, pg, ctrl);
   return hipGetLastError();
 }
 
