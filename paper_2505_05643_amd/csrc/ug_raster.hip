@@ -488,8 +488,8 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
     uint32_t dst = run_koff[run] + koff + index;
     if (index == last_index) dst = find_emitted(emitted, rec_koff, rid, dst - index, t, (1u << tile_bits) - 1u);
     const uint32_t left = ke - k;
-    // a pass takes an even part of what is left, at most 64 keys
-    const uint32_t want = left > 64u ? (left + (left + 63u) / 64u - 1u) / ((left + 63u) / 64u) : left;
+    // at most 64 keys per pass, the last two passes alike
+    const uint32_t want = left > 128u ? 64u : (left > 64u ? (left + 1u) / 2u : left);
     const float du0 = (float)(ub - x0) + A.fu, dv0 = (float)(vb - y0) + A.fv;
     const WeightScale ws = weight_scale(A.e0, A.emin, cut);
     ItemStage& in = slot[wave].in;
