@@ -56,6 +56,7 @@ struct SortShape {
   int bits;          // of the tile id
   uint32_t blocks;
   bool small;        // one round per block
+  uint32_t chunk;    // keys of capacity per block
   int passes, digit_bits;
   uint32_t slots;    // digits of a histogram row
   size_t hist_words() const { return (size_t)slots * (blocks + 1u); }

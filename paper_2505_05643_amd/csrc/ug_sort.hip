@@ -106,99 +106,76 @@ __global__ __launch_bounds__(kScanDigits* kScanGroups) void k_radix_colscan(uint
   }
 }
 
-// Stable scatter.  The block's chunk is walked in rounds of up to 4096 keys;
-// in a round wave w owns the w-th quarter of the round's keys (rounded up to
-// whole loads of 64), loaded 64 at a time.  Each wave ranks its keys on its own: lanes holding
-// the same digit are found with one ballot per digit bit, and a per-wave digit counter
-// in LDS orders the wave's loads.  One block step then orders the waves and
-// the digits, the round is reordered by digit in LDS and written out as
-// contiguous runs per digit, so the global writes coalesce.
-// kItems keys per thread and round: 8 for small inputs (more blocks, less
-// LDS), 16 when every block walks several rounds.
-
-// Every key carries its record id.  It is loaded with the key (coalesced, in
-// flight during the ranking) and follows it through the same LDS slots: the
-// keys are reordered and written, then the record ids.  (A second payload
-// word, the emission index, cost a third of the traffic and of the LDS work:
-// 823 us for two passes over 42M keys with it.)
+// Stable scatter.  The block's chunk is walked in rounds of NT kItems keys; in
+// a round every wave owns an equal share of the round's keys (whole loads of
+// 64).  Each wave ranks its keys on its own: lanes holding the same digit are
+// found with one ballot per digit bit, and a per-wave digit counter in LDS
+// orders the wave's loads.  One block step then orders the waves and the
+// digits, the round is reordered by digit in LDS, keys and record ids
+// together, and written out as contiguous runs per digit, so the global
+// writes coalesce.  The next round's loads are in flight during the writes.
+// (A second payload word, the emission index, cost a third of the traffic and
+// of the LDS work: 823 us for two passes over 42M keys with it.)
 struct SortSet {
   uint32_t* key;
   uint32_t* rec;
 };
 
-template <int kItems>
-__device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in,
-                                                                SortSet out,
-                                                                const uint32_t* __restrict__ cnt,
-                                                                const uint32_t* __restrict__ coltot, uint32_t G,
-                                                                int shift, int dbits, uint32_t* __restrict__ tile_start,
-                                                                uint32_t T) {
-  constexpr int kRound = kSortThreads * kItems, D = 256;
-  const uint32_t* __restrict__ kin = in.key;
-  __shared__ uint32_t s_key[kRound];  // the round reordered by digit: keys, then record ids
-  constexpr int kPer = D / kSortThreads;  // digits per thread, consecutive
-  __shared__ uint32_t run[D];      // global output position of the next key of each digit
-  __shared__ uint32_t loc[D];      // first LDS slot of each digit in this round
-  __shared__ uint32_t rcnt[D];     // keys of each digit in this round
-  __shared__ uint32_t wcnt[4][D];  // per-wave digit counts, then the waves' prefixes
-  __shared__ uint32_t sh[4];
+template <int kItems, int NT>
+__device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in, SortSet out,
+                                              const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ coltot,
+                                              uint32_t G, int shift, int dbits, uint32_t* __restrict__ tile_start,
+                                              uint32_t T) {
+  constexpr int kRound = NT * kItems, D = 256, NW = NT / 64;
+  static_assert(NT >= D, "a digit per thread");
+  __shared__ uint32_t s_key[kRound], s_rec[kRound];  // the round reordered by digit
+  __shared__ uint32_t first[D];                      // output position of a digit's next key, less its first slot
+  __shared__ uint32_t wcnt[NW][D];                   // per-wave digit counts, then the slots of their first keys
+  __shared__ uint32_t sh[NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t dmask = (1u << dbits) - 1u;
   uint32_t s, e;
   sort_chunk(ctrl->n_key_eff, G, blockIdx.x, s, e);
+  uint32_t kk[kItems], rr[kItems], rc[kItems];
+  // a round's keys, split evenly over the waves in whole loads of 64
+  auto segment = [&](uint32_t base) { return ((min((uint32_t)kRound, e - base) + NT - 1u) / NT) * 64u; };
+  auto load_round = [&](uint32_t base) {
+    const uint32_t seg = segment(base), w0 = base + (uint32_t)wave * seg;
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+      const uint32_t i = w0 + (uint32_t)(it * 64 + lane);
+      const bool valid = (uint32_t)(it * 64) < seg && i < e;
+      kk[it] = valid ? in.key[i] : 0u;
+      rc[it] = valid ? in.rec[i] : 0u;
+    }
+  };
+  if (s < e) load_round(s);
+  uint32_t run = 0u;  // thread d: global output position of the next key of digit d
   {
-    uint32_t tot[kPer], sum = 0u;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      tot[k] = coltot[tid * kPer + k];
-      sum += tot[k];
-    }
-    uint32_t x = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) sh[wave] = x;
+    const uint32_t tot = tid < D ? coltot[tid] : 0u;
+    const uint32_t mine = tid < D ? cnt[(size_t)blockIdx.x * D + tid] : 0u;
+    const uint32_t incl = wave_incl_sum(tot);
+    if (lane == 63) sh[wave] = incl;
     __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < wave; ++w) before += sh[w];
-    uint32_t at = before + x - sum;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int d = tid * kPer + k;
-      // one pass over the whole tile id: a digit's first output position is
-      // its tile's start
-      if (tile_start && blockIdx.x == 0 && (uint32_t)d < T) tile_start[d] = at;
-      run[d] = at + cnt[(size_t)blockIdx.x * D + d];
-      at += tot[k];
-    }
+    uint32_t at = incl - tot;
+    for (int w = 0; w < wave; ++w) at += sh[w];
+    // one pass over the whole tile id: a digit's first output position is its
+    // tile's start
+    if (tile_start && blockIdx.x == 0 && tid < D && (uint32_t)tid < T) tile_start[tid] = at;
     if (tile_start && blockIdx.x == 0 && tid == 0) tile_start[T] = ctrl->n_key_eff;
+    run = at + mine;
   }
   for (uint32_t base = s; base < e; base += kRound) {
-    // ---- per wave: ranks of its 512 keys among its own keys of each digit
+    // ---- per wave: ranks of its keys among its own keys of each digit
 #pragma unroll
     for (int j = 0; j < D / 64; ++j) wcnt[wave][lane + 64 * j] = 0u;
     wave_lds_sync();
-    // the round's keys split evenly over the waves, in whole loads of 64
-    const uint32_t n_round = min((uint32_t)kRound, e - base);
-    const uint32_t seg = ((n_round + 255u) / 256u) * 64u;
-    uint32_t kk[kItems], rr[kItems], rc[kItems];
-    // all of the round's loads first: the ranking's wave fences would
-    // otherwise keep each load behind the previous key's LDS update
+    const uint32_t n_round = min((uint32_t)kRound, e - base), seg = segment(base);
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
       const uint32_t i = base + (uint32_t)wave * seg + (uint32_t)(it * 64 + lane);
       const bool valid = (uint32_t)(it * 64) < seg && i < e;
-      kk[it] = valid ? kin[i] : 0u;
-      rc[it] = valid ? in.rec[i] : 0u;
-    }
-#pragma unroll
-    for (int it = 0; it < kItems; ++it) {
-      const uint32_t i = base + (uint32_t)wave * seg + (uint32_t)(it * 64 + lane);
-      const bool valid = (uint32_t)(it * 64) < seg && i < e;
-      const uint32_t k = kk[it];
-      const uint32_t d = (k >> shift) & dmask;
+      const uint32_t d = (kk[it] >> shift) & dmask;
       unsigned long long peers = __ballot(valid);
       for (int bit = 0; bit < dbits; ++bit) {
         const bool on = (d >> bit) & 1u;
@@ -212,75 +189,49 @@ __device__ __forceinline__ void radix_scatter(const Ctrl* __restrict__ ctrl, Sor
       rr[it] = valid ? before + lanemask_lt_popc(peers) : 0xffffffffu;
     }
     __syncthreads();
-    // ---- per digit: the waves' prefixes and the round's count
-    {
-      uint32_t c[kPer], sum = 0u;
+    // ---- thread d: the slots of digit d's keys, wave by wave
+    uint32_t c[NW], sum = 0u;
 #pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int d = tid * kPer + k;
-        const uint32_t c0 = wcnt[0][d], c1 = wcnt[1][d], c2 = wcnt[2][d], c3 = wcnt[3][d];
-        wcnt[0][d] = 0u;
-        wcnt[1][d] = c0;
-        wcnt[2][d] = c0 + c1;
-        wcnt[3][d] = c0 + c1 + c2;
-        c[k] = c0 + c1 + c2 + c3;
-        rcnt[d] = c[k];
-        sum += c[k];
-      }
-      uint32_t x = sum;
+    for (int w = 0; w < NW; ++w) {
+      c[w] = tid < D ? wcnt[w][tid] : 0u;
+      sum += c[w];
+    }
+    const uint32_t incl = wave_incl_sum(sum);
+    if (lane == 63) sh[wave] = incl;
+    __syncthreads();
+    if (tid < D) {
+      uint32_t slot = incl - sum;
+      for (int w = 0; w < wave; ++w) slot += sh[w];
+      first[tid] = run - slot;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+      for (int w = 0; w < NW; ++w) {
+        wcnt[w][tid] = slot;
+        slot += c[w];
       }
-      if (lane == 63) sh[wave] = x;
-      __syncthreads();
-      uint32_t before = 0;
-      for (int w = 0; w < wave; ++w) before += sh[w];
-      uint32_t at = before + x - sum;
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        loc[tid * kPer + k] = at;
-        at += c[k];
-      }
+      run += sum;
     }
     __syncthreads();
-    // slot of each of the thread's keys in the reordered round
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
       if (rr[it] != 0xffffffffu) {
-        const uint32_t d = (kk[it] >> shift) & dmask;
-        rr[it] += loc[d] + wcnt[wave][d];
-        s_key[rr[it]] = kk[it];
+        const uint32_t slot = rr[it] + wcnt[wave][(kk[it] >> shift) & dmask];
+        s_key[slot] = kk[it];
+        s_rec[slot] = rc[it];
       }
     }
     __syncthreads();
-    // keys out, as contiguous runs per digit; each slot's output position is
-    // kept for the record id
-    uint32_t opos[kItems];
+    if (base + kRound < e) load_round(base + kRound);  // in flight while this round is written
+    // keys and record ids out, as contiguous runs per digit
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const uint32_t i = (uint32_t)tid + (uint32_t)(j * kSortThreads);
-      opos[j] = 0xffffffffu;
+      const uint32_t i = (uint32_t)(tid + j * NT);
       if (i < n_round) {
         const uint32_t k = s_key[i];
-        const uint32_t d = (k >> shift) & dmask;
-        opos[j] = run[d] + (i - loc[d]);
-        out.key[opos[j]] = k;
+        const uint32_t o = first[(k >> shift) & dmask] + i;
+        out.key[o] = k;
+        out.rec[o] = s_rec[i];
       }
     }
-    // the record ids through the same slots
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < kItems; ++it)
-      if (rr[it] != 0xffffffffu) s_key[rr[it]] = rc[it];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kItems; ++j)
-      if (opos[j] != 0xffffffffu) out.rec[opos[j]] = s_key[(uint32_t)tid + (uint32_t)(j * kSortThreads)];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) run[tid * kPer + k] += rcnt[tid * kPer + k];
     __syncthreads();
   }
 }
@@ -393,23 +344,32 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter_small(
   }
 }
 
-// Kernels around the scatter body.  The large-input variant (16 keys per
-// thread and round, 256 digits) is held to four workgroups per CU, which its
-// LDS allows; the compiler would otherwise give it more registers and three.
+// Kernels around the scatter body: rounds of 2048 keys while the chunks are
+// about that long (more blocks, less LDS), of 4096 above, and from kLongChunk
+// keys per block on of 8192, whose runs of 32 keys per digit are whole lines.
+// Bound by the scattered writes' address path and the ranking.  Two passes:
+// 33M keys 398 us with rounds of 4096 that moved keys and record ids one after
+// the other, 378 with both together and the next round's loads early, 327 with
+// 8192; 69M keys 553, 532, 464; 25M keys (15 K per block) 165, 151, 151; 11.8M
+// (7 K) 125, 116, 121; 5.7M (3.5 K) 80, 78, 107.  (Rounds of 16384 by 1024
+// threads: 366 and 557.)
+constexpr uint32_t kLongChunk = 12288;
+
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const Ctrl* __restrict__ ctrl, SortSet in,
                                                                 SortSet out,
                                                                 const uint32_t* __restrict__ cnt,
                                                                 const uint32_t* __restrict__ coltot, uint32_t G,
                                                                 int shift, int dbits, uint32_t* __restrict__ tile_start,
                                                                 uint32_t T) {
-  radix_scatter<8>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
+  radix_scatter<8, kSortThreads>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
 }
 
-__global__ __launch_bounds__(kSortThreads, 4) void k_radix_scatter_large(
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void k_radix_scatter_large(
     const Ctrl* __restrict__ ctrl, SortSet in, SortSet out, const uint32_t* __restrict__ cnt,
     const uint32_t* __restrict__ coltot, uint32_t G, int shift, int dbits, uint32_t* __restrict__ tile_start,
     uint32_t T) {
-  radix_scatter<16>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
+  radix_scatter<16, NT>(ctrl, in, out, cnt, coltot, G, shift, dbits, tile_start, T);
 }
 
 // tile_start[t] = first sorted key index whose tile id is >= t (t in [0, T]).
@@ -451,6 +411,7 @@ SortShape sort_shape(int bits, uint32_t key_cap) {
   const uint32_t chunk = S.small ? kSmallChunk : 2048u;
   S.blocks = std::min(std::max((key_cap + chunk - 1u) / chunk, 1u), kSortMaxBlocks);
   const bool one = S.small && (bits <= 11 || (bits == 12 && key_cap <= kWideKeys));
+  S.chunk = key_cap / S.blocks;
   S.passes = one ? 1 : (bits + 7) / 8;
   S.digit_bits = (bits + S.passes - 1) / S.passes;
   S.slots = S.digit_bits <= 8 ? 256u : S.digit_bits <= 10 ? 1024u : S.digit_bits <= 11 ? 2048u : 4096u;
@@ -488,20 +449,22 @@ hipError_t launch_radix_scatter(const Ctrl* ctrl, const uint32_t* const in[2], u
   const SortSet si{const_cast<uint32_t*>(in[0]), const_cast<uint32_t*>(in[1])};
   const SortSet so{out[0], out[1]};
   const uint32_t* coltot = hist + (size_t)S.slots * S.blocks;
-#define UG_SCATTER(kernel) \
-  hipLaunchKernelGGL(kernel, dim3(S.blocks), dim3(kSortThreads), 0, s, ctrl, si, so, hist, coltot, S.blocks, shift, pb, tile_start, num_tiles)
+#define UG_SCATTER(kernel, NT) \
+  hipLaunchKernelGGL(kernel, dim3(S.blocks), dim3(NT), 0, s, ctrl, si, so, hist, coltot, S.blocks, shift, pb, tile_start, num_tiles)
   if (S.small && S.slots == 4096u)
-    UG_SCATTER(k_radix_scatter_small<4096>);
+    UG_SCATTER(k_radix_scatter_small<4096>, kSortThreads);
   else if (S.small && S.slots == 2048u)
-    UG_SCATTER(k_radix_scatter_small<2048>);
+    UG_SCATTER(k_radix_scatter_small<2048>, kSortThreads);
   else if (S.small && S.slots == 1024u)
-    UG_SCATTER(k_radix_scatter_small<1024>);
+    UG_SCATTER(k_radix_scatter_small<1024>, kSortThreads);
   else if (S.small)
-    UG_SCATTER(k_radix_scatter_small<256>);
+    UG_SCATTER(k_radix_scatter_small<256>, kSortThreads);
+  else if (S.chunk >= kLongChunk)
+    UG_SCATTER(k_radix_scatter_large<512>, 512);
   else if (S.blocks >= kSortMaxBlocks)
-    UG_SCATTER(k_radix_scatter_large);
+    UG_SCATTER(k_radix_scatter_large<256>, 256);
   else
-    UG_SCATTER(k_radix_scatter);
+    UG_SCATTER(k_radix_scatter, kSortThreads);
 #undef UG_SCATTER
   return hipGetLastError();
 }
