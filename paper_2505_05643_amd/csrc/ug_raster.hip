@@ -14,7 +14,11 @@
 // sums its Gaussians in the same order whatever the launch shape), keeps
 // those whose mask touches its band in a wave-private LDS list and walks the
 // list: per pixel-record pair two FMAs give the exponent, one compare
-// applies the cut-off and one v_exp_f32 gives the weight.
+// applies the cut-off and one v_exp_f32 gives the weight.  The masks of eight
+// list entries travel in one scalar word, so an entry costs its LDS reads and
+// its evaluated sub-blocks: with a mask read back from LDS and broadcast per
+// entry the kernel issued 12% more (33M keys on 32x16 tiles 1254 us, 1163 so;
+// 25M on 16x16 799, 723; 11.8M needles 667, 592).  Bound by its VALU issue.
 //
 // Adjoint: a block takes keys of one tile, its waves up to 64 each at a time,
 // and expands them into (key, four-column strip) items; lanes = items, each
@@ -159,8 +163,7 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
     }
     if (base + SPLIT * BG < e) fetch(base + SPLIT * BG);
     wave_lds_sync();
-    auto eval_rec = [&](const float4& a, const float2& rb) {
-      const uint32_t m = __builtin_amdgcn_readfirstlane(__float_as_uint(a.w));
+    auto eval_rec = [&](const float4& a, const float2& rb, uint32_t m) {
       const float erow = rb.x, B = rb.y;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
@@ -176,15 +179,44 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
         }
       }
     };
-    // two records per iteration so their LDS reads overlap
-    uint32_t j = 0;
-    for (; j + 1 < n; j += 2) {
-      const float4 a0 = cA[wv][j], a1 = cA[wv][j + 1];
-      const float2 r0 = cR[wv][j][lrow], r1 = cR[wv][j + 1][lrow];
-      eval_rec(a0, r0);
-      eval_rec(a1, r1);
+    if constexpr (K == 1) {  // an entry's one sub-block is always evaluated
+      uint32_t j = 0;
+      for (; j + 1 < n; j += 2) {
+        const float4 a0 = cA[wv][j], a1 = cA[wv][j + 1];
+        const float2 r0 = cR[wv][j][lrow], r1 = cR[wv][j + 1][lrow];
+        asm volatile("" ::"v"(a0.w), "v"(a1.w));  // 16-byte reads (see below)
+        eval_rec(a0, r0, 1u);
+        eval_rec(a1, r1, 1u);
+      }
+      if (j < n) eval_rec(cA[wv][j], cR[wv][j][lrow], 1u);
+      n = 0;
     }
-    if (j < n) eval_rec(cA[wv][j], cR[wv][j][lrow]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      if ((uint32_t)(64 * q) >= n) break;  // uniform
+      // the masks of eight neighbouring records in one word (K <= 4 bits each;
+      // zero behind the list's end), in every lane of the eight
+      const uint32_t nq = min(n - (uint32_t)(64 * q), 64u);
+      uint32_t mw = (uint32_t)lane < nq ? __float_as_uint(cA[wv][64 * q + lane].w) << (4 * (lane & 7)) : 0u;
+      mw |= (uint32_t)__builtin_amdgcn_mov_dpp((int)mw, 0xb1, 0xf, 0xf, true);   // lanes 1 0 3 2
+      mw |= (uint32_t)__builtin_amdgcn_mov_dpp((int)mw, 0x4e, 0xf, 0xf, true);   // lanes 2 3 0 1
+      mw |= (uint32_t)__builtin_amdgcn_mov_dpp((int)mw, 0x141, 0xf, 0xf, true);  // mirrored in the eight
+      for (uint32_t j = 0; j < nq; j += 8) {
+        const uint32_t m8 = (uint32_t)__builtin_amdgcn_readlane((int)mw, (int)j);
+        const float4* ca = &cA[wv][64 * q + j];
+        const float2(*cr)[kSubBlock] = &cR[wv][64 * q + j];
+        // two records at a time so that their LDS reads overlap
+#pragma unroll
+        for (uint32_t i = 0; i < 8; i += 2) {
+          if (j + i >= nq) break;  // uniform
+          const float4 a0 = ca[i], a1 = ca[i + 1];
+          const float2 r0 = cr[i][lrow], r1 = cr[i + 1][lrow];
+          asm volatile("" ::"v"(a0.w), "v"(a1.w));  // 16-byte reads: 12-byte ones hold the LDS longer
+          eval_rec(a0, r0, m8 >> (4 * i));
+          eval_rec(a1, r1, m8 >> (4 * i + 4));
+        }
+      }
+    }
     wave_lds_sync();
   }
   if constexpr (SPLIT == 2) {
