@@ -28,14 +28,11 @@
 #include <algorithm>
 
 #include "ug_kernels.h"
+#include "ug_quality_tile.h"
 
 namespace ug {
 
-constexpr int kQRad = 5, kQWin = 2 * kQRad + 1;
-constexpr int kQOut = 64 - 2 * kQRad;  // output columns per strip
-constexpr int kQRows = 4;              // rows per step
-constexpr int kQMom = 4;               // x, y, x^2 + y^2, x y
-constexpr int kQPitch = 68;            // doubles per row of column sums in LDS (the last group reads up to 66)
+constexpr int kQMom = 4;  // x, y, x^2 + y^2, x y
 
 // Strips and row chunks of a plane (at least one: a plane too small for a
 // window still has its squared differences).
@@ -43,11 +40,6 @@ __device__ __host__ __forceinline__ int q_strips(int W) { return W - 2 * kQRad >
 __device__ __host__ __forceinline__ int q_chunks(int H, int rows) {
   return H - 2 * kQRad > rows ? (H - 2 * kQRad + rows - 1) / rows : 1;
 }
-
-// LDS place of a column: the pairs of columns 32 and up swap with their
-// neighbours, so that lanes eight groups of four apart read 16 bytes from
-// different banks.
-__device__ __forceinline__ int q_pair(int pair) { return pair ^ ((pair >> 4) & 1); }
 
 __global__ __launch_bounds__(64, 3) void k_quality_strip(const PlaneInt* __restrict__ pint, int chunk_rows,
                                                          uint32_t max_strips, const float* __restrict__ img,
@@ -82,9 +74,10 @@ __global__ __launch_bounds__(64, 3) void k_quality_strip(const PlaneInt* __restr
   for (int f = 0; f < kQMom; ++f)
 #pragma unroll
     for (int i = 0; i < kQWin - 1; ++i) acc[f][i] = 0.0;
+  static_assert(kQCols == 64 && kQRows * (64 / kQRows) == 64, "lanes = columns, then (row, group) pairs");
   double s_ssim = 0.0, s_se = 0.0;
   const int place = 2 * q_pair(lane >> 1) + (lane & 1);
-  const int orow = lane >> 4, og = lane & 15;  // the lane's outputs: row, group of four columns
+  const int orow = lane >> 4, og = lane & 15;  // the lane's outputs: row, group of four columns (the last two groups have none)
   load_rows(ya);
   for (int y0 = ya; y0 < yb; y0 += kQRows) {
 #pragma unroll
@@ -104,17 +97,17 @@ __global__ __launch_bounds__(64, 3) void k_quality_strip(const PlaneInt* __restr
     load_rows(y0 + kQRows);
     if (y0 + kQRows - 1 - ya < 2 * kQRad) continue;  // uniform: no window is complete yet
     wave_lds_sync();
-    double m[kQMom][4];
+    double m[kQMom][kQPer];
 #pragma unroll
     for (int f = 0; f < kQMom; ++f) {
 #pragma unroll
-      for (int j = 0; j < (kQWin + 3) / 2; ++j) {
-        const double2 t = s_h[orow][f][q_pair(2 * og + j)];
+      for (int j = 0; j < kQPairs; ++j) {
+        const double2 t = s_h[orow][f][q_read_pair(og, j)];
         const double v[2] = {t.x, t.y};
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
-          for (int o = 0; o < 4; ++o) {
+          for (int o = 0; o < kQPer; ++o) {
             const int tap = 2 * j + k - o;
             if (tap == 0) m[f][o] = q.taps[0] * v[k];
             else if (tap > 0 && tap < kQWin) m[f][o] = fma(q.taps[tap], v[k], m[f][o]);
@@ -123,15 +116,15 @@ __global__ __launch_bounds__(64, 3) void k_quality_strip(const PlaneInt* __restr
       // computed here and not behind the bounds test of the output they serve
       // (which keeps all the sums read alive until then)
 #pragma unroll
-      for (int o = 0; o < 4; ++o) asm volatile("" : "+v"(m[f][o]));
+      for (int o = 0; o < kQPer; ++o) asm volatile("" : "+v"(m[f][o]));
     }
     const int y = y0 + orow;  // the windows' last row
     const bool row_ok = y - ya >= 2 * kQRad && y < yb;
 #pragma unroll
-    for (int o = 0; o < 4; ++o) {
+    for (int o = 0; o < kQPer; ++o) {
       const double t = m[0][o] * m[1][o], e = fma(m[0][o], m[0][o], m[1][o] * m[1][o]);
       const double s = (fma(2.0, t, q.c1) * fma(2.0, m[3][o] - t, q.c2)) / ((e + q.c1) * ((m[2][o] - e) + q.c2));
-      const int c = 4 * og + o;
+      const int c = kQPer * og + o;
       s_ssim += row_ok && c < kQOut && strip * kQOut + c + 2 * kQRad < PI.W ? s : 0.0;
     }
     wave_lds_sync();  // the next rows take the sums' place
