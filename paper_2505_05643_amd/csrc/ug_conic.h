@@ -339,10 +339,14 @@ __device__ __forceinline__ bool band_cols(const BandPrep& b, int ya, int yb, int
 // name a sub-block too many, whose pairs add exact zeros; it must not miss
 // one).  At row offset dv the ellipse spans -(t12 / t11) dv -/+
 // sqrt(d - t22^2 dv^2) / t11, with its right end at dvr and its left at -dvr.
+// The plane's own columns relative to the centre are exact in single precision
+// up to kFarColumns pixels from it; a record farther away (a plane that is
+// tiny against the Gaussian) takes every sub-block of its tiles.
+constexpr int kFarColumns = 1 << 23;
 struct BandMask {
   float t22, a, i11, d, dvr, fu, fv;
   int ub, vb;
-  bool all;  // no cut-off, or a constant that is not finite
+  bool all;  // no cut-off, a constant that is not finite, or a far centre
 };
 
 __device__ __forceinline__ bool band_mask_prep(const RecAcc& ra, int ub, int vb, BandMask& b) {
@@ -357,7 +361,8 @@ __device__ __forceinline__ bool band_mask_prep(const RecAcc& ra, int ub, int vb,
   b.fv = ra.fv;
   b.ub = ub;
   b.vb = vb;
-  b.all = !(d < 1e30f && fabsf(b.a) < 1e12f && fabsf(b.dvr) < 1e12f && b.i11 < 1e12f && ra.t22 < 1e12f);
+  b.all = !(d < 1e30f && fabsf(b.a) < 1e12f && fabsf(b.dvr) < 1e12f && b.i11 < 1e12f && ra.t22 < 1e12f &&
+            ub >= -kFarColumns && ub <= kFarColumns);
   return d >= 0.f;
 }
 
