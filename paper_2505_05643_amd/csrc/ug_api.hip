@@ -16,9 +16,7 @@ using namespace ug;
 // the loader with the code object and held until the process ends.  Host code
 // uses only the address hipGetSymbolAddress returns for the current device
 // (the array's name on the host is a stand-in, not a device address).
-// The 64 KiB beyond the documented size hold what the size check leaves out
-// (Layout::checked).
-static __device__ __align__(256) unsigned char scratch[UG_NOALLOC_WORKSPACE_BYTES + (64u << 10)];
+static __device__ __align__(256) unsigned char scratch[UG_NOALLOC_WORKSPACE_BYTES];
 
 namespace {
 
@@ -31,9 +29,6 @@ struct Layout {
   size_t tile_start, dsave, hist;
   size_t emitted, key0, key1, rec0, rec1, run_koff, partial;
   size_t loss_part;
-  // what the no-allocation forward's limit is held against: the total, less
-  // what run_koff takes beyond one word per key
-  size_t checked;
   size_t total;
 };
 
@@ -79,7 +74,6 @@ void compute_layout(ug_plan* pl) {
   };
   const size_t n = (size_t)pl->n, P = (size_t)pl->p;
   const size_t T = pl->num_tiles, R = pl->rec_cap, K = pl->key_cap;
-  const size_t tpx = (size_t)pl->prm.tile_w * pl->prm.tile_h;
   L.ctrl = take(sizeof(Ctrl));
   L.pconst = take(P * sizeof(PlaneConst));
   L.pcull = take(P * sizeof(PlaneCull));
@@ -101,22 +95,19 @@ void compute_layout(ug_plan* pl) {
   L.key1 = take(K * 4);
   L.rec0 = take(K * 4);
   L.rec1 = take(K * 4);
-  const size_t runs = (size_t)record_blocks(pl->rec_cap) * kRuns;  // more than K only in small plans
-  L.run_koff = take(std::max(runs, K) * 4);
-  const size_t beyond = runs > K ? align_up(runs * 4) - align_up(K ? K * 4 : 1) : 0;
+  // The runs' key offsets: at most 16,384 words in the place of a sixth word
+  // per key (a plan keeps its 56 bytes per key), or, where a plan has fewer
+  // keys than runs, in that of the acceptance bits, which are dead once the
+  // cull has written its pairs.  They fit there: kRuns words per 256 records,
+  // one bit per (Gaussian, plane).
+  L.run_koff = take(K * 4);
+  if ((size_t)record_blocks(pl->rec_cap) * kRuns > K) L.run_koff = L.accbits;
+  static_assert(kRuns * 4 * 8 <= 256, "run offsets fit the acceptance bits");
   L.partial = take(K * 32);
   // the sort's histograms are dead before the adjoint writes its partials
   const size_t hist = pl->sort.hist_words() * 4;
-  const bool apart = hist > K * 32;  // a few keys only
-  L.hist = apart ? take(hist) : L.partial;
+  L.hist = hist > K * 32 ? take(hist) : L.partial;  // apart with a few keys only
   L.loss_part = take(T * 4);
-  // What the no-allocation limit counts, so that it refuses what it always
-  // has: 8 bytes per tile pixel, the loss sums by 1024 pixels, and the
-  // histograms apart, by blocks of 2048 keys and at most 1024 digits.
-  const size_t g = std::min<size_t>(std::max<size_t>((K + 2047) / 2048, 1), 2048);
-  const size_t slots = pl->bits > 8 && pl->bits <= 10 && g <= 256 ? 1024 : 256;
-  L.checked = o - beyond - (apart ? align_up(hist) : 0) + align_up(slots * (g + 1) * 4) + align_up(T * tpx * 8) +
-              align_up((T * tpx + 1023) / 1024 * 4) - align_up(T * 4);
   L.total = o;
 }
 
@@ -461,8 +452,7 @@ int ug_render_planes(const ug_plan* plan, const ug_gaussians* g, const ug_planes
 int ug_render_planes_noalloc(const ug_plan* plan, const ug_gaussians* g, const ug_planes* planes, float* image,
                              void* stream) {
   if (!plan) return UG_ERR_INVALID_ARG;
-  if (plan->lay.checked > (size_t)UG_NOALLOC_WORKSPACE_BYTES || plan->lay.total > sizeof(scratch))
-    return UG_ERR_SCRATCH_SIZE;
+  if (plan->lay.total > sizeof(scratch)) return UG_ERR_SCRATCH_SIZE;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return UG_ERR_HIP;
   if (dev != plan->device) return UG_ERR_INVALID_ARG;  // the plan's tables live on its own device
