@@ -147,7 +147,8 @@ __device__ __forceinline__ GaussRaw load_gauss_raw(const ug_gaussians& g, int i)
   return r;
 }
 
-// exact: divisions for the reciprocals (the cull's decisions rest on them).
+// exact: divisions for the reciprocals (the float cull's and the box support's
+// decisions rest on them).
 template <typename T>
 __device__ __forceinline__ void gauss_setup(const GaussRaw& r, T beta, GaussT<T>& G, bool exact = false) {
   bool fin = true;
@@ -496,7 +497,8 @@ __device__ __forceinline__ bool box_pixels(double centre, double half, int32_t s
 __device__ __forceinline__ bool make_box_record(const GaussIn& G, const PlaneRec& Q, const Conic& k, double chi2,
                                                 Footprint& f) {
   const PlaneT<double>& P = Q.pose;
-  // exact divisions: a pixel centre on the box's edge decides here
+  // exact divisions, here and in the Gaussian's factor (load_gauss): a pixel
+  // centre on the box's edge decides here
   int ulo, uhi, vlo, vhi;
   if (!box_pixels(k.m1 / P.sx + Q.cu, sqrt(chi2 * k.S11) / P.sx, Q.W, ulo, uhi)) return false;
   if (!box_pixels(k.m2 / P.sy + Q.cv, sqrt(chi2 * k.S22) / P.sy, Q.H, vlo, vhi)) return false;

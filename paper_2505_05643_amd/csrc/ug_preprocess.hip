@@ -644,13 +644,16 @@ __device__ __forceinline__ PlaneRec plane_rec_from_lds(const double* d, const in
 // roots, plane constants 24 doubles apart and every lane storing its own
 // slot; 567 without the exact forms, 548 without the bank conflicts too, 446
 // with the slots stored through LDS (2.5 TB/s written).
-template <bool STAGE>
+// BOX: the paper-literal box support (a template argument, so that its exact
+// divisions take none of the other records' registers, which are at the limit).
+// chi2 is passed as the double it is used as, in scalar registers.
+template <bool STAGE, bool BOX>
 __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_gaussians g, const PlaneConst* __restrict__ pc,
                                                               const PlaneInt* __restrict__ pint, RenderParams rp,
                                                               const uint2* __restrict__ rec_pair,
                                                               Rec* __restrict__ recs, uint32_t* __restrict__ rec_nkey,
                                                               uint32_t* __restrict__ blk_tot,
-                                                              Ctrl* __restrict__ ctrl) {
+                                                              Ctrl* __restrict__ ctrl, double chi2_arg) {
   constexpr uint32_t NT = STAGE ? 512u : 256u;
   extern __shared__ double s_planes[];  // STAGE: rp.p x kPlaneDoubles, then rp.p sizes
   constexpr int kSlotPitch = 5;  // float4 per slot in LDS: four and one of padding
@@ -667,7 +670,6 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
   }
   if (threadIdx.x == 0) s_tot = s_counted = 0;
   __syncthreads();
-  const double chi2 = (double)rp.chi2;
   const bool rows = rp.by_rows != 0;  // the records carry their row spans
   uint32_t mine = 0, counted = 0;
   const uint32_t r_end = min(r_begin + rpb, nrec);
@@ -687,7 +689,9 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
         Footprint f;
         const uint2 gp = rec_pair[r];
         GaussIn G;
-        load_gauss(g, (int)gp.x, (double)rp.beta, G);
+        load_gauss(g, (int)gp.x, (double)rp.beta, G, BOX);
+        double chi2 = chi2_arg;
+        asm volatile("" : "+s"(chi2));  // its products are not kept from record to record in vector registers
         const PlaneRec Q = STAGE ? plane_rec_from_lds(s_planes + kPlaneDoubles * gp.y, s_wh[gp.y])
                                  : plane_rec(pc[gp.y], pint[gp.y]);
         Conic k;
@@ -695,8 +699,8 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
         conic_full(G, Q.pose, k);
         // Box support: the FP64 Phase-1 decision is final (a pair the
         // conservative float cull let through would otherwise fill its box).
-        const bool ok = rp.box_support ? (meets && make_box_record(G, Q, k, chi2, f))
-                                       : make_footprint(G, Q, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
+        const bool ok = BOX ? (meets && make_box_record(G, Q, k, chi2, f))
+                            : make_footprint(G, Q, k, chi2, rp.box_mode, rows, rp.tile_w, rp.tile_h, f);
         if (!ok) {
           // the plane cuts the ellipsoid (or box) outside the image: a record with no keys
           f.keys = f.counted = 0;
@@ -1315,14 +1319,18 @@ hipError_t launch_cull_write(const RenderParams& rp, const uint32_t* cnt_rec, co
 hipError_t launch_record(const ug_gaussians& g, const PlaneConst* pc, const PlaneInt* pint, const RenderParams& rp,
                          const uint2* rec_pair, Rec* recs, uint32_t* rec_nkey, uint32_t* blk_tot,
                          Ctrl* ctrl, hipStream_t s) {
-  if (rp.p <= kStagePlanes) {
-    const size_t lds = (size_t)rp.p * kPlaneLds;
-    hipLaunchKernelGGL(k_record<true>, dim3(record_blocks(rp.rec_cap)), dim3(512), lds, s, g, pc, pint, rp,
-                       rec_pair, recs, rec_nkey, blk_tot, ctrl);
-  } else {
-    hipLaunchKernelGGL(k_record<false>, dim3(record_blocks(rp.rec_cap)), dim3(256), 0, s, g, pc, pint, rp,
-                       rec_pair, recs, rec_nkey, blk_tot, ctrl);
-  }
+  const bool stage = rp.p <= kStagePlanes;
+  const size_t lds = stage ? (size_t)rp.p * kPlaneLds : 0;
+  const dim3 grid(record_blocks(rp.rec_cap)), block(stage ? 512 : 256);
+#define UG_RECORD(STAGE, BOX)                                                                                      \
+  if (stage == STAGE && (rp.box_support != 0) == BOX)                                                              \
+    hipLaunchKernelGGL((k_record<STAGE, BOX>), grid, block, lds, s, g, pc, pint, rp, rec_pair, recs, rec_nkey,     \
+                       blk_tot, ctrl, (double)rp.chi2);
+  UG_RECORD(true, false)
+  UG_RECORD(false, false)
+  UG_RECORD(true, true)
+  UG_RECORD(false, true)
+#undef UG_RECORD
   return hipGetLastError();
 }
 
