@@ -406,7 +406,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
   __shared__ float4 kpB[kThreads];                   // du0, dv0, d, c
   __shared__ uint32_t bucket[TH + 1];           // items per row count
   __shared__ uint32_t more[NW];                 // whether the wave has keys left after the pass
-  __shared__ float wave_sq[NW];                 // squared differences of the waves' pixels
+  __shared__ float quarter_sq[4];               // squared differences of every fourth 64 pixels
   __shared__ uint32_t grab;                     // next group of 64 items to evaluate
   __shared__ uint32_t sorted[NW * kSlotsWave];   // slot | wave << 8 | key << 10 | strip << 18 | first row << 21 | rows << 26
   // the items' sums; before a wave's items are evaluated its part holds what
@@ -482,7 +482,13 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
     }
     if (n) load_recs();
     float2* g2 = reinterpret_cast<float2*>(gt);
-    float sq = 0.f;
+    // The squared differences are added by quarters (every fourth 64 pixels of
+    // the tile: one wave's of four), then over the lanes, then the quarters in
+    // order, whatever the number of waves: the loss does not depend on it.
+    constexpr int kSums = 4 / NW;
+    float sq[kSums];
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) sq[q] = 0.f;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int j = (int)threadIdx.x + kThreads * i;
@@ -490,7 +496,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
       if (loss_part) {  // uniform
         const float d = im[i] - dI;
         dI = scale * d;
-        sq = fmaf(d, d, sq);
+        sq[i % kSums] = fmaf(d, d, sq[i % kSums]);
       }
       const float gam = dI / dt[i];
       if (j < TW * TH) g2[j / TW * (2 * kRow) + j % TW] = make_float2(gam, gam * im[i]);
@@ -498,18 +504,16 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
     if (threadIdx.x < kRow) gt[TH * kRow + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (loss) {  // uniform
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-      if (lane == 0) wave_sq[wave] = sq;
+      for (int q = 0; q < kSums; ++q) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq[q] += __shfl_xor(sq[q], o, 64);
+        if (lane == 0) quarter_sq[wave * kSums + q] = sq[q];
+      }
     }
   }
   __syncthreads();  // gt, bucket and grab are ready
   if (loss) {  // uniform
-    if (threadIdx.x == 0) {
-      float sq = wave_sq[0];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) sq += wave_sq[w];
-      loss_part[t] = sq;
-    }
+    if (threadIdx.x == 0) loss_part[t] = ((quarter_sq[0] + quarter_sq[1]) + quarter_sq[2]) + quarter_sq[3];
     if (n == 0) return;
   }
   for (;;) {
