@@ -265,9 +265,18 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
 }
 
 // ---------------------------------------------------------------- backward
-// nsplit blocks of NW waves per tile; each wave has a contiguous share of
-// the tile's keys and takes up to 64 of them per pass.  The block forms the
-// tile's per-pixel inputs, gamma = dL/dc_hat / D and gamma c_hat, in LDS (every
+// nsplit blocks of NW waves per tile for the tile's first keys, up to twice
+// the mean of all tiles, and blocks for the rest of the tiles that have more:
+// the sorted keys are cut into chunks, and each of those blocks looks at its
+// chunks' first keys (whose words name their tiles) for chunks behind a tile's
+// dealt keys.  With nsplit blocks for every tile, however many keys it has, a
+// dense tile's walk alone set the time: half of 100,000 Gaussians in a
+// fiftieth of the volume, 64 planes of 256 x 256, 6.88 ms per step, 3.37 so;
+// shells and a core in 160 x 160 planes (50,000 on 16 planes, one wave per
+// tile) 217 and 160 us.  Where no tile has more the blocks for the rest cost
+// nothing that was measured.  Each wave has a contiguous
+// share of its block's keys and takes up to 64 of them per pass.  The block
+// forms the tile's per-pixel inputs, gamma = dL/dc_hat / D and gamma c_hat, in LDS (every
 // row the evaluation reads comes from there); the loss gradient takes the
 // float operations of the separate kernel.  A kernel of its own that wrote
 // them tile by tile took 61 us and this one 14 us less at 16.8M pixels (step
@@ -386,14 +395,17 @@ __device__ __noinline__ uint32_t find_emitted(const uint32_t* __restrict__ emitt
   return a;
 }
 
+// The block's keys: [lo, hi) of the keys of tile t, `share` to a wave; with
+// loss also the tile's sum of squared differences (loss_part also tells that
+// `second` is the target).
 template <int TW, int TH, int NW>
-__global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_accum_bwd(
+__device__ __forceinline__ void accum_bwd_keys(
     const uint32_t* __restrict__ tile_org, const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ skey,
     const uint32_t* __restrict__ srec, const uint32_t* __restrict__ emitted, const uint32_t* __restrict__ rec_koff,
     const uint32_t* __restrict__ run_koff, const Rec* __restrict__ recs, const PlaneInt* __restrict__ pint,
     const uint32_t* __restrict__ tile_plane, const float* __restrict__ image, const float* __restrict__ second,
     const float* __restrict__ dsave, float scale, float* __restrict__ loss_part, float4* __restrict__ partial, int kcut,
-    int tile_bits, uint32_t num_tiles, uint32_t nsplit) {
+    int tile_bits, uint32_t t, uint32_t lo, uint32_t hi, uint32_t share, bool loss) {
   constexpr int kMaskShift = key_mask_shift(TW, TH);
   constexpr int kSlotsWave = slots_wave(TW, TH), kGroups = (kSlotsWave + 63) / 64;
   constexpr int kMaxStrips = TW / kStrip, kThreads = 64 * NW;
@@ -422,24 +434,17 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
   };
   __shared__ Slots slot[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // all tiles' first parts, then their second ...: the blocks left without
-  // keys come last, instead of every few (which left the same CUs idle)
-  const uint32_t part = blockIdx.x / num_tiles, t = xcd_remap(blockIdx.x - part * num_tiles, num_tiles);
+  const float ln2 = (float)kLn2;
+  const bool cut = kcut != kNoCutBits;
+  const uint32_t tmask = (1u << tile_bits) - 1u;
   const uint32_t s = tile_start[t], n = tile_start[t + 1] - s;
-  // the waves' shares of the tile's keys, at least 32 each (fewer, fuller
-  // waves where a tile has few)
-  const uint32_t share = max((n + NW * nsplit - 1u) / (NW * nsplit), 32u);
-  const bool loss = loss_part && part == 0;
-  if (part * NW * share >= n && !loss) return;  // uniform: no keys left for this block
   if (threadIdx.x <= TH) bucket[threadIdx.x] = 0u;
   if (threadIdx.x == 0) grab = 0u;
   const PlaneInt& PI = pint[tile_plane[t]];
   const uint32_t org = tile_org[t];  // x0 | y0 << 16
   const int x0 = (int)(org & 0xffffu), y0 = (int)(org >> 16);
-  const float ln2 = (float)kLn2;
-  const bool cut = kcut != kNoCutBits;
-  uint32_t k = min((part * NW + (uint32_t)wave) * share, n);  // the wave's next key
-  const uint32_t ke = min(k + share, n);                      // its last
+  uint32_t k = min(lo + (uint32_t)wave * share, hi);  // the wave's next key
+  const uint32_t ke = min(k + share, hi);             // its last
   // A pass's keys are loaded during the pass before it, and their records (a
   // random 64-byte gather per key) before that pass's evaluation.  Lanes past
   // the wave's keys read the tile's last key and are masked off.
@@ -522,7 +527,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
     const uint32_t last_index = (1u << (kMaskShift - tile_bits)) - 1u;
     const uint32_t index = (kw >> tile_bits) & last_index;
     uint32_t dst = run_koff[run] + koff + index;
-    if (index == last_index) dst = find_emitted(emitted, rec_koff, rid, dst - index, t, (1u << tile_bits) - 1u);
+    if (index == last_index) dst = find_emitted(emitted, rec_koff, rid, dst - index, t, tmask);
     const uint32_t left = ke - k;
     // at most 64 keys per pass, the last two passes alike
     const uint32_t want = left > 128u ? 64u : (left > 64u ? (left + 1u) / 2u : left);
@@ -691,6 +696,54 @@ __global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_ac
   }
 }
 
+template <int TW, int TH, int NW>
+__global__ __launch_bounds__(64 * NW, NW > 1 && TW * TH > 512 ? 3 : 4) void k_accum_bwd(
+    const uint32_t* __restrict__ tile_org, const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ skey,
+    const uint32_t* __restrict__ srec, const uint32_t* __restrict__ emitted, const uint32_t* __restrict__ rec_koff,
+    const uint32_t* __restrict__ run_koff, const Rec* __restrict__ recs, const PlaneInt* __restrict__ pint,
+    const uint32_t* __restrict__ tile_plane, const float* __restrict__ image, const float* __restrict__ second,
+    const float* __restrict__ dsave, float scale, float* __restrict__ loss_part, float4* __restrict__ partial, int kcut,
+    int tile_bits, uint32_t num_tiles, uint32_t nsplit, uint32_t min_deal, float twice, uint32_t chunk) {
+  auto keys = [&](uint32_t t, uint32_t lo, uint32_t hi, uint32_t share, bool loss) {
+    accum_bwd_keys<TW, TH, NW>(tile_org, tile_start, skey, srec, emitted, rec_koff, run_koff, recs, pint, tile_plane,
+                               image, second, dsave, scale, loss_part, partial, kcut, tile_bits, t, lo, hi, share,
+                               loss);
+  };
+  const uint32_t n_all = tile_start[num_tiles];
+  // keys of a tile that its own blocks take
+  const uint32_t deal = max(min_deal, (uint32_t)fminf((float)n_all * twice, 4e9f));
+  if (blockIdx.x < num_tiles * nsplit) {
+    // all tiles' first parts, then their second ...: the blocks left without
+    // keys come last, instead of every few (which left the same CUs idle)
+    const uint32_t part = blockIdx.x / num_tiles, t = xcd_remap(blockIdx.x - part * num_tiles, num_tiles);
+    const uint32_t dealt = min(tile_start[t + 1] - tile_start[t], deal);
+    // at least 32 each (fewer, fuller waves where a tile has few)
+    const uint32_t share = max((dealt + NW * nsplit - 1u) / (NW * nsplit), 32u);
+    const uint32_t lo = min(part * NW * share, dealt), hi = min(lo + NW * share, dealt);
+    const bool loss = loss_part && part == 0;
+    if (lo < hi || loss) keys(t, lo, hi, share, loss);  // uniform
+    return;
+  }
+  // The rest: 64 chunks at a time, a lane each (every wave of the block the
+  // same ones), neighbouring chunks in different blocks.  A chunk holds keys
+  // behind a tile's dealt ones only if it starts in that tile (chunk <= deal).
+  const uint32_t nrest = gridDim.x - num_tiles * nsplit, lane = threadIdx.x & 63u;
+  for (uint32_t c = blockIdx.x - num_tiles * nsplit; (uint64_t)c * chunk < n_all; c += 64u * nrest) {
+    const uint64_t at = (uint64_t)(c + lane * nrest) * chunk;
+    const bool in = at < n_all;
+    const uint32_t pos = in ? (uint32_t)at : 0u, tile = skey[pos] & ((1u << tile_bits) - 1u);
+    const uint32_t ts = tile_start[tile], te = tile_start[tile + 1];
+    const uint32_t a = max(pos - ts, deal), z = pos - ts + min(chunk, te - pos);
+    for (unsigned long long todo = __ballot(in && a < z); todo; todo &= todo - 1ull) {
+      const int l = __builtin_ctzll(todo);
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)a, l);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)z, l);
+      keys((uint32_t)__builtin_amdgcn_readlane((int)tile, l), lo, hi, max((hi - lo + NW - 1u) / NW, 32u), false);
+      wave_lds_sync();  // as between two passes
+    }
+  }
+}
+
 // ---------------------------------------------------------------- dispatch
 template <int TW, int TH, int SPLIT>
 static hipError_t fwd_bg(int bg, dim3 grid, hipStream_t s, const PlaneInt* pint, const uint32_t* tp,
@@ -757,6 +810,18 @@ hipError_t launch_accum_fwd(int tile_w, int tile_h, int lds_batch, int split, co
 // block per tile 41 us, eight 13; 600 tiles of 150: one 11, two 15).
 constexpr uint32_t kBwdBlockKeys = 1024, kBwdMinBlocks = 1024, kBwdMinKeys = 128;
 
+// A tile's own blocks take kBwdDealKeys keys each (a quarter of that with one
+// wave) or twice the mean of all tiles, if that is more; the keys behind go to
+// up to kBwdRestWaves waves in chunks of about a 1,024th of the capacity,
+// kBwdMinChunk to kBwdDealKeys keys (kBwdMinChunk with one wave).  Fewer dealt
+// keys share better, but cut the even scenes' blocks up, whose fullest tiles
+// hold 1.3 times the mean.  The kernel's time, half of these, these, twice
+// these, then 1.3 and 4 times the mean: a core of 500,000 in 256 x 256 planes
+// (32x16 tiles) 639, 631, 720, 629, 712 us; shells and a core, 80 planes of
+// 160 x 160 (16x16) 186, 189, 215, 191, 192; the same on 16 planes (one wave)
+// 49, 51, 72, 48, 87.
+constexpr uint32_t kBwdDealKeys = 1024, kBwdMinChunk = 256, kBwdRestWaves = 4096;
+
 // One wave per block where a tile has few keys: 40 KB of LDS let four blocks
 // of four waves on a CU, and with a wave's worth of keys in a tile their time
 // is the block's start-up, which a block of one wave (10 to 18 KB) repeats
@@ -783,12 +848,18 @@ hipError_t launch_accum_bwd(int tile_w, int tile_h, int tile_bits, const uint32_
   const bool one = num_tiles >= kBwdOneTiles && (uint64_t)avg * avg * px < kBwdOneKeys * kBwdOneKeys;
   const uint32_t fill = std::min((kBwdMinBlocks + num_tiles - 1u) / num_tiles, avg / kBwdMinKeys);
   const uint32_t nsplit = std::max(std::max(avg / kBwdBlockKeys, fill), 1u);
-  const dim3 grid(num_tiles * nsplit);
+  const uint32_t waves = one ? 1u : 4u;
+  const uint32_t min_deal = nsplit * (kBwdDealKeys / 4u * waves);
+  const uint32_t chunk = one ? kBwdMinChunk : std::min(std::max(key_cap / kBwdMinBlocks, kBwdMinChunk), kBwdDealKeys);
+  const uint32_t nrest =
+      key_cap > min_deal ? std::min(key_cap / chunk + 1u, kBwdRestWaves / waves) : 0u;  // else no tile has more
+  const float twice = 2.f / (float)num_tiles;
+  const dim3 grid(num_tiles * nsplit + nrest);
   const int kcut = cut ? kCutBits : kNoCutBits;
 #define UG_BWD_NW(W, H, NW)                                                                                     \
   hipLaunchKernelGGL((k_accum_bwd<W, H, NW>), grid, dim3(64 * NW), 0, s, tile_org, tile_start, skey, srec,      \
                      emitted, rec_koff, run_koff, recs, pint, tile_plane, image, second, dsave, scale,          \
-                     loss_part, p4, kcut, tile_bits, num_tiles, nsplit)
+                     loss_part, p4, kcut, tile_bits, num_tiles, nsplit, min_deal, twice, chunk)
 #define UG_BWD(W, H)                                                                                            \
   if (tile_w == W && tile_h == H) {                                                                             \
     if (one)                                                                                                    \
