@@ -930,11 +930,20 @@ __device__ __forceinline__ PlaneT<float> plane_from_lds(const float* d) {
 // How a record's partials are added (always in emission order, so all three
 // give the same bits):
 //  - COOP, launches of up to kCoopBlocks waves of records: a block per 64
-//    records, whose four waves bring their keys through LDS and add them eight
-//    lanes to a record.  Few waves have the chip to themselves and the time is
-//    the longest one's: 9 K records with 90 K keys, some with hundreds each,
-//    29 us with a lane walking its record's keys, 15 here; at 79 K records with
-//    two keys each both take 9.5.
+//    records, eight lanes to a record, one value each.  Few waves have the
+//    chip to themselves and the time is the longest one's.  The block brings
+//    its keys through LDS, 256 at a time: 9 K records with 90 K keys, some with
+//    hundreds each, 29 us with a lane walking its record's keys, 12.5 here.
+//    Where that takes many rounds and the records' lengths are alike (the
+//    longest's kCoopEven times or more in the block), it would leave all but a
+//    group or two waiting, and each group reads its own records' keys instead,
+//    eight in flight: 3,840 records of 256 keys 68 us a lane each, 184 staged,
+//    34 so; 24,000 of 100 keys 33, 40 and 20; 400 of 13,375 keys 5.1 ms, 9.2
+//    and 1.8.  (A round of 256 keys takes 2.7 us if they are one record's and
+//    under 1 if they are ten's; eight keys of every group 1.1, more out of cold
+//    caches.  So it takes kCoopEvenKeys keys in the block: with a quarter of
+//    that line the 9 K records above are 3 us slower on new inputs, with none
+//    79 K records of two keys 0.6.)
 //  - kStagedKeys or more keys per record on average: the wave brings its keys
 //    through LDS, loaded side by side while the ones before are added, a lane
 //    per record.  25M keys of 2.1M records 138 us (190 with each lane reading
@@ -946,6 +955,7 @@ __device__ __forceinline__ PlaneT<float> plane_from_lds(const float* d) {
 // segmented scan) and the round trips before them: 16M records 410 us with
 // exact divisions and the scan over LDS shuffles.
 constexpr uint32_t kCoopBlocks = 2048;
+constexpr uint32_t kCoopEven = 10, kCoopEvenKeys = 4096;
 constexpr uint32_t kStagedKeys = 3;
 
 // Adds to every value that of the lane the DPP control names, where that lane
@@ -992,8 +1002,7 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
   uint32_t w = COOP ? blockIdx.x : blockIdx.x * 4u + (uint32_t)wave;
   for (; w < nw; w += COOP ? gridDim.x : gridDim.x * 4u) {
     if (COOP) {
-      // 256 keys at a time go through LDS; eight neighbouring lanes add a
-      // record's keys, one value each, in order
+      // eight neighbouring lanes add a record's keys, one value each, in order
       const uint32_t rb = w * 64u;
       const uint32_t ka = rec_koff[rb], kb = rec_koff[min(rb + 64u, nrec)];
       const int fq = (int)(threadIdx.x & 7u), q0 = (int)(threadIdx.x >> 3);
@@ -1005,32 +1014,55 @@ __global__ __launch_bounds__(256) void k_record_adjoint(ug_gaussians g, const Pl
         qa[h] = rec_koff[rq];
         qz[h] = rq < nrec ? rec_koff[rq + 1] : qa[h];
       }
+      // the first chunk, in flight while the form is decided
       const float4* p4 = partial + 2 * (size_t)ka;
       const uint32_t n4 = 2u * (kb - ka);
       float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
       if (threadIdx.x < n4) x = p4[threadIdx.x];
       if (threadIdx.x + 256u < n4) y = p4[threadIdx.x + 256u];
-      for (uint32_t kc = ka; kc < kb; kc += 256) {
-        __syncthreads();  // the chunk before, and the block's sums before, are read
-        s_key[threadIdx.x] = x;
-        s_key[threadIdx.x + 256] = y;
-        __syncthreads();
-        const uint32_t nx = 2u * (kc + 256u - ka) + threadIdx.x;
-        if (nx < n4) x = p4[nx];
-        if (nx + 256u < n4) y = p4[nx + 256u];
-        const float* sk = reinterpret_cast<const float*>(s_key);
+      bool even = false;  // uniform over the block
+      if (kb - ka > kCoopEvenKeys) {
+        const uint32_t rm = min(rb + (uint32_t)lane, nrec), len = rm < nrec ? rec_koff[rm + 1] - rec_koff[rm] : 0u;
+        const uint32_t longest = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(len), 63);
+        even = (uint64_t)(kb - ka) > (uint64_t)kCoopEven * longest;
+      }
+      if (even) {
+        // each group reads its records' keys itself, eight at a time (an add
+        // of zero behind the last)
+        const float* p = reinterpret_cast<const float*>(partial) + fq;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const uint32_t ke = min(qz[h], kc + 256u);
-          uint32_t k = max(qa[h], kc);
-          for (; k + 8u <= ke; k += 8) {
+          for (uint32_t k = qa[h]; k < qz[h]; k += 8) {
             float t[8];
 #pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) t[u] = sk[8u * (k + u - kc) + (uint32_t)fq];
+            for (uint32_t u = 0; u < 8; ++u) t[u] = p[8 * (size_t)min(k + u, qz[h] - 1u)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc[h] += t[u];
+            for (uint32_t u = 0; u < 8; ++u) acc[h] += k + u < qz[h] ? t[u] : 0.f;
           }
-          for (; k < ke; ++k) acc[h] += sk[8u * (k - kc) + (uint32_t)fq];
+        }
+      } else {  // 256 keys at a time through LDS
+        for (uint32_t kc = ka; kc < kb; kc += 256) {
+          __syncthreads();  // the chunk before, and the block's sums before, are read
+          s_key[threadIdx.x] = x;
+          s_key[threadIdx.x + 256] = y;
+          __syncthreads();
+          const uint32_t nx = 2u * (kc + 256u - ka) + threadIdx.x;
+          if (nx < n4) x = p4[nx];
+          if (nx + 256u < n4) y = p4[nx + 256u];
+          const float* sk = reinterpret_cast<const float*>(s_key);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t ke = min(qz[h], kc + 256u);
+            uint32_t k = max(qa[h], kc);
+            for (; k + 8u <= ke; k += 8) {
+              float t[8];
+#pragma unroll
+              for (uint32_t u = 0; u < 8; ++u) t[u] = sk[8u * (k + u - kc) + (uint32_t)fq];
+#pragma unroll
+              for (int u = 0; u < 8; ++u) acc[h] += t[u];
+            }
+            for (; k < ke; ++k) acc[h] += sk[8u * (k - kc) + (uint32_t)fq];
+          }
         }
       }
       __syncthreads();
