@@ -118,7 +118,7 @@ struct RecAcc {
 static_assert(sizeof(RecAcc) == 32, "RecAcc layout");
 
 // Integer part of the record: conic centre base pixel, the run of records it
-// belongs to (kRuns per record block, each built by one wave) and its keys'
+// belongs to (up to kRuns per record block, each built by one wave) and its keys'
 // offset among that run's keys, and the tile rectangle.
 constexpr uint32_t kRuns = 8;
 struct RecGeo {

@@ -479,6 +479,13 @@ __device__ __forceinline__ uint32_t record_rpb_dev(uint32_t nrec, uint32_t grid)
   return (per < 1u ? 1u : per) * 256u;
 }
 
+// Records per run: whole waves of 64, in up to kRuns runs per block (four at 256
+// records per block: an eighth of a block, 32, left half of every wave's lanes
+// idle up to 524,288 records).
+__device__ __forceinline__ uint32_t record_run_dev(uint32_t rpb) {
+  return (rpb / kRuns + 63u) & ~63u;
+}
+
 // What the emission's items need of a record, in LDS (80 bytes, read 16 at a
 // time).
 struct EmitRec {
@@ -676,7 +683,7 @@ __global__ __launch_bounds__(STAGE ? 512 : 256, STAGE ? 4 : 3) void k_record(ug_
   // A wave builds whole runs, so a record's key offset within its run needs
   // no other wave (a barrier per round for offsets within the block made the
   // kernel 25% slower).
-  const uint32_t len = rpb / kRuns;
+  const uint32_t len = record_run_dev(rpb);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (uint32_t run = (uint32_t)wave; run < kRuns; run += NT / 64) {
     const uint32_t run_end = min(r_begin + (run + 1u) * len, r_end);
@@ -846,7 +853,7 @@ __global__ __launch_bounds__(256) void k_emit(const PlaneInt* __restrict__ pint,
   if (part != 0) return;
   __syncthreads();  // rec_koff of the block's records
   if (threadIdx.x < kRuns) {
-    const uint32_t rr = r_begin + threadIdx.x * (rpb / kRuns);
+    const uint32_t rr = r_begin + threadIdx.x * record_run_dev(rpb);
     if (rr < r_end) run_koff[blk * kRuns + threadIdx.x] = rec_koff[rr];
   }
   if (blk == nact - 1 && threadIdx.x == 0) {
