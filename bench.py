@@ -367,8 +367,9 @@ def main():
     g_sort = min(2048, max(1, -(-plan.key_capacity // chunk)))
     dbits = -(-plan_bits(plan) // passes)
     dslots = 256 if dbits <= 8 else max(1024, 1 << dbits)
-    sizes = dict(n=g.n, p=pl.p, r=n_rec, k=n_key, t=plan.num_tiles, m=int(pl.npix), passes=passes,
-                 w=(pl.p + 63) // 64, rows=params.box_mode == 2, g_sort=g_sort, dslots=dslots)
+    n_emit = emitted_keys(plan)
+    sizes = dict(n=g.n, p=pl.p, r=n_rec, t=plan.num_tiles, m=int(pl.npix), passes=passes,
+                 w=(pl.p + 63) // 64, g_sort=g_sort, dslots=dslots, **key_sizes(params, n_emit))
     kernels = {}
     cull_grouped = cull_searches_groups(pl, params, g.n)
     for nm, (ms, n) in stages.items():
@@ -434,8 +435,9 @@ def main():
         "in_support_pairs": n_eval,
         "records": n_rec,
         "keys": n_key,
+        "keys_emitted": n_emit,
         "evaluated_pairs": n_exec,
-        "tile_efficiency": n_eval / max(n_key * tpx, 1),
+        "tile_efficiency": n_eval / max(n_emit * tpx, 1),
         "subblock_efficiency": n_eval / max(n_exec, 1),
         "plain_per_plane": plain,
         "accumulate_kernels": acc,
@@ -751,6 +753,23 @@ def cull_searches_groups(pl, params, n) -> bool:
 def plan_bits(plan) -> int:
     t = max(plan.num_tiles, 2)
     return int(np.ceil(np.log2(t)))
+
+
+def emitted_keys(plan) -> int:
+    """Keys of the last render as emitted and sorted: with PAPER boxes fewer
+    than the count the plan reports, which is the rectangles'."""
+    from paper_2505_05643_amd import _lib
+    n = int(_lib.lib.ug_debug_keys(plan._h, plan._ws_ptr, None, None, None, None, 0, None))
+    _lib.check(min(n, 0), "ug_debug_keys")
+    return n
+
+
+def key_sizes(params, emitted: int) -> dict:
+    """What the binning's kernels move: the emitted keys, and whether the
+    records carry their row spans (ROWS, and PAPER outside the scatter)."""
+    from paper_2505_05643_amd._lib import UG_FLAG_SCATTER
+    return {"k": emitted,
+            "rows": params.box_mode == 2 or (params.box_mode == 0 and not params.flags & UG_FLAG_SCATTER)}
 
 
 def kernel_bytes(name, n, p, r, k, t, m, passes, w, rows, g_sort, dslots) -> int:
