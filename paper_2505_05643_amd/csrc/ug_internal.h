@@ -150,12 +150,6 @@ struct Rec {
 };
 static_assert(sizeof(Rec) == 64, "Rec layout");
 
-// Per-key partial derivatives written by the adjoint accumulate
-// (dt11, dt12, dt22, dfu, dfv, de0, dc, unused).
-struct Partial {
-  float v[8];
-};
-
 // ---------------------------------------------------------------- launch params
 struct RenderParams {
   float beta, chi2, bg_alpha, bg_color;
