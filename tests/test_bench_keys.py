@@ -4,6 +4,7 @@ that the plan reports, and every record binned by rows carries its spans."""
 import types
 
 import pytest
+import torch  # noqa: F401  (before the library: the process must map one HIP runtime, torch's)
 
 import bench
 from paper_2505_05643_amd._lib import UG_FLAG_SCATTER
