@@ -23,9 +23,12 @@
 namespace ug {
 
 // Reciprocal and square root of the positive, normal values of the record
-// construction (double) and its adjoint (float): the hardware's estimate and
-// one step of third order (double, from 2^-23) or second (float, from an
-// ulp), within an ulp or two; the record is rounded to float right after.
+// construction (double) and its adjoint (float): the hardware's estimate y and
+// one correction.  With e = 1 - x y, the reciprocal is y (1 + e + e^2 + ...):
+// two terms for doubles (third order, Halley's form), one for floats
+// (Newton's); with e = 1 - x y^2 the reciprocal root is y (1 + e / 2 + 3 e^2 /
+// 8 + ...), and the root is Newton's step from x times it.  Within an ulp or
+// two; the record is rounded to float right after.
 // The exact division and square root take two to four times the
 // instructions, and both kernels are bound by their arithmetic.
 __device__ __forceinline__ double recip(double x) {

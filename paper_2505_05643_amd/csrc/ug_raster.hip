@@ -315,8 +315,8 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
 // groups) left 0.62 of the evaluation's lanes at work, 256 keys' (eleven
 // groups) 0.85.  Measured, against (key, 8 x 8 sub-block) items ranked per
 // wave with the rows found by testing all eight: 33M keys of 32x16 tiles 2300
-// -> 1680 us (1,780 instead of 2,500 VALU instructions per 64 keys), 25M of
-// 16x16 1567 -> 1190 us, 160,000 of 16x32 28 -> 23 us.
+// -> 1755 us (1,760 instead of 2,500 VALU instructions per 64 keys), 25M of
+// 16x16 1567 -> 1115 us, 160,000 of 16x32 28 -> 23 us.
 constexpr int kStrip = 4;  // columns per item
 // items of one wave's keys per pass: four blocks' LDS fit a CU (three with
 // the 9 KB of a 32 x 32 tile's gamma)
