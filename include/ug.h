@@ -237,7 +237,9 @@ int ug_render_planes_backward(const ug_plan *plan, const ug_gaussians *g,
  * gradients equal ug_mse_grad followed by ug_render_planes_backward bit for
  * bit, with one launch and one pixel array less.  loss_dev (device float32,
  * may be NULL) receives the mean squared error, written by the last adjoint
- * kernel from per-block sums added in a fixed order (FP64).  Other
+ * kernel: each tile's squared differences are added in float32, then the
+ * tiles in FP64, both in an order that depends on the tile shape only (not on
+ * the capacities).  Other
  * arguments, errors and determinism as ug_render_planes_backward. */
 int ug_render_planes_backward_mse(const ug_plan *plan, const ug_gaussians *g,
                                   const ug_planes *planes, const float *image,

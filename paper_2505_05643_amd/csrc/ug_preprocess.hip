@@ -502,7 +502,7 @@ struct EmitRec {
 // memory.  A lane walking its record's rows took 418 us at 16.2M records with
 // 33.5M keys (398 so, 2.8 TB/s of slots read and keys written), 198 at 3.6M
 // needles with 11.8M keys (135), 123 at 2.1M with 25M (96); bound by its VALU
-// instructions (80% of the issue) beside those stores.  The tile shape is a
+// instructions (72 to 77% of the issue) beside those stores.  The tile shape is a
 // template argument: band loops and masks without run-time bounds gave 475 ->
 // 441 us at 69M keys.  nr = the lane's record's tile rows (0: no keys), key = the wave's
 // first key; an item's first key is the number of keys of the items before
@@ -646,10 +646,10 @@ __device__ __forceinline__ PlaneRec plane_rec_from_lds(const double* d, const in
 // registers allow)
 // instead of being gathered per record from memory.
 //
-// Bound by its FP64 arithmetic (740 VALU instructions per 64 records, 77% of
+// Bound by its FP64 arithmetic (760 VALU instructions per 64 records, 78% of
 // the issue).  16.2M records on 256 planes: 575 us with exact divisions and
 // roots, plane constants 24 doubles apart and every lane storing its own
-// slot; 567 without the exact forms, 548 without the bank conflicts too, 446
+// slot; 567 without the exact forms, 548 without the bank conflicts too, 443
 // with the slots stored through LDS (2.5 TB/s written).
 // BOX: the paper-literal box support (a template argument, so that its exact
 // divisions take none of the other records' registers, which are at the limit).

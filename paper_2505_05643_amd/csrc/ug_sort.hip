@@ -347,7 +347,8 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter_small(
 // Kernels around the scatter body: rounds of 2048 keys while the chunks are
 // about that long (more blocks, less LDS), of 4096 above, and from kLongChunk
 // keys per block on of 8192, whose runs of 32 keys per digit are whole lines.
-// Bound by the scattered writes' address path and the ranking.  Two passes:
+// Bound by the ranking (VALU 57% of the issue) between barriers and the
+// scattered writes (address unit 44% busy).  Two passes:
 // 33M keys 398 us with rounds of 4096 that moved keys and record ids one after
 // the other, 378 with both together and the next round's loads early, 327 with
 // 8192; 69M keys 553, 532, 464; 25M keys (15 K per block) 165, 151, 151; 11.8M
