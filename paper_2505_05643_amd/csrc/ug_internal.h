@@ -191,6 +191,21 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
   return x;
 }
 
+// Sum over the wave's lanes, in lane 63 (in rows of 16 lanes first, then over
+// the rows; the lanes a step names no lane for add zero).
+__device__ __forceinline__ float wave_total(float x) {
+#define UG_DPP_ADD(CTRL, ROWS) \
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, true));
+  UG_DPP_ADD(0x111, 0xf)  // row_shr:1
+  UG_DPP_ADD(0x112, 0xf)  // row_shr:2
+  UG_DPP_ADD(0x114, 0xf)  // row_shr:4
+  UG_DPP_ADD(0x118, 0xf)  // row_shr:8
+  UG_DPP_ADD(0x142, 0xa)  // lane 15 of a row to the next
+  UG_DPP_ADD(0x143, 0xc)  // lane 31 to the upper half
+#undef UG_DPP_ADD
+  return x;
+}
+
 // Inclusive prefix maximum over the wave's lanes.
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t x) {
   x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));
