@@ -946,11 +946,12 @@ __device__ __forceinline__ PlaneT<float> plane_from_lds(const float* d) {
 //    group or two waiting, and each group reads its own records' keys instead,
 //    eight in flight: 3,840 records of 256 keys 68 us a lane each, 184 staged,
 //    34 so; 24,000 of 100 keys 33, 40 and 20; 400 of 13,375 keys 5.1 ms, 9.2
-//    and 1.8.  (A round of 256 keys takes 2.7 us if they are one record's and
+//    and 1.9.  (A round of 256 keys takes 2.7 us if they are one record's and
 //    under 1 if they are ten's; eight keys of every group 1.1, more out of cold
 //    caches.  So it takes kCoopEvenKeys keys in the block: with a quarter of
 //    that line the 9 K records above are 3 us slower on new inputs, with none
-//    79 K records of two keys 0.6.)
+//    79 K records of two keys 0.6.  kCoopEven: at ten, 200,000 Gaussians on one
+//    plane of 4000 x 3000 with records of uneven lengths took 318 us, 263 so.)
 //  - kStagedKeys or more keys per record on average: the wave brings its keys
 //    through LDS, loaded side by side while the ones before are added, a lane
 //    per record.  25M keys of 2.1M records 138 us (190 with each lane reading
@@ -962,7 +963,7 @@ __device__ __forceinline__ PlaneT<float> plane_from_lds(const float* d) {
 // segmented scan) and the round trips before them: 16M records 410 us with
 // exact divisions and the scan over LDS shuffles.
 constexpr uint32_t kCoopBlocks = 2048;
-constexpr uint32_t kCoopEven = 10, kCoopEvenKeys = 4096;
+constexpr uint32_t kCoopEven = 24, kCoopEvenKeys = 4096;
 constexpr uint32_t kStagedKeys = 3;
 
 // Adds to every value that of the lane the DPP control names, where that lane
