@@ -288,11 +288,11 @@ __global__ __launch_bounds__(64 * (TH / kSubBlock) * SPLIT) void k_accum_fwd(
 // dense tile's walk alone set the time: half of 100,000 Gaussians in a
 // fiftieth of the volume, 64 planes of 256 x 256, 6.88 ms per step, 3.37 so;
 // shells and a core in 160 x 160 planes (50,000 on 16 planes, one wave per
-// tile) 217 and 160 us.  Where no tile has more the blocks for the rest cost
-// nothing that was measured.  Each wave has a contiguous
-// share of its block's keys and takes up to 64 of them per pass.  The block
-// forms the tile's per-pixel inputs, gamma = dL/dc_hat / D and gamma c_hat, in LDS (every
-// row the evaluation reads comes from there); the loss gradient takes the
+// tile) 217 and 160 us.  Where no tile has more it costs 0.1 to 0.4% of a step.
+// Each wave has a contiguous share of its block's keys and takes up to 64 of
+// them per pass.  The block forms the tile's per-pixel inputs, gamma =
+// dL/dc_hat / D and gamma c_hat, in LDS (every row the evaluation reads comes
+// from there); the loss gradient takes the
 // float operations of the separate kernel.  A kernel of its own that wrote
 // them tile by tile took 61 us and this one 14 us less at 16.8M pixels (step
 // 4948 -> 4885 us); at 16 planes of 160 x 160 it was a launch more (99 -> 96 us).
